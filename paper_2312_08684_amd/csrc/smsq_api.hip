@@ -188,11 +188,11 @@ smsq_status_t launch_step_kd(const StepArgs<T> &a, int batch, hipStream_t s)
 // (batched plans run it at any size).
 constexpr int kMfmaMinParticles = 32;
 
-bool use_mfma(int n, int n_prev, int step_kernel)
+bool use_mfma(int d, int n, int n_prev, int step_kernel)
 {
     if (step_kernel == SMSQ_STEP_VALU) return false;
-    const MfmaLds L(n, n_prev);
-    const bool fits = L.npad <= kMaxParticles && L.total <= kLdsLimit;
+    const MfmaLds L(d <= 3, n, n_prev);
+    const bool fits = L.npad <= kMaxParticles && L.total <= MfmaLds::kMfmaLdsBytes;
     if (step_kernel == SMSQ_STEP_MFMA) return fits;
     return fits && n >= kMfmaMinParticles;
 }
@@ -205,17 +205,17 @@ smsq_status_t launch_mfma_split(const StepArgs<float> &a, int batch, hipStream_t
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [&] { attr_err = allow_big_lds(fn); });
     if (attr_err != hipSuccess) return SMSQ_ERR_HIP;
-    const MfmaLds L(a.n, a.n_prev);
+    const MfmaLds L(D <= 3, a.n, a.n_prev);
     hipLaunchKernelGGL(fn, dim3(batch), dim3(L.nwaves * kWave), (size_t)L.total, s, a);
     return hipGetLastError() == hipSuccess ? SMSQ_OK : SMSQ_ERR_HIP;
 }
 
-// Fewer 64-particle tasks than 16 waves: the split instantiation fills the
-// workgroup with waves that share each task's sources.
+// Up to 16 32-particle tasks: the split instantiation, whose waves share each
+// task's sources.
 template <int KIND, int D>
 smsq_status_t launch_mfma_kd(const StepArgs<float> &a, int batch, hipStream_t s)
 {
-    return MfmaLds(a.n, a.n_prev).ns_max > 1 ? launch_mfma_split<KIND, D, true>(a, batch, s)
+    return MfmaLds(D <= 3, a.n, a.n_prev).split ? launch_mfma_split<KIND, D, true>(a, batch, s)
                                               : launch_mfma_split<KIND, D, false>(a, batch, s);
 }
 
@@ -278,7 +278,7 @@ smsq_status_t launch_step<float>(const smsq_model_desc_t &d, const StepArgs<floa
     if (use_wave(a.n, a.n_prev, d.d, true, step_kernel)) return launch_wave<float>(d, a, batch, s);
     // the matrix-core kernel runs the RBF kernel on states of up to 7
     // dimensions; IMQ, Matern and the 14-D model take the vector-ALU kernel
-    if (a.kernel == 0 && d.d <= 7 && use_mfma(a.n, a.n_prev, step_kernel)) {
+    if (a.kernel == 0 && d.d <= 7 && use_mfma(d.d, a.n, a.n_prev, step_kernel)) {
         switch (d.kind) {
         case SMSQ_MODEL_GROWTH1D: return launch_mfma_kd<GROWTH1D, 1>(a, batch, s);
         case SMSQ_MODEL_RANGE2D: return launch_mfma_kd<RANGE2D, 2>(a, batch, s);
@@ -538,7 +538,7 @@ smsq_status_t launch_coop_kd(const StepArgs<float> &a, int batch, const CoopArgs
     std::call_once(once, [&] { attr_err = allow_big_lds(fn); });
     if (attr_err != hipSuccess) return SMSQ_ERR_HIP;
     const int npad = (a.n + 63) / 64 * 64;
-    const MfmaLds L(a.n, a.n_prev, kMaxWaves, npad / 64 / c.G, kCoopWinCap);
+    const MfmaLds L(D <= 3, a.n, a.n_prev, kMaxWaves, npad / c.G);
     hipLaunchKernelGGL(k_coop_reset, dim3((batch + 63) / 64), dim3(64), 0, s, c.base, c.stride, batch);
     StepArgs<float> aa = a;
     CoopArgs cc = c;
@@ -674,13 +674,12 @@ int coop_groups(smsq_dtype_t dt, const smsq_model_desc_t &d, int batch, int n, b
 {
     if (dt != SMSQ_F32 || !coop_family(d.kind) || d.d > 7) return 1;
     const int ntasks = (n + 63) / 64;
-    const MfmaLds L1(n, n);
-    if (L1.npad > kMaxParticles) return 1;
+    if (ntasks * 64 > kMaxParticles) return 1;
     if (!force && (n < kCoopMinParticles || 4L * batch > device_cus())) return 1;
     int G = 1;
     while (2 * G <= ntasks && ntasks % (2 * G) == 0 && (long)batch * 2 * G <= device_cus()) G *= 2;
-    if (G > 1 && (MfmaLds(n, n, kMaxWaves, ntasks / G, kCoopWinCap).total > kLdsLimit ||
-                  MfmaLds(n, 1, kMaxWaves, ntasks / G, kCoopWinCap).total > kLdsLimit))
+    if (G > 1 && (MfmaLds(d.d <= 3, n, n, kMaxWaves, ntasks * 64 / G).total > MfmaLds::kMfmaLdsBytes ||
+                  MfmaLds(d.d <= 3, n, 1, kMaxWaves, ntasks * 64 / G).total > MfmaLds::kMfmaLdsBytes))
         return 1;
     return G;
 }
@@ -1321,11 +1320,11 @@ smsq_status_t smsq_batch_plan_create(const smsq_model_t *models, const smsq_svgd
             return SMSQ_ERR_INVALID;
         const smsq_model_desc_t &d = models[q.model]->desc;
         if (batch_code(d) < 0) return SMSQ_ERR_UNSUPPORTED;
-        const MfmaLds L1(q.n, q.n), L2(q.n, 1);
-        if (L1.npad > kMaxParticles || L1.total > kLdsLimit - kBatchStaticLds ||
-            L2.total > kLdsLimit - kBatchStaticLds)
-            return SMSQ_ERR_UNSUPPORTED;
-        lds = std::max(lds, std::max(L1.total, L2.total));
+        if (q.n > kMaxParticles) return SMSQ_ERR_UNSUPPORTED;
+        // either workgroup shape, first and later steps
+        for (int waves : {8, 16})
+            for (int np : {1, q.n}) lds = std::max(lds, MfmaLds(d.d <= 3, q.n, np, waves).total);
+        if (lds > kLdsLimit - kBatchStaticLds) return SMSQ_ERR_UNSUPPORTED;
         max_n = std::max(max_n, q.n);
         T_max = std::max(T_max, q.T);
         n_parts += (size_t)q.T * q.n * d.d;

@@ -1,30 +1,46 @@
-// FP32 step kernel on the matrix cores (v_mfma_f32_16x16x4f32 and
-// v_mfma_f32_4x4x1f32, wave64).
+// FP32 step kernel on the matrix cores (v_mfma_f32_16x16x32_bf16 and
+// v_mfma_f32_16x16x32_f16, wave64).
 //
 // Same computation as k_step (one workgroup per sequence, state in LDS), with
 // the pairwise work of every SVGD iteration (eq. SVGD_newupdate) on MFMA:
-//   * bandwidth: the squared distances D_ik = n_i + n_k - 2 x_i . x_k come
-//     from 16x16 Gram tiles; the exact lower median is found by one pass that
-//     counts the distances below a window predicted from the previous
+//   * bandwidth: half the squared distances, n_i / 2 + n_k / 2 - x_i . x_k,
+//     come from 16x16 Gram tiles; the exact lower median is found by one pass
+//     that counts the distances below a window predicted from the previous
 //     iterations' medians and keeps (and bins) those inside it, then a rank
 //     among the kept values of the median's bin (radix selections as
 //     fallbacks);
 //   * scores: the transition-mixture softmax over the previous particles,
 //     logit_kj = 2 mh_j . xh_k + c_j - |mh_j|^2 (log2 units; the common
-//     -|xh_k|^2 drops out), as 16x16 logit tiles [xh_k, 1] . [2 mh_j, c'_j],
-//     a per-particle reference maximum raised only when a tile exceeds it by
-//     2^64, exp2 on the VALU, and the weighted sums sum_j e_kj [2 mh_j, 1]
-//     accumulated by MFMA;
-//   * Stein direction: Gram tiles give the kernel argument
-//     2 beta x_k . x_i - beta n_k (the norm rides in the free eighth
-//     K-column), kappa_ik = exp2(that - beta n_i) with beta = log2(e) / h,
-//     and sum_k kappa_ik [s_k - (2/h) x_k, 1] is accumulated by MFMA.
+//     -|xh_k|^2 drops out), as 16x16 tiles relative to a per-particle
+//     reference, exp2 on the VALU, and the weighted sums
+//     sum_j e_kj [2 mh_j, 1] accumulated by MFMA;
+//   * Stein direction: tiles of the exponent of kappa,
+//     2 beta x_k . x_i - beta n_k - beta n_i with beta = log2(e) / h, exp2,
+//     and sum_k kappa_ik [s_k - (2/h) x_k, 1] accumulated by MFMA.
 // Particles are stored centred on the mean of the previous step's transition
 // means, which keeps |x|^2 small next to the squared distances in FP32.
 //
-// Operand layouts of v_mfma_f32_16x16x4f32 (checked on gfx950): lane l gives
-// A[l % 16][l / 16] and B[l / 16][l % 16]; result register r of lane l is
-// D[4 (l / 16) + r][l % 16].
+// FP32 operands on the 16-bit units.  The FP32 MFMA of gfx950 occupies the
+// vector ALU (34 cycles per 16x16x4 product, nothing else issues on the SIMD
+// meanwhile), the 16-bit one runs beside it (a 16x16x32 product takes 6 to 8
+// cycles of the ALU's time), so every contraction runs on the latter with its
+// FP32 operands split:
+//   * logits, Gram tiles and distances: each operand is cut (truncation) into
+//     three bf16 pieces h + m + l of 8 bits, which hold all 24 bits exactly,
+//     and the products hh, hm, mh, mm, hl, lh (and ml where there is room)
+//     fill the K-slots; what is left out is below 2^-24 of |a||b|;
+//   * weighted sums: the exponentials and the vectors they weigh are cut
+//     (round to nearest) into two f16 pieces, 2^-24 of the value, all four
+//     products kept; the exponentials are held near 2^10 (softmax) or at most
+//     2^14 (kappa), and the vectors scaled by a power of two, so that the
+//     pieces stay above the subnormals.
+// Products of pieces are exact in FP32 and the sums accumulate in FP32.
+// Measured against 64-bit values the results are at or below the error of
+// the FP32 MFMA's.
+//
+// Operand layouts of the 16x16x32 MFMA (checked on gfx950): lane l gives
+// A[l % 16][8 (l / 16) + j] and B[8 (l / 16) + j][l % 16], j = 0..7; result
+// register r of lane l is D[4 (l / 16) + r][l % 16].
 #pragma once
 
 #include "smsq_kernels.hpp"
@@ -32,10 +48,54 @@
 namespace smsq {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c)
+__device__ __forceinline__ f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c)
 {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+                                                   0, 0);
+}
+
+__device__ __forceinline__ f32x4 mfma_f16(u32x4 a, u32x4 b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0,
+                                                  0);
+}
+
+// the three bf16 pieces of two floats, packed (first float in the low half)
+struct Pieces3 {
+    uint32_t h, m, l;
+};
+__device__ __forceinline__ Pieces3 split3(float a, float b)
+{
+    const uint32_t ah = __float_as_uint(a) & 0xffff0000u, bh = __float_as_uint(b) & 0xffff0000u;
+    const float ar = a - __uint_as_float(ah), br = b - __uint_as_float(bh);
+    const uint32_t am = __float_as_uint(ar) & 0xffff0000u, bm = __float_as_uint(br) & 0xffff0000u;
+    const float al = ar - __uint_as_float(am), bl = br - __uint_as_float(bm);
+    // the high halves of two words (0x07060302: bytes 2, 3 of the second
+    // argument, then of the first)
+    return Pieces3{__builtin_amdgcn_perm(bh, ah, 0x07060302u), __builtin_amdgcn_perm(bm, am, 0x07060302u),
+                   __builtin_amdgcn_perm(__float_as_uint(bl), __float_as_uint(al), 0x07060302u)};
+}
+// low / high bf16 of a packed word as a float
+__device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+
+// the two f16 pieces of two floats, packed.  `neg1` is -1 held in a register
+// the compiler cannot see through, so that the residuals stay mixed-precision
+// fused multiply-adds into FP32 (v_fma_mix_f32, 4 cycles each, and one packed
+// conversion; writing f16 halves with v_fma_mixlo / mixhi takes 8 cycles each).
+__device__ __forceinline__ void split_f16(float a, float b, float neg1, uint32_t &hi, uint32_t &lo)
+{
+    const f16x2 h = __builtin_convertvector(f32x2{a, b}, f16x2);
+    const float ra = __builtin_fmaf((float)h[0], neg1, a), rb = __builtin_fmaf((float)h[1], neg1, b);
+    hi = __builtin_bit_cast(uint32_t, h);
+    lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{ra, rb}, f16x2));
 }
 
 __device__ __forceinline__ float fmax_(float a, float b) { return a > b ? a : b; }
@@ -51,14 +111,31 @@ __device__ __forceinline__ uint32_t lanes_below(unsigned long long mask)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// Lanes of the diagonal 16x16 distance tile that hold a pair k > i in
-// result register r (k = 4 (l / 16) + r, i = l % 16).
-__host__ __device__ constexpr unsigned long long diag_lanes(int r)
+// Reductions over a wave's lanes without LDS: rotations within the 16-lane
+// rows (DPP), then across the rows; every lane gets the result.
+template <int N> __device__ __forceinline__ uint32_t row_rotate(uint32_t v)
 {
-    unsigned long long m = 0;
-    for (int l = 0; l < 64; ++l)
-        if (4 * (l >> 4) + r > (l & 15)) m |= 1ull << l;
-    return m;
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x120 + N, 0xf, 0xf, false);
+}
+template <typename Op> __device__ __forceinline__ uint32_t wave_reduce(uint32_t v, Op op)
+{
+    v = op(v, row_rotate<8>(v));
+    v = op(v, row_rotate<4>(v));
+    v = op(v, row_rotate<2>(v));
+    v = op(v, row_rotate<1>(v));
+    auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = op(a[0], a[1]);
+    a = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return op(a[0], a[1]);
+}
+// largest of non-negative values (as bit patterns; a NaN counts as larger)
+__device__ __forceinline__ float wave_max_abs(float v)
+{
+    return __uint_as_float(wave_reduce(__float_as_uint(v), [](uint32_t a, uint32_t b) { return a > b ? a : b; }));
+}
+__device__ __forceinline__ uint32_t wave_count(uint32_t v)
+{
+    return wave_reduce(v, [](uint32_t a, uint32_t b) { return a + b; });
 }
 
 // max over the four 16-lane groups that hold the same column (lanes l, l^16,
@@ -74,203 +151,477 @@ __device__ __forceinline__ float group_max4(float v)
 // Up to sixteen waves per workgroup (four per SIMD), one 64-particle task
 // each at the largest size.
 constexpr int kMaxWaves = 16;
-constexpr int kTilesPerWave = 4;  // register blocking: 64 particles per wave task
 constexpr int kMaxParticles = 1024;  // largest sequence the kernel takes
 // A workgroup of W waves takes up to W * TS tasks (TS task slots per wave).
-constexpr int kVtRows = 9;        // rows of the transition-mean table: 2 mh (7), 1, c'
-constexpr int kWinCap = 8192;     // capacity of the median window buffer (floats)
-constexpr int kWinRegion = kWinCap / kMaxWaves; // per-wave share of the window buffer
-constexpr int kWinTarget = 512;   // aimed-for number of distances in the window
-// log2 headroom before the softmax reference moves: a tile's exponentials
-// stay at most 2^64 and a row's sums of up to 1024 of them far below the
-// FP32 range, while a column's reference seldom moves after its first tile
-constexpr float kRescaleGap = 64.f;
-constexpr int kProgSlot = 48;      // first of the 16 wave-progress words in the reduction slots
-constexpr int kPartStride = 9;     // floats per particle in a split's partial sums (8 rows + 1)
+// Exponentials of the softmax are taken relative to a reference 10 below (in
+// log2 units) the particle's log-sum-exp at the previous iteration, so they
+// sum to about 2^10.  A pass whose sums leave [2^5, inf) repeats with the
+// reference at the largest logit: above 2^16 an f16 piece overflows (and
+// turns the sum into a NaN), and below 2^5 the smallest pieces, of absolute
+// error 2^-25, would show beside FP32 rounding.
+constexpr float kRefShift = 10.f;
+constexpr float kRefMinSum = 32.f;
+constexpr float kKapShift = 14.f;  // kappa is held times 2^14 (same reason)
+constexpr float kNoSource = -1e30f;  // logit of a source that takes no part (its exponential is 0)
+// Half the squared norm of a pad particle: its distances are never the median
+// and its kernel values are 0 (one bf16 piece, so no infinity minus infinity)
+constexpr float kPadHalfNorm = 8.507059173023462e37f;  // 2^126
 
 // LDS byte layout of the MFMA step workgroup, and how its waves share the
-// pairwise work.  With fewer 64-particle tasks than waves (N below 1024 for
-// 16 waves) the source tiles of each task are split among several waves
-// ("splits"): a wave handles task w % ntasks over the split w / ntasks of
-// the source range, leaves partial sums in LDS, and the partials are merged
-// in split order (the same result whatever the timing).  ns_sc / ns_st are
-// the splits of the score and Stein passes (at most the source tiles each
+// pairwise work.  Large sequences (more 32-particle tasks than waves): each
+// wave takes whole tasks of 64 targets over all sources.  The others (split):
+// tasks of 32 targets, whose 32-source blocks are split among several waves
+// where there are waves left: a wave handles task w % ntasks over the split
+// w / ntasks of the source range and leaves partial sums in LDS, merged in
+// split order (the same result whatever the timing).  32-target tasks halve
+// the longest wave's share at up to 192 particles and the splits to merge
+// above (64-target tasks: 0.81 to 0.91 of today's rate at 48 and 64
+// particles, where they left two waves; equal work at 384 and 512).  ns_sc /
+// ns_st are the splits of the score and Stein passes (at most the blocks each
 // pass has); nwaves the waves a launch of this shape uses.
-// A workgroup of the multi-workgroup mode owns tasks_local of the tasks (its
-// targets) and holds every particle; win_cap is its window buffer's capacity.
+// A workgroup of the multi-workgroup mode owns targets_local particles as its
+// targets and holds every particle.
+//
+// k4 (d <= 3): rows of four components (three coordinates and the last) in
+// place of eight.  Tables, with R = 4 or 8 components:
+//   off_x   three planes [npad][R] bf16, the pieces of [x, |x|^2 / 2]
+//   off_vt  three planes [nppad][R] bf16, the pieces of [2 mh, c']
+//   off_v   [npad / 32][2 R][32] f16: pieces of the scaled [v, 1] (Stein sums)
+//   off_ms  [nppad / 32][2 R][32] f16: pieces of the scaled [2 mh, 1]
+//   off_b   operands of the workgroup's targets, in turn of the score and the
+//           Stein pass, where several waves share a task (each would form them
+//           again: 250 to 550 instructions a pass, as much as the pass itself
+//           at 256 particles)
+// The two sums' tables share one region where LDS is short (1024 particles of
+// d >= 4): the transition one is then rebuilt each iteration.
 struct MfmaLds {
-    long off_x, off_s, off_m, off_phip, off_scr, off_win, off_z, off_mask, off_red, off_part, total;
-    int npad, nppad, nwaves, ntasks, ns_sc, ns_st, ns_max, win_cap, win_region;
-    __host__ __device__ MfmaLds(int n, int n_prev, int waves = kMaxWaves, int tasks_local = 0,
-                                int win = kWinCap)
+    long off_x, off_vt, off_v, off_ms, off_b, off_win, off_z, off_mask, off_red, off_ones, off_part, total;
+    int npad, nppad, nwaves, task, ntasks, ns_sc, ns_st, ns_max, win_cap;
+    bool split, ms_shared, b_table;
+    __host__ __device__ MfmaLds(bool k4, int n, int n_prev, int waves = kMaxWaves, int targets_local = 0)
     {
         npad = (n + 63) / 64 * 64;
-        nppad = (n_prev + 15) / 16 * 16;
-        ntasks = tasks_local > 0 ? tasks_local : npad / 64;
-        win_cap = win;
-        win_region = win / kMaxWaves;
-        if (ntasks >= waves) {
-            ns_sc = ns_st = ns_max = 1;
-            nwaves = waves;
-        } else {
+        nppad = (n_prev + 31) / 32 * 32;
+        const int targets = targets_local > 0 ? targets_local : npad;
+        split = targets / 32 <= waves;
+        task = split ? 32 : 64;
+        ntasks = targets / task;
+        ns_sc = ns_st = ns_max = 1;
+        nwaves = waves;
+        if (split) {
             const int cap = waves / ntasks;
-            ns_sc = cap < nppad / 16 ? cap : nppad / 16;
-            ns_st = cap < npad / 16 ? cap : npad / 16;
+            ns_sc = cap < nppad / 32 ? cap : nppad / 32;
+            ns_st = cap < npad / 32 ? cap : npad / 32;
             ns_max = ns_sc > ns_st ? ns_sc : ns_st;
-            nwaves = ntasks * ns_max;
+            // (from 256 particles on the idle waves take part in the median's pass)
+            if (npad < 256) nwaves = ntasks * ns_max;
+        }
+        const long row = k4 ? 8 : 16;  // bytes of a table row
+        // partial sums of the splits: [ns_max][targets][R + 1] floats
+        const long part = split ? align16((long)ns_max * targets * (k4 ? 5 : 9) * 4) : 0;
+        // the multi-workgroup mode keeps them over the sums' tables
+        const bool alias = targets_local > 0;
+        const long vb = (long)npad * 2 * row, mb = (long)nppad * 2 * row;
+        // target operands: four planes (k4: three) of 16 bytes per target
+        const long bb = (long)targets * (k4 ? 48 : 64);
+        const long fixed = 3 * row * (npad + nppad) + 128 + 64 + 512 + 16 + (alias ? 0 : part) + 1024;
+        // what fits, in the order of what it saves: target operands in a table
+        // (several waves share each task), the sums' tables apart (else the
+        // transition one is rebuilt each iteration), a window buffer of 4096
+        // values (else 2048; also the histogram of a range or radix pass)
+        long sums = 0;
+        for (int choice = 0; choice < 8; ++choice) {
+            b_table = !(choice & 4);
+            ms_shared = alias || (choice & 2);
+            win_cap = alias || (choice & 1) ? 2048 : 4096;
+            if (b_table && !split) continue;
+            sums = ms_shared ? (vb > mb ? vb : mb) : vb + mb;
+            if (alias && sums < part) sums = part;
+            if (fixed + sums + (b_table ? bb : 0) + 4L * win_cap <= kMfmaLdsBytes) break;
         }
         long o = 0;
-        off_x = o; o += align16((long)npad * 8 * 4);
-        off_s = o; o += align16((long)npad * 8 * 4);
-        off_m = o; o += align16((long)kVtRows * nppad * 4);
-        off_phip = o; o += align16((long)nppad * 4);
-        off_scr = o; o += (long)kBins * 4;  // the radix-selection histogram
-        off_win = o; o += (long)(win_cap + 256) * 4;       // window buffer + its histogram
-        off_z = o; o += align16((long)kMaxObs * 4);
+        off_x = o; o += 3 * row * npad;
+        off_vt = o; o += 3 * row * nppad;
+        off_v = o;
+        off_ms = ms_shared ? o : o + vb;
+        off_part = alias ? o : o + sums;
+        o += sums + (alias ? 0 : part);
+        off_b = o; o += b_table ? bb : 0;
+        off_win = o; o += 4L * win_cap + 1024;  // window buffer, bins of its selection
+        off_z = o; o += 128;
         off_mask = o; o += 64;
-        off_red = o; o += 512;  // uint slots 0..63 (48..63: wave progress), float slots from byte 256
-        // partial sums of the splits: [ns_max][ntasks * 64][9] floats
-        off_part = o; o += ns_max > 1 ? align16((long)ns_max * ntasks * 64 * kPartStride * 4) : 0;
+        off_red = o; o += 512;  // uint slots 0..63, float slots from byte 256
+        off_ones = o; o += 16;
         total = o;
+    }
+    static constexpr long kMfmaLdsBytes = 160 * 1024 - 256;  // less the persistent kernels' static words
+};
+
+// A lane's 16-bit A operands of one table: rows are sources, K-slots the
+// piece products.  With eight components lane group g holds in the first MFMA
+// piece (h, h, m, m)[g] against the B pieces (h, m, h, m)[g], in the second
+// (h, l, 1, m)[g] against (l, h, constant, l)[g]; with four components the
+// one MFMA holds two products per group, (hh, hm | mh, mm | hl, lh |
+// constant).  The constant group carries the pieces of a per-target constant
+// against ones.
+template <bool K4> struct SourceRows {
+    uint32_t o0, o1, s1;
+    __device__ void init(long base, int rows, long ones, int g, int col)
+    {
+        if (K4) {
+            o0 = (uint32_t)(g == 3 ? ones : base + (long)(g == 1 ? rows * 8 : 0) + col * 8);
+            o1 = (uint32_t)(g == 3 ? ones + 8 : base + (long)g * rows * 8 + col * 8);
+            s1 = g == 3 ? 0u : 128u;
+        } else {
+            o0 = (uint32_t)(base + (long)(g >> 1) * rows * 16 + col * 16);
+            o1 = (uint32_t)(g == 2 ? ones : base + (long)(g == 0 ? 0 : g == 1 ? 2 : 1) * rows * 16 + col * 16);
+            s1 = g == 2 ? 0u : 256u;
+        }
+    }
+    __device__ __forceinline__ void load(const unsigned char *smem, int tile, u32x4 &a0, u32x4 &a1) const
+    {
+        if (K4) {
+            const u32x2 p = *(const u32x2 *)(smem + o0 + (uint32_t)tile * s1);
+            const u32x2 q = *(const u32x2 *)(smem + o1 + (uint32_t)tile * s1);
+            a0 = u32x4{p[0], p[1], q[0], q[1]};
+        } else {
+            a0 = *(const u32x4 *)(smem + o0 + (uint32_t)tile * 256u);
+            a1 = *(const u32x4 *)(smem + o1 + (uint32_t)tile * s1);
+        }
+    }
+    // moves the rows on by some tiles
+    __device__ __forceinline__ void skip(int tiles)
+    {
+        o0 += (uint32_t)tiles * (K4 ? s1 : 256u);
+        o1 += (uint32_t)tiles * s1;
+    }
+    static __device__ __forceinline__ f32x4 dot(u32x4 a0, u32x4 a1, u32x4 b0, u32x4 b1,
+                                                f32x4 c = f32x4{0.f, 0.f, 0.f, 0.f})
+    {
+        return K4 ? mfma_bf16(a0, b0, c) : mfma_bf16(a0, b0, mfma_bf16(a1, b1, c));
     }
 };
 
-// K-chunks of the distance and Gram tiles.  Eight K-rows (two MFMAs) hold
-// up to seven coordinates and the norm in row 7; with K4 (d <= 3) four
-// K-rows (one MFMA) hold up to three coordinates and the norm in row 3.
-// ka(g): the particle-row column that K-row g (of the first chunk) reads.
-template <bool K4> __device__ __forceinline__ int gram_col(int g) { return K4 && g == 3 ? 7 : g; }
+// bits of a where mask is set, of b elsewhere (lane masks are 0 or ~0; written
+// as bit operations so that no branch comes of it)
+__device__ __forceinline__ uint32_t pick(uint32_t mask, uint32_t a, uint32_t b) { return (mask & a) | (~mask & b); }
 
-// Visits the squared distances D_ik = n_i + n_k - 2 x_i . x_k of every pair
-// i < k from 16x16 MFMA Gram tiles: the A rows are the source particles with
-// their norm n_k in the last K-row (coordinates zero-padded), the B columns
-// are -2 x_i with a 1 in that row, and the accumulator starts at n_i, so
-// the tile holds the distances themselves.  Each wave takes whole rows of tiles
-// (target tile ib, source tiles kb >= ib) and issues the MFMAs of four source
-// tiles before using any result.  fn(Dv, diag) receives the four distances
-// of a lane for one tile (k = 16 kb + 4 g + r, i = 16 ib + col); in the
-// diagonal tile (diag true) only the lanes of diag_lanes(r) hold pairs k > i.
-// Pad particles have n = +inf, so their distances are +inf.  The median
-// window pass (TileWalker) computes every distance the same way.
-template <bool K4, typename Fn>
-__device__ __forceinline__ void for_each_distance(const float *X8, int npad, Fn &&fn, int vwave = -1, int nvwaves = 0)
+// B operands of a target: the packed pieces of its R components and its
+// constant, in the slots matching SourceRows.
+template <bool K4>
+__device__ __forceinline__ void target_operand(const uint32_t *h, const uint32_t *m, const uint32_t *l, float cst, int g,
+                                               u32x4 &b0, u32x4 &b1)
 {
-    constexpr int kBatch = 4;
-    const int lane = threadIdx.x & 63;
-    const int wave = nvwaves > 0 ? vwave : wave_id(), nwaves = nvwaves > 0 ? nvwaves : (int)(blockDim.x >> 6);
-    const int g = lane >> 4, col = lane & 15;
-    const int nt16 = npad / 16;
-    // Rows of tiles (target tile ib, source tiles kb >= ib) go to the waves in
-    // snake order, which gives every wave the same number of tiles when the
-    // row count is a multiple of 2 * nwaves.
-    for (int rr = 0;; ++rr) {
-        const int ib = (rr & 1) ? (rr + 1) * nwaves - 1 - wave : rr * nwaves + wave;
-        if (ib >= nt16) break;
-        const int i0 = ib * 16;
-        const float *xi = X8 + (long)(i0 + col) * 8;
-        const int ka = gram_col<K4>(g);
-        const float bi0 = K4 && g == 3 ? 1.f : -2.f * xi[g];
-        const float bi1 = g == 3 ? 1.f : -2.f * xi[4 + g];
-        const float nni = xi[7];
-        const f32x4 cn = {nni, nni, nni, nni};
-        fn(K4 ? mfma16(xi[ka], bi0, cn) : mfma16(xi[4 + g], bi1, mfma16(xi[g], bi0, cn)), true);
-        // A operands of a batch of source tiles; past the row's end a tile is
-        // repeated and its results are not used
-        float a0[kBatch], a1[kBatch];
-        auto load_batch = [&](int kb) {
+    const Pieces3 c = split3(cst, 0.f);
+    const uint32_t cc[2] = {c.h | (c.m << 16), c.l};
+    const uint32_t odd = 0u - (uint32_t)(g & 1), high = 0u - (uint32_t)(g >> 1);
+    if (K4) {
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const float *xk = X8 + (long)(min(kb + u, nt16 - 1) * 16 + col) * 8;
-                a0[u] = xk[ka];
-                a1[u] = K4 ? 0.f : xk[4 + g];
+        for (int q = 0; q < 2; ++q) {
+            b0[q] = pick(high, pick(odd, cc[q], l[q]), h[q]);
+            b0[2 + q] = pick(high, h[q] & ~odd, m[q]);
+        }
+    } else {
+        const uint32_t g1 = odd & ~high, g2 = high & ~odd;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            b0[q] = pick(odd, m[q], h[q]);
+            b1[q] = pick(g2, q < 2 ? cc[q < 2 ? q : 0] : 0u, pick(g1, h[q], l[q]));
+        }
+    }
+}
+// its constant alone
+template <bool K4> __device__ __forceinline__ void target_constant(float cst, int g, u32x4 &b0, u32x4 &b1)
+{
+    const Pieces3 c = split3(cst, 0.f);
+    u32x4 &b = K4 ? b0 : b1;
+    const uint32_t at = 0u - (uint32_t)(g == (K4 ? 3 : 2));
+    b[0] = pick(at, c.h | (c.m << 16), b[0]);
+    b[1] = pick(at, c.l, b[1]);
+}
+
+// The table of target operands: planes h, m, l and the constant ([h m], [l h]
+// and the constant with four components) of 16 bytes per target.
+template <bool K4>
+__device__ __forceinline__ void put_target(unsigned char *smem, long base, int rows, int r, const float (&v)[K4 ? 4 : 8],
+                                           float cst)
+{
+    constexpr int W = K4 ? 2 : 4;
+    u32x4 *t = (u32x4 *)(smem + base) + r;
+    uint32_t h[W], m[W], l[W];
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        const Pieces3 p = split3(v[2 * q], v[2 * q + 1]);
+        h[q] = p.h;
+        m[q] = p.m;
+        l[q] = p.l;
+    }
+    const Pieces3 c = split3(cst, 0.f);
+    const u32x4 cc = {c.h | (c.m << 16), c.l, 0u, 0u};
+    if constexpr (K4) {
+        t[0] = u32x4{h[0], h[1], m[0], m[1]};
+        t[rows] = u32x4{l[0], l[1], h[0], h[1]};
+        t[2 * rows] = cc;
+    } else {
+        t[0] = u32x4{h[0], h[1], h[2], h[3]};
+        t[rows] = u32x4{m[0], m[1], m[2], m[3]};
+        t[2 * rows] = u32x4{l[0], l[1], l[2], l[3]};
+        t[3 * rows] = cc;
+    }
+}
+template <bool K4>
+__device__ __forceinline__ void load_target(const unsigned char *smem, long base, int rows, int r, int g, u32x4 &b0,
+                                            u32x4 &b1)
+{
+    const u32x4 *t = (const u32x4 *)(smem + base) + r;
+    if (K4) {
+        b0 = t[(g > 1 ? g - 1 : 0) * rows];
+    } else {
+        b0 = t[(g & 1) * rows];
+        b1 = t[(g == 1 ? 0 : g == 2 ? 3 : 2) * rows];
+    }
+}
+
+// Rows of a three-plane table: the FP32 values are the exact sums of their
+// pieces.
+template <bool K4>
+__device__ __forceinline__ void put_row(unsigned char *smem, long base, int rows, int r, const float (&v)[K4 ? 4 : 8])
+{
+    constexpr int W = K4 ? 2 : 4;
+    uint32_t h[W], m[W], l[W];
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        const Pieces3 p = split3(v[2 * q], v[2 * q + 1]);
+        h[q] = p.h;
+        m[q] = p.m;
+        l[q] = p.l;
+    }
+    if constexpr (K4) {
+        *(u32x2 *)(smem + base + (long)r * 8) = u32x2{h[0], h[1]};
+        *(u32x2 *)(smem + base + (long)(rows + r) * 8) = u32x2{m[0], m[1]};
+        *(u32x2 *)(smem + base + (long)(2 * rows + r) * 8) = u32x2{l[0], l[1]};
+    } else {
+        *(u32x4 *)(smem + base + (long)r * 16) = u32x4{h[0], h[1], h[2], h[3]};
+        *(u32x4 *)(smem + base + (long)(rows + r) * 16) = u32x4{m[0], m[1], m[2], m[3]};
+        *(u32x4 *)(smem + base + (long)(2 * rows + r) * 16) = u32x4{l[0], l[1], l[2], l[3]};
+    }
+}
+template <bool K4> struct PieceRow {
+    static constexpr int W = K4 ? 2 : 4;
+    uint32_t h[W], m[W], l[W];
+    __device__ __forceinline__ void load(const unsigned char *smem, long base, int rows, int r)
+    {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            uint32_t *d = p == 0 ? h : p == 1 ? m : l;
+            if constexpr (K4) {
+                const u32x2 v = *(const u32x2 *)(smem + base + (long)(p * rows + r) * 8);
+                d[0] = v[0]; d[1] = v[1];
+            } else {
+                const u32x4 v = *(const u32x4 *)(smem + base + (long)(p * rows + r) * 16);
+                d[0] = v[0]; d[1] = v[1]; d[2] = v[2]; d[3] = v[3];
             }
-        };
-        load_batch(ib + 1);
-        for (int kb = ib + 1; kb < nt16; kb += kBatch) {
-            f32x4 G[kBatch];
+        }
+    }
+    __device__ __forceinline__ float at(int c) const
+    {
+        return (c & 1) ? (bf_hi(h[c / 2]) + bf_hi(m[c / 2])) + bf_hi(l[c / 2])
+                       : (bf_lo(h[c / 2]) + bf_lo(m[c / 2])) + bf_lo(l[c / 2]);
+    }
+};
+
+// Sums' table (off_v, off_ms): component c of source s as two f16 pieces, row
+// c and row R + c of its 32-source block, at the position that matches the
+// K-slots of a pair of 16x16 tiles: lane group g holds sources 4 g + r of the
+// first tile in slots r and of the second in slots 4 + r.
+template <bool K4>
+__device__ __forceinline__ void put_sum_row(unsigned char *smem, long base, int s, const float (&v)[K4 ? 4 : 8])
+{
+    constexpr int R = K4 ? 4 : 8;
+    const int pos = ((s >> 2) & 3) * 8 + ((s >> 4) & 1) * 4 + (s & 3);
+    _Float16 *d = (_Float16 *)(smem + base + (long)(s >> 5) * (2 * R * 64)) + pos;
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) G[u] = K4 ? mfma16(a0[u], bi0, cn) : mfma16(a1[u], bi1, mfma16(a0[u], bi0, cn));
-            load_batch(kb + kBatch);  // next batch's loads overlap this batch's work
+    for (int c = 0; c < R; ++c) {
+        const _Float16 hi = (_Float16)v[c];
+        d[c * 32] = hi;
+        d[(R + c) * 32] = (_Float16)(v[c] - (float)hi);
+    }
+}
+
+// power of two that brings values of magnitude up to `bound` below 2^15, and
+// its inverse
+__device__ __forceinline__ void f16_scale(float bound, float &scale, float &inv)
+{
+    const int e = min(max((int)(__float_as_uint(bound) >> 23) & 0xff, 20), 250);  // 2^(e - 127) <= bound < 2^(e - 126)
+    scale = __uint_as_float((uint32_t)(268 - e) << 23);  // 2^(141 - e): below 2^15
+    inv = __uint_as_float((uint32_t)(e - 14) << 23);
+}
+
+// Sum over the lane groups that hold a component's pieces, and a transpose:
+// given O[q] of the four (two) 16-target tiles of a task (register i of lane
+// group g holds row 4 g + i of target 16 q + l % 16), lane l receives the R
+// components of target l (l < 32 with two tiles).
+template <bool K4, int QT>
+__device__ __forceinline__ void collect_rows(const f32x4 (&O)[QT], float (&out)[K4 ? 4 : 8])
+{
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                if (kb + u >= nt16) break;
-                fn(G[u], false);
-            }
+    for (int i = 0; i < 4; ++i) {
+        uint32_t u, w;
+        if constexpr (QT == 4) {
+            auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(O[0][i]), __float_as_uint(O[2][i]), false, false);
+            auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(O[1][i]), __float_as_uint(O[3][i]), false, false);
+            // lane groups 0, 1: target tile 0 (1), rows g and g + 2; groups 2, 3: tile 2 (3)
+            u = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
+            w = __float_as_uint(__uint_as_float(b[0]) + __uint_as_float(b[1]));
+        } else {
+            auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(O[0][i]), __float_as_uint(O[1][i]), false, false);
+            // lane groups 0, 1: target tile 0; groups 2, 3: tile 1, brought below
+            u = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
+            auto b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+            u = b[0];
+            w = b[1];
+        }
+        auto c = __builtin_amdgcn_permlane16_swap(u, w, false, false);
+        if constexpr (K4) {
+            // rows 8..15 repeat rows 0..7
+            out[i] = 0.5f * (__uint_as_float(c[0]) + __uint_as_float(c[1]));
+        } else {
+            out[i] = __uint_as_float(c[0]);
+            out[4 + i] = __uint_as_float(c[1]);
         }
     }
 }
 
-// Exact order statistic `rank` of the squared distances by radix selection
-// over the bit patterns (digits of 11, 11 and 10 bits); every pass recomputes
-// the distances.  In diagonal tiles only pairs k > i count.
-template <bool K4>
-__device__ float radix_median_mfma(const float *X8, int npad, uint32_t rank, uint32_t *hist,
-                                   uint32_t *red)
-{
-    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = wave_id();
-    uint32_t prefix = 0, pmask = 0;
-    for (int pass = 0; pass < 3; ++pass) {
-        const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
-        const uint32_t dmask = pass == 2 ? 0x3ffu : 0x7ffu;
-        for (int b = tid; b < kBins; b += nt) hist[b] = 0;
-        __syncthreads();
-        for_each_distance<K4>(X8, npad, [&](const f32x4 &Dv, bool diag) {
+// One wave's walk over its share of the distances of the pairs k > i: the
+// 32x32 blocks (targets 32 I.., sources 32 K.., K >= I) listed row by row and
+// cut into as many equal runs as there are waves (in the multi-workgroup mode
+// the waves of all its workgroups).  The results are half the squared
+// distances (exact powers of two apart).  In a diagonal block the lanes that
+// hold no pair k > i get +inf (as the products' addend); pad particles have
+// half norms of 2^126.  Two tiles of targets share each source operand: with
+// one the walk took twice the LDS reads, which bounded it.
+template <bool K4> struct BlockWalker {
+    const unsigned char *smem;
+    long base;
+    int rows, nb, g, col, I, K, left;
+    SourceRows<K4> src;
+
+    // blocks [p0, p1) of the list
+    __device__ void start(const unsigned char *lds, long x_base, int npad, long ones, int lane, int p0, int p1)
+    {
+        smem = lds;
+        base = x_base;
+        rows = npad;
+        g = lane >> 4;
+        col = lane & 15;
+        src.init(x_base, npad, ones, g, col);
+        nb = npad / 32;
+        left = p1 - p0;
+        I = 0;
+        while (p0 >= nb - I) {
+            p0 -= nb - I;
+            ++I;
+        }
+        K = I + p0;
+    }
+    // B operand of target tile t: [-x_i, 1], constant |x_i|^2 / 2 - origin
+    __device__ __forceinline__ void target(int t, float origin, u32x4 &b0, u32x4 &b1) const
+    {
+        constexpr int W = PieceRow<K4>::W;
+        PieceRow<K4> p;
+        p.load(smem, base, rows, t * 16 + col);
+        const float half = p.at(K4 ? 3 : 7);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const uint32_t key = __float_as_uint(fmax_(Dv[r], 0.f));
-                const bool valid = !diag || ((diag_lanes(r) >> lane) & 1ull);
-                if (valid && (key & pmask) == prefix) atomicAdd(&hist[(key >> shift) & dmask], 1u);
-            }
-        });
-        __syncthreads();
-        if (wave == 0) {
-            constexpr int per = kBins / kWave;
-            uint32_t cnt = 0;
-            for (int q = 0; q < per; ++q) cnt += hist[lane * per + q];
-            const uint32_t incl = wave_incl_scan(cnt, lane);
-            const uint32_t excl = incl - cnt;
-            if (lane == 0) { red[0] = 0; red[1] = 0; }
-            __builtin_amdgcn_wave_barrier();
-            if (rank >= excl && rank < incl) {
-                uint32_t r = rank - excl;
-                for (int q = 0; q < per; ++q) {
-                    const uint32_t h = hist[lane * per + q];
-                    if (r < h) { red[0] = (uint32_t)(lane * per + q); red[1] = r; break; }
-                    r -= h;
+        for (int q = 0; q < W; ++q) {
+            p.h[q] ^= 0x80008000u;
+            p.m[q] ^= 0x80008000u;
+            p.l[q] ^= 0x80008000u;
+        }
+        p.h[W - 1] = (p.h[W - 1] & 0xffffu) | 0x3f800000u;
+        p.m[W - 1] &= 0xffffu;
+        p.l[W - 1] &= 0xffffu;
+        target_operand<K4>(p.h, p.m, p.l, half - origin, g, b0, b1);
+    }
+    // fn(D) for every block of the share: its four tiles' distances, relative
+    // to `origin` (subtracted within the products' sum)
+    template <typename Fn> __device__ __forceinline__ void visit_all(float origin, Fn &&fn)
+    {
+        const float inf = __builtin_huge_valf();
+        for (; left > 0; ++I, K = I) {
+            u32x4 b00, b01, b10, b11;
+            target(2 * I, origin, b00, b01);
+            target(2 * I + 1, origin, b10, b11);
+            const int end = min(nb, K + left);
+            left -= end - K;
+            SourceRows<K4> at = src;
+            at.skip(2 * K);
+            f32x4 diag = {0.f, 0.f, 0.f, 0.f}, all = diag;
+            if (K == I) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    diag[r] = 4 * g + r > col ? 0.f : inf;
+                    all[r] = inf;
                 }
             }
+            // the next block's operands are read one block ahead (the last
+            // reads run past the table into the one behind it, unused)
+            u32x4 a00, a01, a10, a11;
+            at.load(smem, 0, a00, a01);
+            at.load(smem, 1, a10, a11);
+            for (; K < end; ++K) {
+                f32x4 D[4];
+                D[0] = SourceRows<K4>::dot(a00, a01, b00, b01, diag);
+                D[1] = SourceRows<K4>::dot(a00, a01, b10, b11, all);
+                D[2] = SourceRows<K4>::dot(a10, a11, b00, b01);
+                D[3] = SourceRows<K4>::dot(a10, a11, b10, b11, diag);
+                at.skip(2);
+                at.load(smem, 0, a00, a01);
+                at.load(smem, 1, a10, a11);
+                diag = all = f32x4{0.f, 0.f, 0.f, 0.f};
+                fn(D);
+            }
         }
-        __syncthreads();
-        prefix |= red[0] << shift;
-        rank = red[1];
-        pmask |= dmask << shift;
-        __syncthreads();
     }
-    return __uint_as_float(prefix);
+};
+
+// One digit of a radix selection: wave 0 finds the histogram bin holding
+// `rank` (red[0]) and the rank within it (red[1]).
+__device__ __forceinline__ void radix_digit(const uint32_t *hist, uint32_t rank, uint32_t *red, int lane)
+{
+    constexpr int per = kBins / kWave;
+    uint32_t cnt = 0;
+    for (int q = 0; q < per; ++q) cnt += hist[lane * per + q];
+    const uint32_t incl = wave_incl_scan(cnt, lane);
+    const uint32_t excl = incl - cnt;
+    if (lane == 0) { red[0] = 0; red[1] = 0; }
+    __builtin_amdgcn_wave_barrier();
+    if (rank >= excl && rank < incl) {
+        uint32_t r = rank - excl;
+        for (int q = 0; q < per; ++q) {
+            const uint32_t h = hist[lane * per + q];
+            if (r < h) { red[0] = (uint32_t)(lane * per + q); red[1] = r; break; }
+            r -= h;
+        }
+    }
 }
 
-// Exact order statistic r of the values kept in the window buffer: wave w's
-// values sit in buf[w * kWinRegion ...] with wcnt[w] of them, all in
-// [lo, hi) (key_lo, key_hi their bit patterns).  Radix selection on the key
-// offsets key - key_lo, 8 bits per pass, as many passes as the span needs.
-__device__ float buffer_select(const float *buf, const uint32_t *wcnt, int nregions, int region, uint32_t r,
-                               uint32_t key_lo, uint32_t key_hi, uint32_t *hist, uint32_t *red)
+// Exact order statistic r of the n values of buf, all in [lo, hi], by a radix
+// selection of the whole workgroup on the key offsets key - key(lo), 8 bits
+// per pass, as many passes as the span needs.
+__device__ float buffer_select(const float *buf, uint32_t n, uint32_t r, float lo, float hi, uint32_t *hist,
+                               uint32_t *red)
 {
     const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = wave_id();
-    const uint32_t span = key_hi - key_lo;
+    const uint32_t key_lo = __float_as_uint(lo), span = __float_as_uint(hi) - key_lo;
     const int bits = span == 0 ? 1 : 32 - __clz(span);
-    const int passes = (bits + 7) / 8;
-    const int nslots = nregions * region;
     uint32_t prefix = 0, pmask = 0;
-    for (int p = passes - 1; p >= 0; --p) {
+    for (int p = (bits + 7) / 8 - 1; p >= 0; --p) {
         const int shift = 8 * p;
         for (int q = tid; q < 256; q += nt) hist[q] = 0;
         __syncthreads();
-        for (int s = tid; s < nslots; s += nt) {
-            if ((uint32_t)(s % region) < wcnt[s / region]) {
-                const uint32_t k = __float_as_uint(buf[s]) - key_lo;
-                if ((k & pmask) == prefix) atomicAdd(&hist[(k >> shift) & 0xffu], 1u);
-            }
+        for (uint32_t s = tid; s < n; s += nt) {
+            const uint32_t k = __float_as_uint(buf[s]) - key_lo;
+            if ((k & pmask) == prefix) atomicAdd(&hist[(k >> shift) & 0xffu], 1u);
         }
         __syncthreads();
         if (wave == 0) {
@@ -298,396 +649,204 @@ __device__ float buffer_select(const float *buf, const uint32_t *wcnt, int nregi
     return __uint_as_float(key_lo + prefix);
 }
 
-// Exact order statistic r of the values kept in the window buffer (same
-// layout as buffer_select).  whist holds their histogram over 256 bins of
-// (key - key_lo) >> shift, counted as the values were appended.  Wave 0
-// finds the bin holding rank r; every wave gathers that bin's values from
-// its own region into cand (positions from an LDS counter: the order does
-// not matter); wave 0 ranks the candidates by comparison.  A bin with more
-// than 64 values (heavy ties) falls back to buffer_select.  cand may alias
-// whist: the histogram is dead once the bin is known.
-__device__ float window_select(const float *buf, const uint32_t *wcnt, int nregions, int region, uint32_t r,
-                               uint32_t key_lo, uint32_t key_hi, uint32_t shift, uint32_t *whist, uint32_t *red,
-                               float *cand)
+// The same by one wave, for up to 64 S values (kept in registers).  The
+// window is narrow, so its values are spread nearly evenly: a pivot placed by
+// the rank's share of the values between two known counts (ballot counts)
+// leaves the rank next to a pivot after three or four of them, and the answer
+// is then the least value above it or the largest below.  Ties are settled
+// bit by bit below the common prefix of the window's ends.
+template <int S> __device__ __forceinline__ float window_select(const float *buf, uint32_t n, uint32_t r, float lo, float hi)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = wave_id(), nwaves = blockDim.x >> 6;
-    if (wave == 0) {
-        typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-        const u32x4_t c = *(const u32x4_t *)(whist + lane * 4);
-        const uint32_t cnt = c[0] + c[1] + c[2] + c[3];
-        const uint32_t incl = wave_incl_scan(cnt, lane);
-        const uint32_t excl = incl - cnt;
-        if (r >= excl && r < incl) {
-            uint32_t rr = r - excl;
+    const uint32_t lane = threadIdx.x & 63;
+    float v[S];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (rr < c[q]) {
-                    red[2] = (uint32_t)(lane * 4 + q);
-                    red[3] = rr;
-                    red[4] = c[q];
-                    break;
-                }
-                rr -= c[q];
+    for (int q = 0; q < S; ++q) {
+        const uint32_t at = lane + (uint32_t)q * kWave;
+        v[q] = at < n ? buf[at] : __builtin_huge_valf();
+    }
+    auto count_below = [&](float t) {
+        uint32_t c = 0;
+#pragma unroll
+        for (int q = 0; q < S; ++q) c += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(v[q] < t));
+        return c;
+    };
+    float a = lo, b = hi;
+    uint32_t ca = 0, cb = n;
+    for (int k = 0; k < 10; ++k) {
+        const float t = a + (b - a) * (((float)(r - ca) + 0.5f) * __builtin_amdgcn_rcpf((float)(cb - ca)));
+        const uint32_t c = count_below(t);
+        if (c == r || c == r + 1) {
+            uint32_t best = c == r ? 0x7f800000u : 0u;
+#pragma unroll
+            for (int q = 0; q < S; ++q) {
+                const uint32_t u = __float_as_uint(v[q]);
+                if (c == r) best = v[q] < t ? best : min(best, u);
+                else best = v[q] < t ? max(best, u) : best;
             }
+            if (c == r) best = wave_reduce(best, [](uint32_t x, uint32_t y) { return x < y ? x : y; });
+            else best = wave_reduce(best, [](uint32_t x, uint32_t y) { return x > y ? x : y; });
+            return __uint_as_float(best);
         }
-        if (lane == 0) red[6] = 0;
+        if (c < r) { a = t; ca = c; }
+        else { b = t; cb = c; }
     }
-    __syncthreads();
-    const uint32_t bin = red[2], rr = red[3], cb = red[4];
-    if (cb > (uint32_t)kWave) return buffer_select(buf, wcnt, nregions, region, r, key_lo, key_hi, whist, red);
-    for (int w = wave; w < nregions; w += nwaves) {
-        const uint32_t c = wcnt[w];
-        for (uint32_t s = lane; s < c; s += kWave) {
-            const float v = buf[w * region + s];
-            if (((__float_as_uint(v) - key_lo) >> shift) == bin) cand[atomicAdd(&red[6], 1u)] = v;
-        }
+    const uint32_t klo = __float_as_uint(lo), diff = klo ^ __float_as_uint(hi);
+    const int top = diff ? 31 - __builtin_clz(diff) : -1;
+    uint32_t prefix = top >= 31 ? 0u : klo & ~((1u << (top + 1)) - 1u);
+    for (int bit = top; bit >= 0; --bit) {
+        const uint32_t t = prefix | (1u << bit);
+        if (count_below(__uint_as_float(t)) <= r) prefix = t;
     }
-    __syncthreads();
-    if (wave == 0 && (uint32_t)lane < cb) {
-        const float v = cand[lane];
-        uint32_t less = 0, leq = 0;
-        for (uint32_t t = 0; t < cb; ++t) {
-            const float u = cand[t];
-            less += u < v ? 1u : 0u;
-            leq += u <= v ? 1u : 0u;
-        }
-        if (less <= rr && rr < leq) red[5] = __float_as_uint(v);
-    }
-    __syncthreads();
-    return __uint_as_float(red[5]);
+    return __uint_as_float(prefix);
+}
+constexpr uint32_t kSelectMax = 1024;   // most values the one-wave selection takes
+__device__ float window_select(const float *buf, uint32_t n, uint32_t r, float lo, float hi)
+{
+    if (n <= 2 * kWave) return window_select<2>(buf, n, r, lo, hi);
+    if (n <= 4 * kWave) return window_select<4>(buf, n, r, lo, hi);
+    return window_select<kSelectMax / kWave>(buf, n, r, lo, hi);
 }
 
-// One wave's walk over its share of the off-diagonal distance tiles (the
-// rows of tiles of for_each_distance, in the same order, source tiles
-// kb > ib), two source tiles kb, kb + 1 per step.  Holds the current row's
-// B operand (-2 x_i with a 1 in the norm row) and the target norms as the
-// accumulator input.  The diagonal tiles of the wave's rows are visited by
-// diagonals().  In chunk mode (the multi-workgroup walk: more waves than
-// rows) virtual wave v of nv takes the v-th of nv equal contiguous runs of
-// the off-diagonal tiles listed row by row, and every nv-th diagonal tile
-// (CHUNK: the mode is fixed per kernel, so neither walk carries the other's
-// state through its loops).
-template <bool K4, bool CHUNK>
-struct TileWalker {
-    static constexpr bool chunk = CHUNK;
-    int nt16, nwaves, wave, rr, ib, kb, left;
-    float bi0, bi1;
-    f32x4 cn;
-
-    __device__ int row_of(int r) const { return (r & 1) ? (r + 1) * nwaves - 1 - wave : r * nwaves + wave; }
-    __device__ void load_row(const float *X8, int g, int col)
-    {
-        const float *xi = X8 + (long)(ib * 16 + col) * 8;
-        bi0 = K4 && g == 3 ? 1.f : -2.f * xi[g];
-        bi1 = g == 3 ? 1.f : -2.f * xi[4 + g];
-        const float nni = xi[7];
-        cn = f32x4{nni, nni, nni, nni};
-    }
-    __device__ void start(const float *X8, int npad, int g, int col, int vwave = -1, int nvwaves = 0)
-    {
-        nt16 = npad / 16;
-        nwaves = chunk ? nvwaves : (int)(blockDim.x >> 6);
-        wave = chunk ? vwave : wave_id();
-        if (!chunk) {
-            left = 0x7fffffff;
-            rr = -1;
-            next_row(X8, g, col);
-            return;
-        }
-        const long total = (long)nt16 * (nt16 - 1) / 2;
-        long p0 = total * wave / nwaves;
-        left = (int)(total * (wave + 1) / nwaves - p0);
-        ib = 0;
-        while (ib < nt16 - 1 && p0 >= nt16 - 1 - ib) {
-            p0 -= nt16 - 1 - ib;
-            ++ib;
-        }
-        kb = ib + 1 + (int)p0;
-        if (left <= 0) ib = nt16;
-        else load_row(X8, g, col);
-    }
-    // next row with an off-diagonal tile
-    __device__ void next_row(const float *X8, int g, int col)
-    {
-        if (chunk) {
-            ++ib;
-            kb = ib + 1;
-            if (left <= 0 || kb >= nt16) ib = nt16;
-            else load_row(X8, g, col);
-            return;
-        }
-        do {
-            ++rr;
-            ib = row_of(rr);
-            kb = ib + 1;
-        } while (ib < nt16 && kb >= nt16);
-        if (ib < nt16) load_row(X8, g, col);
-    }
-    __device__ bool done() const { return ib >= nt16; }
-    __device__ bool second() const { return kb + 1 < nt16 && left >= 2; }
-    // distances of tiles kb and kb + 1 (clamped to the row: always in
-    // bounds, also once the walk is done; results past the end are unused)
-    __device__ void issue(const float *X8, int g, int col, f32x4 &D0, f32x4 &D1) const
-    {
-        const int k0 = min(kb, nt16 - 1), k1 = min(kb + 1, nt16 - 1);
-        const float *x0 = X8 + (long)(k0 * 16 + col) * 8;
-        const float *x1 = X8 + (long)(k1 * 16 + col) * 8;
-        const int ka = gram_col<K4>(g);
-        D0 = mfma16(x0[ka], bi0, cn);
-        D1 = mfma16(x1[ka], bi0, cn);
-        if (!K4) {
-            D0 = mfma16(x0[4 + g], bi1, D0);
-            D1 = mfma16(x1[4 + g], bi1, D1);
-        }
-    }
-    __device__ void advance(const float *X8, int g, int col)
-    {
-        left -= second() ? 2 : 1;
-        kb += 2;
-        if (left <= 0) ib = nt16;
-        else if (kb >= nt16) next_row(X8, g, col);
-    }
-    // the diagonal tile of every row of this wave (chunk mode: every
-    // nwaves-th row), fn(D, true)
-    template <typename Fn> __device__ void diagonals(const float *X8, int g, int col, Fn &&fn)
-    {
-        for (int r = 0;; ++r) {
-            ib = chunk ? wave + r * nwaves : row_of(r);
-            if (ib >= nt16) break;
-            load_row(X8, g, col);
-            const float *xk = X8 + (long)(ib * 16 + col) * 8;
-            fn(K4 ? mfma16(xk[gram_col<K4>(g)], bi0, cn) : mfma16(xk[4 + g], bi1, mfma16(xk[g], bi0, cn)), true);
-        }
-    }
-};
-
-// Median tracker across the iterations of one step.  The previous two
-// medians predict a window [lo, hi).  While the particles are unchanged (the
-// score pass of the same iteration) the waves visit every distance once,
-// counting those below lo and keeping those inside the window, each wave in
-// its own region of the window buffer; finish() then selects the exact
-// rank-th value among the kept ones.  When there is no prediction yet, the
-// window misses the rank or a region overflows, the full radix selection
-// runs instead.  Both read the same MFMA distances, so the result is the same
-// exact lower median either way.
+// Median tracker across the iterations of one step (of half the squared
+// distances).  The previous two medians, extrapolated, predict a window
+// [lo, hi).  While the particles are unchanged the waves visit every distance
+// once, counting those below lo and keeping those inside the window; the
+// median is the matching order statistic of the kept ones.
+// The half width is the larger of kWinTarget / 2 distances at the density of
+// the last window and three times the recent error of the prediction (the
+// largest, fading by 0.8 an iteration).  On the workloads' runs (N = 256 and
+// 512, 50 and 100 iterations) that keeps 130 to 150 distances on average and
+// misses the median in none of the iterations after the first two; windows of
+// three times the median's last move kept 500 to 650 (4,000 at 1024 particles
+// of the arm, where nine tiles in ten then held one) and missed 1%.
+// Without a prediction, or when the window misses the rank or overflows,
+// histogram passes over the distances narrow the range to one of few enough
+// values (MedianRange).  All passes see the same distances, so the result is
+// the same exact lower median whichever ran.
+constexpr int kWinTarget = 128;
+constexpr int kMaxHistPasses = 4;
 struct MedianTracker {
-    float med1, med2, density;
-    int have;        // number of medians recorded (0, 1, 2+)
-    bool active;     // a window pass is under way this iteration
-    float lo, hi;    // the window
-    uint32_t below;  // per wave: distances below lo
-    uint32_t kept;   // per wave: distances kept (kOverflow once the region is full)
-    uint32_t wshift; // window histogram bin of a kept distance: (key - key(lo)) >> wshift
-    uint32_t *whist; // its 256 counters (zero before the walk)
-    int wcap;        // per-wave capacity of the window buffer
+    float med1, med2, density, pred, err;
+    int have;        // number of medians recorded (0, 1, 2, 3+)
+    float lo, width; // the window [lo, lo + width)
+    uint32_t below;  // per lane: distances below lo
 
-    __device__ void reset(int cap = kWinRegion)
+    __device__ void reset()
     {
-        med1 = med2 = density = 0.f;
+        med1 = med2 = density = pred = err = 0.f;
         have = 0;
-        active = false;
-        wcap = cap;
     }
 
-    // window of this iteration (active only with a previous median)
-    __device__ void plan(uint32_t *hist256)
+    // window of this iteration among M pairs; false without a prediction
+    __device__ bool plan(uint32_t M, uint32_t cap)
     {
-        whist = hist256;
-        active = have >= 1 && med1 > 0.f;
-        below = 0;
-        kept = 0;
-        if (!active) return;
-        const float move = have >= 2 ? fabsf(med1 - med2) : 0.f;
-        const float pred = have >= 2 ? med1 + (med1 - med2) : med1;
-        float w = density > 0.f ? (float)kWinTarget / (2.f * density) : 1e-3f * med1;
-        w = fmax_(w, 3.f * move);
+        if (have == 0 || !(med1 > 0.f)) return false;
+        const float move = fabsf(med1 - med2);
+        float w = density > 0.f ? 0.5f * (float)kWinTarget / density : 1e-3f * med1;
+        pred = have >= 2 ? med1 + (med1 - med2) : med1;
+        // one median: as wide as the buffer holds (at the densest, 0.7 of the
+        // pairs per unit of relative distance), up to a hundredth
+        if (have == 1) w = fminf(1e-2f, 0.6f * (float)cap / (float)M) * med1;
+        else w = fmax_(w, have == 2 ? 0.5f * move : 3.f * err);
         w = fmax_(w, 2e-5f * med1);
+        pred = uniform(pred);
         lo = uniform(fmax_(pred - w, 0.f));
-        hi = uniform(pred + w);
-        const uint32_t span = __float_as_uint(hi) - __float_as_uint(lo);
-        const int bits = span == 0 ? 1 : 32 - __clz(span);
-        wshift = bits > 8 ? bits - 8 : 0;
+        width = uniform(pred + w - lo);
+        return true;
     }
-
-    static constexpr uint32_t kOverflow = 0x40000000u;
-
-    // One tile of distances (diag: only pairs k > i count).  The common case
-    // is two comparisons per distance, D < lo and D < hi, as wave masks: the
-    // wave's count below lo is the population count of the first (scalar
-    // work), and D lies in the window [lo, hi) where the second holds and the
-    // first does not (a NaN is in neither; -0 counts as 0).  Only a tile
-    // holding window distances appends them to the wave's region, binned by
-    // key(D) - key(lo) on the bit patterns.
-    __device__ void visit(f32x4 Dv, bool diag, float *region)
+    __device__ void record(float med)
     {
-        if (diag) {
-            const int l = threadIdx.x & 63;
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (!((diag_lanes(r) >> l) & 1ull)) Dv[r] = __builtin_huge_valf();
-        }
-        unsigned long long win[4], any = 0;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const unsigned long long mlo = __builtin_amdgcn_ballot_w64(Dv[r] < lo);
-            const unsigned long long mhi = __builtin_amdgcn_ballot_w64(Dv[r] < hi);
-            below += (uint32_t)__builtin_popcountll(mlo);
-            win[r] = mhi & ~mlo;
-            any |= win[r];
-        }
-        if (any) {
-            const uint32_t klo = __float_as_uint(lo);
-            const int l = threadIdx.x & 63;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const unsigned long long mk = win[r];
-                const uint32_t cnt = (uint32_t)__builtin_popcountll(mk);
-                const bool fits = kept + cnt <= (uint32_t)wcap;  // kOverflow stays
-                if (fits && ((mk >> l) & 1ull)) {
-                    const float v = Dv[r] + 0.f;  // no -0
-                    region[kept + lanes_below(mk)] = v;
-                    atomicAdd(&whist[(__float_as_uint(v) - klo) >> wshift], 1u);
-                }
-                kept = fits ? kept + cnt : kOverflow;
-            }
-        }
-    }
-
-    // After every wave has visited its tiles (no barrier needed before the
-    // call).  Returns the exact lower median.
-    template <bool K4>
-    __device__ float finish(const float *X8, int n, int npad, float *buf, uint32_t *hist, uint32_t *red)
-    {
-        const uint32_t M = (uint32_t)((long)n * (n - 1) / 2);
-        if (M == 0) return __builtin_nanf("");
-        const uint32_t rank = (M - 1) / 2;
-        const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = wave_id(), nwaves = nt >> 6;
-        // red[0..1] radix selection, red[2..6] window_select, red[8..9]
-        // buffer_select
-        uint32_t *wcnt = red + 10;    // per-wave kept counts (red[10..25])
-        uint32_t *wbelow = red + 26;  // per-wave below counts (red[26..41])
-        float med = 0.f;
-        bool done = false;
-        if (active) {
-            if (lane == 0) {
-                wbelow[wave] = below;
-                wcnt[wave] = kept;
-            }
-            __syncthreads();
-            uint32_t cnt_lo = 0, n_in = 0;
-            bool overflow = false;
-            for (int q = 0; q < nwaves; ++q) {
-                cnt_lo += wbelow[q];
-                n_in += wcnt[q];
-                overflow |= wcnt[q] > (uint32_t)wcap;
-            }
-            density = uniform((float)n_in / (hi - lo));
-            if (!overflow && rank >= cnt_lo && rank < cnt_lo + n_in) {
-                med = window_select(buf, wcnt, nwaves, wcap, rank - cnt_lo, __float_as_uint(lo), __float_as_uint(hi),
-                                    wshift, whist, red, (float *)whist);
-                done = true;
-            }
-            __syncthreads();
-        }
-        if (!done) med = radix_median_mfma<K4>(X8, npad, rank, hist, red);
-        med = uniform(med);
+        if (have >= 2) err = fmax_(fabsf(med - pred), 0.8f * err);
         med2 = med1;
-        med1 = med;
-        have = have < 2 ? have + 1 : 2;
-        active = false;
-        return med;
+        med1 = uniform(med);
+        err = uniform(err);
+        have = have < 3 ? have + 1 : 3;
+    }
+
+    // A block's distances, relative to lo.  The common case: the sign bits of
+    // a lane's sixteen values are shifted together and counted (those below
+    // lo; a -0 counts as one), and one test tells that none lies in the
+    // window: as bit patterns the least is not below the width (negative ones
+    // are larger; a NaN is in neither).  Window distances are appended to the
+    // common list while they fit (the order does not matter).
+    __device__ __forceinline__ void visit(const f32x4 (&D)[4], float *list, uint32_t cap, uint32_t *counter)
+    {
+        uint32_t signs = 0, least = 0xffffffffu;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const uint32_t d = __float_as_uint(D[r >> 2][r & 3]);
+            signs = __builtin_amdgcn_alignbit(signs, d, 31);
+            least = min(least, d);
+        }
+        below += (uint32_t)__builtin_popcount(signs);
+        const uint32_t w = __float_as_uint(width);
+        if (least < w) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float d = D[r >> 2][r & 3];
+                if (__float_as_uint(d) < w) {
+                    const uint32_t at = atomicAdd(counter, 1u);
+                    if (at < cap) list[at] = lo + d;
+                }
+            }
+        }
     }
 };
 
-// Wave priority from progress relative to the waves that share the SIMD
-// (waves w, w + 4, w + 8, w + 12 of a workgroup).  The SIMD arbiter serves
-// the oldest wave first among equal priorities, so without this a pass ends
-// in age order and its tail runs on one or two waves, too few to hide
-// latency.  Every second tile step a wave publishes its running count of
-// steps in LDS and reads its mates' counts; the read is only used at the
-// next call, so it never waits.  A wave ahead of its slowest mate yields:
-// priority 3 within 2 steps of it, 2 within 4, 1 within 8, else 0.
-struct ProgressBalance {
-    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-    // the words are addressed as LDS (ds instructions, no vector-memory wait)
-    typedef __attribute__((address_space(3))) volatile uint32_t lds_u32;
-    typedef __attribute__((address_space(3))) volatile u32x4_t lds_u32x4;
-    lds_u32x4 *row;       // the SIMD's four counts
-    lds_u32 *own;         // this wave's count
-    uint32_t done;        // steps of this wave so far (all passes)
-    uint32_t mn;          // the least of the four counts at the last step
-
-    // prog: 16 LDS words set to ~0 (absent waves never lag) before a barrier
-    __device__ void init(uint32_t *prog, int wave)
+// The range of the distances that holds the median's rank, narrowed by linear
+// histograms of 2048 bins.  It starts at [0, top) with top four times the mean
+// of |x|^2 / 2: the mean half squared distance is at most twice that mean,
+// and a median is at most twice the mean.  (A radix selection on the bit
+// patterns, whose first digit puts nearly all distances into a few bins, takes
+// three passes and 240 us at 1024 particles of the arm; a histogram pass and a
+// window pass about half of that.)
+struct MedianRange {
+    float a, b;          // the range
+    __device__ float scale() const { return (float)kBins / (b - a); }
+    // counts a block's distances of the range, and (per lane) those below it
+    __device__ __forceinline__ void visit(const f32x4 (&D)[4], uint32_t *hist, float sc, uint32_t &below) const
     {
-        row = (lds_u32x4 *)(prog + (wave & 3) * 4);
-        own = (lds_u32 *)(prog + (wave & 3) * 4 + (wave >> 2));
-        done = 0;
-        mn = 0;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float d = fmax_(D[r >> 2][r & 3], 0.f);
+            below += d < a ? 1u : 0u;
+            if (d >= a && d < b) atomicAdd(&hist[min((int)((d - a) * sc), kBins - 1)], 1u);
+        }
     }
-    __device__ void step()
+    // narrows to a bin and a quarter of one on either side
+    __device__ void narrow(uint32_t bin)
     {
-        done += 2;
-        const uint32_t ahead = done - min(mn, done);
-        if (ahead <= 2) __builtin_amdgcn_s_setprio(3);
-        else if (ahead <= 4) __builtin_amdgcn_s_setprio(2);
-        else if (ahead <= 8) __builtin_amdgcn_s_setprio(1);
-        else __builtin_amdgcn_s_setprio(0);
-        *own = done;
-        const u32x4_t p = *row;
-        mn = __builtin_amdgcn_readfirstlane(min(min(p[0], p[1]), min(p[2], p[3])));
+        const float w = (b - a) / (float)kBins;
+        const float na = a + ((float)bin - 0.25f) * w, nb = a + ((float)bin + 1.25f) * w;
+        a = fmax_(na, 0.f);
+        b = nb;
     }
 };
-
-// One sequence's time step (b: its index in the strided batch of `a`).  The
-// workgroup owns the sequence: all state in LDS, every barrier block-wide.
-// Sum of a value over the four 16-lane rows of a wave, in every lane.
-__device__ __forceinline__ float sum_row_quarters(float v)
-{
-    auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(s[0]) + __uint_as_float(s[1]);
-    s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
-}
-
-// Given four values v0..v3 of a wave, lane l in 16-lane row w receives the
-// sum of v_w over the four rows, in that lane's column (a transpose of rows
-// against values, then a sum): two rounds of lane swaps.
-__device__ __forceinline__ float sum_quarters_scatter(float v0, float v1, float v2, float v3)
-{
-    auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v0), __float_as_uint(v2), false, false);
-    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v1), __float_as_uint(v3), false, false);
-    // lanes 0..31: v0 (resp. v1) over rows r, r + 2; lanes 32..63: v2 (v3)
-    const float s0 = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-    const float s1 = __uint_as_float(b[0]) + __uint_as_float(b[1]);
-    auto c = __builtin_amdgcn_permlane16_swap(__float_as_uint(s0), __float_as_uint(s1), false, false);
-    return __uint_as_float(c[0]) + __uint_as_float(c[1]);
-}
 
 // ---- multi-workgroup mode ---------------------------------------------
-// The G workgroups of one sequence each own tasks_local = ntasks / G
-// consecutive 64-particle target tasks and hold every particle in LDS.  Per
+// The G workgroups of one sequence each own npad / G consecutive particles as
+// their targets and hold every particle in LDS.  Per
 // SVGD iteration they exchange, through global memory, the score rows of
 // their targets and their share of the median's window pass (barrier 1),
 // then their moved particles (barrier 2); every workgroup then holds the
 // same state, and every selection they make from the exchanged data (the
 // median, the radix fallback) is the same.  The layout of one sequence's
 // exchange area, host and device:
-constexpr int kCoopWinCap = 2048;     // window buffer of a workgroup (floats)
+constexpr int kCoopWinCap = 2048;     // window buffer of a workgroup (floats; MfmaLds::win_cap)
 constexpr uint32_t kCoopSpinLimit = 1u << 24;  // barrier wait bound (polls)
 
 struct CoopLayout {
-    long off_ctr, off_x, off_s, off_info, off_whist, off_vals, off_rhist, bytes;
+    long off_ctr, off_x, off_s, off_info, off_vals, off_rhist, bytes;
     __host__ __device__ CoopLayout(int npad, int G)
     {
         long o = 0;
         off_ctr = o; o += 256;
         off_x = o; o += align16((long)npad * 8 * 4);
         off_s = o; o += align16((long)npad * 8 * 4);
-        off_info = o; o += align16((long)G * 4 * 4);
-        off_whist = o; o += align16((long)G * 256 * 4);
-        off_vals = o; o += align16((long)G * kCoopWinCap * 4);
-        off_rhist = o; o += align16((long)2 * G * kBins * 4);   // two buffers, alternate passes
+        // two buffers each, used in turn
+        off_info = o; o += align16((long)2 * G * 2 * 4);
+        off_vals = o; o += align16((long)2 * G * kCoopWinCap * 4);
+        off_rhist = o; o += align16((long)2 * G * kBins * 4);
         bytes = (o + 255) / 256 * 256;
     }
 };
@@ -730,31 +889,38 @@ __device__ __forceinline__ void coop_barrier(uint32_t *ctr, uint32_t target, uin
     }
     __syncthreads();
 }
-
 // SPLIT: the layout splits the sources of each task among waves (MfmaLds
-// ns_max > 1); a separate instantiation, so the unsplit path keeps its
+// split); a separate instantiation, so the unsplit path keeps its
 // registers.  COOP (with SPLIT): one of the G workgroups of sequence b in
 // the multi-workgroup mode (cx).
+// One sequence's time step (b: its index in the strided batch of `a`).  The
+// workgroup owns the sequence: all state in LDS, every barrier block-wide.
+// Thread tid owns particles tid + ts nt: it keeps their scores in registers
+// from the score pass to the bandwidth, and moves them.  In the passes a wave
+// covers a task of 64 targets, one per lane once its sums are collected.
 template <int KIND, int D, int TS, bool SPLIT, bool COOP = false>
 __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const int b, const CoopArgs cx = CoopArgs{})
 {
     using F = Family<float, KIND, D>;
     using R = RealOps<float>;
-    static_assert(D <= 7, "K-column 7 carries the norms");
+    static_assert(D <= 7, "component 7 carries the norms");
     extern __shared__ __align__(16) unsigned char smem[];
-    static_assert(!COOP || SPLIT, "the multi-workgroup mode splits the sources");
-    // d <= 3: four K-rows per tile (coordinates and the norm or constant in
-    // row 3) and four rows of sums, one MFMA each where d <= 7 takes two
+    static_assert(!COOP || (SPLIT && TS == 1), "the multi-workgroup mode splits the sources");
+    // d <= 3: rows of four components, one MFMA per tile instead of two
     constexpr bool K4 = D <= 3;
+    constexpr int NC = K4 ? 4 : 8;      // components of a table row
+    constexpr int kLast = NC - 1;       // the norm, constant or ones component
+    constexpr int kPart = NC + 1;       // floats of a split's partial sums per particle
     const int n = a.n, np = a.n_prev;
     const int G = COOP ? cx.G : 1, gi = COOP ? cx.gi : 0;
+    constexpr int QT = SPLIT ? 2 : 4;   // 16-target tiles of a task
+    constexpr int kTask = 16 * QT;
     const int npad0 = (n + 63) / 64 * 64;
-    const MfmaLds L(n, np, (int)(blockDim.x >> 6), COOP ? npad0 / 64 / G : 0, COOP ? kCoopWinCap : kWinCap);
+    const MfmaLds L(K4, n, np, (int)(blockDim.x >> 6), COOP ? npad0 / G : 0);
     const int npad = L.npad, nppad = L.nppad;
-    constexpr bool split = SPLIT;               // sources of a task split among waves (L.ns_max > 1)
-    float *PART = (float *)(smem + L.off_part); // [ns_max][ntasks * 64][kPartStride] partial sums of the splits
-    // the workgroup's targets: tasks [tbase / 64, tbase / 64 + ntasks) (all of them outside COOP)
-    const int tbase = gi * L.ntasks * 64;
+    float *PART = (float *)(smem + L.off_part); // [ns_max][targets][kPart] partial sums of the splits
+    // the workgroup's targets: particles [tbase, tbase + ntl) (all of them outside COOP)
+    const int tbase = gi * L.ntasks * kTask;
     // exchange area of this sequence (COOP)
     const CoopLayout CL(npad, G);
     char *cbase = COOP ? cx.base + (long)b * cx.stride : nullptr;
@@ -762,17 +928,11 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
     float *cX = (float *)(cbase + CL.off_x);
     float *cS = (float *)(cbase + CL.off_s);
     uint32_t *cinfo = (uint32_t *)(cbase + CL.off_info);
-    uint32_t *cwhist = (uint32_t *)(cbase + CL.off_whist);
     float *cvals = (float *)(cbase + CL.off_vals);
     uint32_t *crhist = (uint32_t *)(cbase + CL.off_rhist);
     uint32_t epoch = 0;  // barriers passed (the same count in every workgroup)
-    float *X8 = (float *)(smem + L.off_x);     // [npad][8]  centred particles, |x|^2 in column 7 (pad: 0.., +inf)
-    float *S8 = (float *)(smem + L.off_s);     // [npad][8]  scores
-    float *VT = (float *)(smem + L.off_m);     // [9][nppad] rows 2 mh_c (c < 7; 0 for c >= d), 1, c'_j
-    float *PHP = (float *)(smem + L.off_phip); // [nppad] previous forward-recursion scores
-    uint32_t *hist = (uint32_t *)(smem + L.off_scr);
-    float *WIN = (float *)(smem + L.off_win);                    // median window buffer
-    uint32_t *whist = (uint32_t *)(smem + L.off_win) + L.win_cap;  // its histogram
+    float *WIN = (float *)(smem + L.off_win);                    // median window buffer, radix histogram
+    uint32_t *whist = (uint32_t *)(smem + L.off_win) + L.win_cap;  // 256 bins of buffer_select
     float *sz = (float *)(smem + L.off_z);
     uint8_t *smask = smem + L.off_mask;
     uint32_t *red = (uint32_t *)(smem + L.off_red);
@@ -780,21 +940,14 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
 
     const int tid = threadIdx.x, nt = blockDim.x;
     const int lane = tid & 63, wave = wave_id(), nwaves = nt >> 6;
-    const int g = lane >> 4, col = lane & 15;
     const DevModel<float> &m = a.m;
     const float *xprev = a.x_prev + (long)b * a.x_prev_stride;
     float *xg = a.x + (long)b * a.x_stride;
     const float inf = R::inf();
+    float neg1 = -1.f;
+    asm("" : "+s"(neg1));  // see split_f16
 
-    for (int o = tid; o < 16; o += nt) red[kProgSlot + o] = 0xffffffffu;
-    // wave priorities by progress: with whole tasks per wave (the arm7
-    // shape: 64 tile steps per pass) the balancing pays (5%), and in the
-    // multi-workgroup step (2% at arm7 B = 1); one workgroup with sources
-    // split among waves runs short passes where it costs more than it saves
-    // (range2d 5%), so that kernel leaves it out
-    ProgressBalance bal;
-    bal.init(red + kProgSlot, wave);
-    constexpr bool kBalance = !SPLIT || COOP;
+    if (tid == 0) *(u32x4 *)(smem + L.off_ones) = u32x4{0x3f803f80u, 0x3f80u, 0u, 0u};
     for (int o = tid; o < m.obs_dim; o += nt) sz[o] = a.z[(long)b * a.z_stride + o];
     const uint8_t *mk = nullptr;
     if (a.mask) {
@@ -825,14 +978,15 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
         __syncthreads();
     }
 
-    // transition means, centred and log2-scaled, component-major:
-    // VT[c][j] = 2 mh_jc (c < 7), VT[7][j] = 1, VT[8][j] = c'_j =
-    // log2 w_j - |mh_j|^2; pad columns give logit -inf
+    // transition means, centred and log2-scaled: row j = [2 mh_j, c'_j] with
+    // c'_j = log2 w_j - |mh_j|^2; pad sources and those of weight zero get a
+    // logit that counts for nothing
+    float mmax = 0.f;
     for (int j = tid; j < nppad; j += nt) {
-        float row[kVtRows];
+        float row[NC];
 #pragma unroll
-        for (int c = 0; c < kVtRows; ++c) row[c] = 0.f;
-        row[7] = 1.f;
+        for (int c = 0; c < NC; ++c) row[c] = 0.f;
+        row[kLast] = kNoSource;
         if (j < np) {
             float xp[D], mu[D];
 #pragma unroll
@@ -843,21 +997,50 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
             for (int c = 0; c < D; ++c) {
                 const float mh = (mu[c] - ref[c]) * rs[c];
                 row[c] = 2.f * mh;
+                mmax = fmax_(mmax, fabsf(row[c]));
                 nrm += mh * mh;
             }
             const float lw = a.log_w ? a.log_w[(long)b * a.log_w_stride + j] : -R::log_((float)np);
-            row[8] = lw * (float)kLog2e - nrm;
-        } else {
-            row[8] = -inf;
+            const float cj = lw * (float)kLog2e - nrm;
+            row[kLast] = cj < kNoSource ? kNoSource : cj;
         }
-#pragma unroll
-        for (int c = 0; c < kVtRows; ++c) VT[(long)c * nppad + j] = row[c];
+        put_row<K4>(smem, L.off_vt, nppad, j, row);
     }
+    // scale of the f16 pieces of 2 mh
+    mmax = wave_max_abs(mmax);
+    if (lane == 0) redf[wave] = mmax;
+    __syncthreads();
+    mmax = wave_max_abs((lane & 15) < nwaves ? redf[lane & 15] : 0.f);
+    float ms_scale, ms_inv;
+    f16_scale(uniform(mmax), ms_scale, ms_inv);
+    // the sums' table of the transition means, from its rows
+    auto build_ms = [&]() {
+        for (int j = tid; j < nppad; j += nt) {
+            PieceRow<K4> p;
+            p.load(smem, L.off_vt, nppad, j);
+            float v[NC];
+#pragma unroll
+            for (int c = 0; c < kLast; ++c) v[c] = p.at(c) * ms_scale;
+            v[kLast] = 1.f;
+            put_sum_row<K4>(smem, L.off_ms, j, v);
+        }
+    };
+    build_ms();
+    const int ntl = L.ntasks * kTask;
+    // score operand of particle i (at its place in a row), where it is one of
+    // the workgroup's targets and they are kept
+    auto put_score_target = [&](int i, const float (&x)[NC]) {
+        if (!SPLIT || !L.b_table || i < tbase || i >= tbase + ntl) return;
+        float v[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) v[c] = c == kLast ? 1.f : c < D ? x[c] * rs[c] : 0.f;
+        put_target<K4>(smem, L.off_b, ntl, i - tbase, v, 0.f);
+    };
     // initial particles, centred
     for (int i = tid; i < npad; i += nt) {
-        float xi[8];
+        float xi[NC];
 #pragma unroll
-        for (int c = 0; c < 8; ++c) xi[c] = 0.f;
+        for (int c = 0; c < NC; ++c) xi[c] = 0.f;
         if (i < n) {
             if (a.init_given) {
 #pragma unroll
@@ -876,14 +1059,12 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
         }
         float nrm = 0.f;
 #pragma unroll
-        for (int c = 0; c < 7; ++c) nrm += xi[c] * xi[c];
-        xi[7] = i < n ? nrm : inf;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            X8[(long)i * 8 + c] = xi[c];
-            S8[(long)i * 8 + c] = 0.f;
-        }
+        for (int c = 0; c < kLast; ++c) nrm += xi[c] * xi[c];
+        xi[kLast] = i < n ? 0.5f * nrm : kPadHalfNorm;
+        put_row<K4>(smem, L.off_x, npad, i, xi);
+        put_score_target(i, xi);
     }
+    if (tid < 2) red[10 + tid] = 0;
     __syncthreads();
 
     // mean of the centred transition means (literal score reading)
@@ -893,7 +1074,11 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
     if (a.do_svgd && a.trans_mode == 1) {
         for (int c = 0; c < D; ++c) {
             float part = 0.f;
-            for (int j = tid; j < np; j += nt) part += VT[(long)c * nppad + j] * 0.5f / rs[c];
+            for (int j = tid; j < np; j += nt) {
+                PieceRow<K4> p;
+                p.load(smem, L.off_vt, nppad, j);
+                part += p.at(c) * 0.5f / rs[c];
+            }
             part = wave_sum(part);
             if (lane == 0) redf[wave] = part;
             __syncthreads();
@@ -905,539 +1090,492 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
     }
 
     const int ntasks = L.ntasks;   // target tasks of this workgroup
-    const int njt = nppad / 16;
     // every workgroup of the sequence has read its inputs before any writes
     // its outputs (the x array may hold the initial particles)
     if (COOP) coop_barrier(cctr, ++epoch * (uint32_t)G, a.status);
-    const int nkt = npad / 16;
     const float inv_n = 1.f / (float)n;
     float h = 1.f;
     MedianTracker tracker;
-    tracker.reset(L.win_region);
+    tracker.reset();
+    // the softmax references of this wave's tasks, negated, one target per
+    // lane, kept from one iteration to the next
+    float negref[TS];
+    bool have_ref = false;
+
+    // This thread's index, opaque to the compiler: addresses derived from it in
+    // a pass are formed there instead of being kept (and spilled) across all
+    // of them.
+    auto fresh_tid = [&]() {
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        return t;
+    };
+    constexpr uint32_t kSumBlock = 2 * NC * 64;
+    // O[q] = the sums over the source blocks [blk0, blk1) of 2^(exponent) times
+    // the rows of a sums' table (at byte `table`), for the 16-target
+    // tiles of a task (operands b0, b1).  A wave's instructions issue in order
+    // and a SIMD has four waves, so the loop is pipelined by hand: while one
+    // target tile's exponentials and their splits run on the vector ALU, the
+    // matrix cores form the exponents of the tile after it and the sums of the
+    // tile before it, one MFMA every four vector instructions; nothing waits
+    // for a result of its own step.
+    auto weighted_sums = [&](const SourceRows<K4> &src, long table, const u32x4 (&b0)[QT],
+                             const u32x4 (&b1)[QT], int blk0, int blk1, f32x4 (&O)[QT]) {
+        constexpr int kQ = QT;
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        // operands of the sums' table: row (component piece) l % 16, K-slots of
+        // group l / 16
+        const int l = fresh_tid() & 63;
+        const uint32_t sum_off = (uint32_t)((l & (K4 ? 7 : 15)) * 64 + (l >> 4) * 16);
+        u32x4 a00, a01, a10, a11, eh = {0u, 0u, 0u, 0u}, el = {0u, 0u, 0u, 0u};
+        src.load(smem, 2 * blk0, a00, a01);
+        src.load(smem, 2 * blk0 + 1, a10, a11);
+        u32x4 av = *(const u32x4 *)(smem + table + sum_off + (uint32_t)blk0 * kSumBlock);
+        f32x4 T0 = SourceRows<K4>::dot(a00, a01, b0[0], b1[0]), T1 = SourceRows<K4>::dot(a10, a11, b0[0], b1[0]);
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) O[q] = zero;
+        for (int blk = blk0; blk < blk1; ++blk) {
+            const int next = min(blk + 1, blk1 - 1);
+#pragma unroll
+            for (int q = 0; q < kQ; ++q) {
+                const int qn = (q + 1) % kQ, qp = (q + kQ - 1) % kQ;
+                f32x4 N0, N1;
+                if (K4) {
+                    N0 = mfma_bf16(a00, b0[qn], zero);
+                    O[qp] = mfma_f16(av, eh, O[qp]);
+                    N1 = mfma_bf16(a10, b0[qn], zero);
+                    O[qp] = mfma_f16(av, el, O[qp]);
+                } else {
+                    N0 = mfma_bf16(a01, b1[qn], zero);
+                    O[qp] = mfma_f16(av, eh, O[qp]);
+                    N1 = mfma_bf16(a11, b1[qn], zero);
+                    O[qp] = mfma_f16(av, el, O[qp]);
+                    N0 = mfma_bf16(a00, b0[qn], N0);
+                    N1 = mfma_bf16(a10, b0[qn], N1);
+                }
+                if (q == 0) av = *(const u32x4 *)(smem + table + sum_off + (uint32_t)blk * kSumBlock);
+                if (q == kQ - 2) {
+                    // the exponents of the next block start at the next step
+                    src.load(smem, 2 * next, a00, a01);
+                    src.load(smem, 2 * next + 1, a10, a11);
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    T0[r] = R::exp2_(T0[r]);
+                    T1[r] = R::exp2_(T1[r]);
+                }
+                uint32_t hi, lo;
+                split_f16(T0[0], T0[1], neg1, hi, lo); eh[0] = hi; el[0] = lo;
+                split_f16(T0[2], T0[3], neg1, hi, lo); eh[1] = hi; el[1] = lo;
+                split_f16(T1[0], T1[1], neg1, hi, lo); eh[2] = hi; el[2] = lo;
+                split_f16(T1[2], T1[3], neg1, hi, lo); eh[3] = hi; el[3] = lo;
+                T0 = N0;
+                T1 = N1;
+            }
+        }
+        O[kQ - 1] = mfma_f16(av, eh, O[kQ - 1]);
+        O[kQ - 1] = mfma_f16(av, el, O[kQ - 1]);
+    };
+
+    // components of the target operands: [x_k in log2 units, 1] of the scores,
+    // [2 beta x_i, -2 beta] of the Stein direction
+    auto score_target = [&](const float (&xt)[D], float (&v)[NC]) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) v[c] = c == kLast ? 1.f : c < D ? xt[c < D ? c : 0] * rs[c] : 0.f;
+    };
+    auto target_row = [&](const float (&v)[NC], float cst, int g, u32x4 &b0, u32x4 &b1) {
+        uint32_t ph[NC / 2], pm[NC / 2], pl[NC / 2];
+#pragma unroll
+        for (int w = 0; w < NC / 2; ++w) {
+            const Pieces3 s = split3(v[2 * w], v[2 * w + 1]);
+            ph[w] = s.h; pm[w] = s.m; pl[w] = s.l;
+        }
+        target_operand<K4>(ph, pm, pl, cst, g, b0, b1);
+    };
+    // os[c] = sum_j e_kj [2 mh_j, 1] (times ms_scale but for the last) over the
+    // source blocks [blk0, blk1) for this lane's particle kbase + lane,
+    // e_kj = exp2(logit_kj - sref)
+    auto score_sums = [&](int kbase, int blk0, int blk1, float &nref, float (&os)[NC], float &sref) {
+        const int lane = fresh_tid() & 63, g = lane >> 4, col = lane & 15;
+        u32x4 b0[QT], b1[QT];
+        SourceRows<K4> src;
+        src.init(L.off_vt, nppad, L.off_ones, g, col);
+#pragma unroll
+        for (int q = 0; q < QT; ++q) {
+            const float cst = have_ref ? __shfl(nref, 16 * q + col, kWave) : 0.f;
+            b1[q] = u32x4{0u, 0u, 0u, 0u};
+            if (SPLIT && L.b_table) {
+                load_target<K4>(smem, L.off_b, ntl, kbase - tbase + 16 * q + col, g, b0[q], b1[q]);
+                target_constant<K4>(cst, g, b0[q], b1[q]);
+            } else {
+                PieceRow<K4> p;
+                p.load(smem, L.off_x, npad, kbase + 16 * q + col);
+                float v[NC];
+                float xt[D];
+#pragma unroll
+                for (int c = 0; c < D; ++c) xt[c] = p.at(c);
+                score_target(xt, v);
+                target_row(v, cst, g, b0[q], b1[q]);
+            }
+        }
+        bool from_max = !have_ref;
+        for (;;) {
+            if (from_max) {
+                // references from the largest logits of the sources
+                float mx[QT];
+#pragma unroll
+                for (int q = 0; q < QT; ++q) {
+                    mx[q] = -inf;
+                    target_constant<K4>(0.f, g, b0[q], b1[q]);
+                }
+                for (int jt = 2 * blk0; jt < 2 * blk1; ++jt) {
+                    u32x4 a0, a1;
+                    src.load(smem, jt, a0, a1);
+#pragma unroll
+                    for (int q = 0; q < QT; ++q) {
+                        const f32x4 T = SourceRows<K4>::dot(a0, a1, b0[q], b1[q]);
+                        mx[q] = fmax_(mx[q], fmax_(fmax_(T[0], T[1]), fmax_(T[2], T[3])));
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < QT; ++q) {
+                    // no source at all (padding, or weights of zero): reference 0
+                    const float gm = group_max4(mx[q]);
+                    const float nr = gm > 0.1f * kNoSource ? kRefShift - gm : 0.f;
+                    target_constant<K4>(nr, g, b0[q], b1[q]);
+                    if (g == q) nref = nr;
+                }
+            }
+            f32x4 O[QT];
+            weighted_sums(src, L.off_ms, b0, b1, blk0, blk1, O);
+            collect_rows<K4, QT>(O, os);
+            const float s = os[kLast];
+            const bool ok = lane >= kTask || (s >= kRefMinSum && s < 1e30f) || (nref == 0.f && s == 0.f);
+            if (from_max || !__builtin_amdgcn_ballot_w64(!ok)) break;
+            from_max = true;
+        }
+        sref = -nref;
+        if (os[kLast] > 0.f && os[kLast] < 1e30f) nref += kRefShift - __builtin_amdgcn_logf(os[kLast]);
+        else if (nref == 0.f) sref = kNoSource;  // nothing to merge
+    };
+    // score row of particle k: the observation's gradient, then the transition
+    // term from its softmax sums
+    auto score_grad = [&](int k, float (&s)[D], float (&xt)[D]) {
+        PieceRow<K4> p;
+        p.load(smem, L.off_x, npad, k);
+        float xa[D];
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+            xt[c] = p.at(c);
+            xa[c] = xt[c] + ref[c];
+        }
+        F::grad(m, sz, mk, xa, s);
+    };
+    auto score_transition = [&](const float *os, const float (&xt)[D], float (&s)[D]) {
+        if (a.trans_mode == 0) {
+            const float inv_sum = ms_inv / os[kLast];
+#pragma unroll
+            for (int c = 0; c < D; ++c) {
+                const float mb = os[c] * inv_sum * 0.5f / rs[c];
+                s[c] -= (xt[c] - mb) * m.inv_q[c];
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < D; ++c) s[c] -= (xt[c] - mbar_all[c]) * m.inv_q[c];
+        }
+    };
+    // the splits' partial sums of target kl, merged in split order (softmax
+    // sums rebased to their largest reference)
+    auto merge_part = [&](int kl, int ns, bool softmax, float (&os)[NC]) {
+        float mx = -inf;
+        for (int sp = 0; softmax && sp < ns; ++sp) mx = fmax_(mx, PART[((long)sp * ntl + kl) * kPart + NC]);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) os[c] = 0.f;
+        for (int sp = 0; sp < ns; ++sp) {
+            const float *pp = PART + ((long)sp * ntl + kl) * kPart;
+            const float w = softmax ? R::exp2_(pp[NC] - mx) : 1.f;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) os[c] += pp[c] * w;
+        }
+    };
+
+    // ---- exact lower median of the half squared distances ----
+    const uint32_t M = (uint32_t)((long)n * (n - 1) / 2);
+    const uint32_t rank = M > 0 ? (M - 1) / 2 : 0u;
+    const uint32_t cap = (uint32_t)L.win_cap;
+    uint32_t *hist = (uint32_t *)WIN;  // histograms use the window buffer
+    // red[10], red[11]: values in the window, values below it (of this
+    // workgroup; red[10] beyond `cap` where they do not fit)
+    // a walk over this wave's share of the distances
+    const int nblocks = npad / 32 * (npad / 32 + 1) / 2;
+    auto walk = [&](float origin, auto &&fn) {
+        const int v = gi * nwaves + wave, nv = G * nwaves;
+        BlockWalker<K4> walker;
+        walker.start(smem, L.off_x, npad, L.off_ones, fresh_tid() & 63, nblocks * v / nv, nblocks * (v + 1) / nv);
+        walker.visit_all(origin, fn);
+    };
+    // adds the lanes' counts of distances below the window or range
+    auto add_below = [&](uint32_t count) {
+        count = wave_count(count);
+        if (lane == 0) atomicAdd(&red[11], count);
+    };
+    auto window_walk = [&]() {
+        tracker.below = 0;
+        walk(tracker.lo, [&](const f32x4 (&Dv)[4]) { tracker.visit(Dv, WIN, cap, &red[10]); });
+        add_below(tracker.below);
+    };
+    // COOP: this workgroup's counts and kept values to the exchange area ...
+    int parity = 0;  // of the exchange buffers: a workgroup may still read the last ones
+    auto publish_window = [&]() {
+        const uint32_t kept = red[10];
+        float *vals = cvals + ((long)parity * G + gi) * kCoopWinCap;
+        for (uint32_t q = tid; q < min(kept, cap); q += nt) vals[q] = WIN[q];
+        if (tid == 0) {
+            cinfo[(parity * G + gi) * 2 + 0] = kept;
+            cinfo[(parity * G + gi) * 2 + 1] = red[11];
+        }
+    };
+    // ... and, past a barrier of the sequence's workgroups, everybody's into
+    // this workgroup's (red[10] beyond `cap` where they do not fit)
+    auto collect_window = [&]() {
+        uint32_t *ci = (uint32_t *)redf;  // [32]
+        if (tid < 2 * G) ci[tid] = cinfo[parity * G * 2 + tid];
+        __syncthreads();
+        uint32_t kept = 0, below = 0;
+        for (int q = 0; q < G; ++q) {
+            const uint32_t c = ci[2 * q];
+            kept = c > cap || kept > cap ? cap + 1 : kept + c;
+            below += ci[2 * q + 1];
+        }
+        if (kept <= cap) {
+            for (uint32_t e = tid; e < kept; e += nt) {
+                uint32_t off = 0;
+                int q = 0;
+                while (e >= off + ci[2 * q]) off += ci[2 * q++];
+                WIN[e] = cvals[((long)parity * G + q) * kCoopWinCap + (e - off)];
+            }
+        }
+        if (tid == 0) {
+            red[10] = kept;
+            red[11] = below;
+        }
+        parity ^= 1;
+        __syncthreads();
+    };
+    // a histogram over every workgroup's distances (COOP)
+    auto share_hist = [&]() {
+        if constexpr (COOP) {
+            uint32_t *rh = crhist + (long)parity * G * kBins;
+            for (int q = tid; q < kBins; q += nt) rh[(long)gi * kBins + q] = hist[q];
+            if (tid == 0) cinfo[(parity * G + gi) * 2 + 1] = red[11];
+            coop_barrier(cctr, ++epoch * (uint32_t)G, a.status);
+            uint32_t below = 0;
+            for (int q = 0; q < G; ++q) below += cinfo[(parity * G + q) * 2 + 1];
+            for (int q = tid; q < kBins; q += nt) {
+                uint32_t c = 0;
+                for (int gg = 0; gg < G; ++gg) c += rh[(long)gg * kBins + q];
+                hist[q] = c;
+            }
+            if (tid == 0) red[11] = below;
+            parity ^= 1;
+            __syncthreads();
+        }
+    };
+    auto clear_counts = [&]() {
+        __syncthreads();
+        if (tid < 2) red[10 + tid] = 0;
+    };
+    // whether the window of the last walk holds the median
+    auto in_window = [&]() { return rank >= red[11] && rank - red[11] < red[10] && red[10] <= cap; };
+    // the median from the window's values: by the last wave (up to kSelectMax
+    // values), or by all
+    auto select_by_wave = [&]() {
+        const float v = window_select(WIN, red[10], rank - red[11], tracker.lo, tracker.lo + tracker.width);
+        if (lane == 0) red[5] = __float_as_uint(v);
+    };
+    // without a window: histogram passes, then a window; a radix selection
+    // (digits of 11, 11 and 10 bits) where values tie too heavily for those
+    auto median_from_range = [&]() {
+        float hsum = 0.f;
+        for (int i = lane; i < n; i += kWave) {
+            PieceRow<K4> p;
+            p.load(smem, L.off_x, npad, i);
+            hsum += p.at(kLast);
+        }
+        MedianRange rg;
+        rg.a = 0.f;
+        rg.b = uniform(4.004f * wave_sum(hsum) / (float)n + 1e-37f);
+        for (int pass = 0; pass < kMaxHistPasses; ++pass) {
+            clear_counts();
+            for (int q = tid; q < kBins; q += nt) hist[q] = 0;
+            __syncthreads();
+            const float sc = rg.scale();
+            uint32_t below = 0;
+            walk(0.f, [&](const f32x4 (&Dv)[4]) { rg.visit(Dv, hist, sc, below); });
+            add_below(below);
+            __syncthreads();
+            share_hist();
+            if (rank < red[11]) break;
+            if (wave == 0) radix_digit(hist, rank - red[11], red, lane);
+            __syncthreads();
+            const uint32_t bin = red[0], count = hist[red[0]];
+            rg.narrow(bin);
+            if (2 * count <= cap) {
+                tracker.lo = uniform(rg.a);
+                tracker.width = uniform(rg.b - rg.a);
+                clear_counts();
+                __syncthreads();
+                window_walk();
+                __syncthreads();
+                if constexpr (COOP) {
+                    publish_window();
+                    coop_barrier(cctr, ++epoch * (uint32_t)G, a.status);
+                    collect_window();
+                }
+                if (!in_window()) break;
+                return buffer_select(WIN, red[10], rank - red[11], tracker.lo, tracker.lo + tracker.width, whist, red);
+            }
+        }
+        uint32_t prefix = 0, pmask = 0, rk = rank;
+        for (int pass = 0; pass < 3; ++pass) {
+            const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
+            const uint32_t dmask = pass == 2 ? 0x3ffu : 0x7ffu;
+            __syncthreads();
+            for (int q = tid; q < kBins; q += nt) hist[q] = 0;
+            __syncthreads();
+            walk(0.f, [&](const f32x4 (&Dv)[4]) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const uint32_t key = __float_as_uint(fmax_(Dv[r >> 2][r & 3], 0.f));
+                    if ((key & pmask) == prefix) atomicAdd(&hist[(key >> shift) & dmask], 1u);
+                }
+            });
+            __syncthreads();
+            share_hist();
+            if (wave == 0) radix_digit(hist, rk, red, lane);
+            __syncthreads();
+            prefix |= red[0] << shift;
+            rk = red[1];
+            pmask |= dmask << shift;
+        }
+        tracker.density = 0.f;  // no window to measure it in
+        return __uint_as_float(prefix);
+    };
 
     for (int it = 0; a.do_svgd && it < a.n_iter; ++it) {
-        // (1) the bandwidth needs the exact lower median of the squared
-        // distances of the current particles; its window pass is spread over
-        // the score pass, which leaves the particles unchanged
-        const bool need_median = a.bw_mode == 0 || it == 0;
-        if (need_median) tracker.plan(whist);
-        TileWalker<K4, COOP> walker;
-        if (tracker.active) {
-            if (COOP)
-                walker.start(X8, npad, g, col, gi * nwaves + wave, G * nwaves);
-            else
-                walker.start(X8, npad, g, col);
-        }
-        float *wregion = WIN + wave * L.win_region;
-        auto walk_step = [&]() {
-            f32x4 W0, W1;
-            walker.issue(X8, g, col, W0, W1);
-            tracker.visit(W0, false, wregion);
-            if (walker.second()) tracker.visit(W1, false, wregion);
-            walker.advance(X8, g, col);
+        const bool need_median = (a.bw_mode == 0 || it == 0) && M > 0;
+        const bool window = need_median && tracker.plan(M, cap);
+        float srow[TS][D];        // scores of this thread's particles
+        float smax = 0.f, xmax = 0.f;  // largest |s|, |x| of its particles
+        auto note_max = [&](const float (&s)[D], const float (&xt)[D]) {
+#pragma unroll
+            for (int c = 0; c < D; ++c) {
+                smax = fmax_(smax, fabsf(s[c]));
+                xmax = fmax_(xmax, fabsf(xt[c]));
+            }
         };
 
-        // (2) scores
-        // score_sums: osum = sum_j e_kj [2 mh_j, 1] over the source tiles
-        // [j0, j1) for this lane's particle kbase + lane, relative to the
-        // reference sref (e_kj = exp2(logit_kj - sref))
-        auto score_sums = [&](int kbase, int j0, int j1, float (&osum)[8], float &sref) {
-            {
-                f32x4 cm[kTilesPerWave];  // -reference of each particle column, as the accumulator input
-                float bx0[kTilesPerWave], bx1[kTilesPerWave];
-#pragma unroll
-                for (int q = 0; q < kTilesPerWave; ++q) {
-                    const int kk = kbase + 16 * q + col;
-                    const int kd0 = g, kd1 = 4 + g;
-                    bx0[q] = kd0 < D ? X8[(long)kk * 8 + kd0] * rs[kd0] : (K4 && kd0 == 3 ? 1.f : 0.f);
-                    bx1[q] = kd1 < D ? X8[(long)kk * 8 + kd1] * rs[kd1] : (kd1 == 7 ? 1.f : 0.f);
-                    cm[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-                }
-                // Sums on the 4x4x1 (16-block) MFMA straight from the logit
-                // tile layout: register r of lane l holds e of source
-                // 16 jt + 4 (l / 16) + r and particle kbase + 16 q + l % 16, so
-                // block b = l / 4 takes B = that register and A = table rows
-                // 4 ch + l % 4 of its source; lane l of O4[ch][q] accumulates
-                // rows 4 ch + i (register i) of particle kbase + 16 q + l % 16
-                // over the source quarter l / 16.  With K4 one group holds
-                // rows 2 mh_0..2 and the 1 (table row 7) as its row 3.
-                constexpr int NGS = K4 ? 1 : 2;
-                f32x4 O4[NGS][kTilesPerWave];
-#pragma unroll
-                for (int ch = 0; ch < NGS; ++ch)
-#pragma unroll
-                    for (int q = 0; q < kTilesPerWave; ++q) O4[ch][q] = f32x4{0.f, 0.f, 0.f, 0.f};
-                // four consecutive sources 4 (l / 16) + r of rows l % 4, 4 + l % 4
-                const float *vt0 = VT + (long)(K4 && (lane & 3) == 3 ? 7 : (lane & 3)) * nppad + 4 * g;
-                const float *vt1 = VT + (long)(4 + (lane & 3)) * nppad + 4 * g;
-                // logit A operands: K-row g (2 mh), K-row 4 + g (row 7 of the
-                // table, the 1, becomes c'_j in K-row 7); with K4, c'_j in
-                // K-row 3 of the one chunk
-                const float *am0p = VT + (long)(K4 && g == 3 ? 8 : g) * nppad + col;
-                const float *am1p = VT + (long)(g == 3 ? 8 : 4 + g) * nppad + col;
-                // logits of tile jt relative to the column references
-                auto logits = [&](int jt, f32x4 (&Lo)[kTilesPerWave]) {
-                    const float am0 = am0p[jt * 16];
-#pragma unroll
-                    for (int q = 0; q < kTilesPerWave; ++q) Lo[q] = mfma16(am0, bx0[q], cm[q]);
-                    if (!K4) {
-                        const float am1 = am1p[jt * 16];
-#pragma unroll
-                        for (int q = 0; q < kTilesPerWave; ++q) Lo[q] = mfma16(am1, bx1[q], Lo[q]);
-                    }
-                };
-                // Raises the reference of the columns of a relative logit tile
-                // whose maximum lies more than 2^64 above it (all four lane
-                // groups of a column agree), rescaling the sums and the tile;
-                // with `first`, sets the references to the tile's maxima.  The
-                // test compares the bit patterns as integers: for a positive
-                // bound that orders like the floats, and NaN also triggers.
-                auto rebase = [&](f32x4 (&T)[kTilesPerWave], bool first) {
-                    int mxi = __float_as_int(T[0][0]);
-#pragma unroll
-                    for (int q = 0; q < kTilesPerWave; ++q)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) mxi = max(mxi, __float_as_int(T[q][r]));
-                    if (first || __builtin_amdgcn_ballot_w64(mxi > __float_as_int(kRescaleGap))) {
-                        float shq[kTilesPerWave];
-#pragma unroll
-                        for (int q = 0; q < kTilesPerWave; ++q) {
-                            const float lmax = fmax_(fmax_(T[q][0], T[q][1]), fmax_(T[q][2], T[q][3]));
-                            const float gm = group_max4(lmax);
-                            const bool up = first ? gm > -inf : gm > kRescaleGap;
-                            shq[q] = up ? gm : 0.f;
-                            T[q] -= shq[q];
-                            cm[q] -= shq[q];
-                        }
-                        if (!first) {
-#pragma unroll
-                            for (int q = 0; q < kTilesPerWave; ++q) {
-                                const float sc = R::exp2_(-shq[q]);
-#pragma unroll
-                                for (int ch = 0; ch < NGS; ++ch) O4[ch][q] *= sc;
-                            }
-                        }
-                    }
-                };
-                // One logit tile per step; with WALK, two tiles of the median
-                // window pass ride along.
-                auto score_loop = [&](auto walk_tag) {
-                    constexpr bool WALK = decltype(walk_tag)::value;
-                    // exponentials and sums of a relative logit tile; with
-                    // WALK the median walk's two tiles W0, W1 (issued before
-                    // the logits are checked) are visited after the sums
-                    auto body = [&](int jt, f32x4 (&T)[kTilesPerWave], const f32x4 &W0, const f32x4 &W1) {
-                        f32x4 va[NGS];
-                        va[0] = *(const f32x4 *)(vt0 + jt * 16);
-                        if (!K4) va[NGS - 1] = *(const f32x4 *)(vt1 + jt * 16);
-#pragma unroll
-                        for (int q = 0; q < kTilesPerWave; ++q)
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) T[q][r] = R::exp2_(T[q][r]);
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-#pragma unroll
-                            for (int q = 0; q < kTilesPerWave; ++q)
-#pragma unroll
-                                for (int ch = 0; ch < NGS; ++ch)
-                                    O4[ch][q] = __builtin_amdgcn_mfma_f32_4x4x1f32(va[ch][r], T[q][r], O4[ch][q], 0,
-                                                                                   0, 0);
-                        if (WALK && !walker.done()) {
-                            tracker.visit(W0, false, wregion);
-                            if (walker.second()) tracker.visit(W1, false, wregion);
-                            walker.advance(X8, g, col);
-                        }
-                    };
-                    if (WALK) {
-                        // one buffer (the walk's registers leave no room for
-                        // two); the walk's MFMAs go between the logits and
-                        // their check, which waits for them
-                        f32x4 T[kTilesPerWave], W0, W1;
-                        logits(j0, T);
-                        walker.issue(X8, g, col, W0, W1);
-                        rebase(T, true);
-                        body(j0, T, W0, W1);
-                        for (int jt = j0 + 1; jt < j1; ++jt) {
-                            if (kBalance && (jt & 1) == 0) bal.step();
-                            logits(jt, T);
-                            walker.issue(X8, g, col, W0, W1);
-                            rebase(T, false);
-                            body(jt, T, W0, W1);
-                        }
-                    } else {
-                        // the logits of tile jt + 1 are issued (and checked)
-                        // around the exponentials and sums of tile jt
-                        const f32x4 none = {0.f, 0.f, 0.f, 0.f};
-                        auto tile = [&](int jt, f32x4 (&T)[kTilesPerWave], f32x4 (&Tn)[kTilesPerWave]) {
-                            logits(min(jt + 1, j1 - 1), Tn);
-                            body(jt, T, none, none);
-                            rebase(Tn, false);
-                        };
-                        f32x4 TA[kTilesPerWave], TB[kTilesPerWave];
-                        logits(j0, TA);
-                        rebase(TA, true);
-                        for (int jt = j0; jt < j1; jt += 2) {
-                            if (kBalance) bal.step();
-                            tile(jt, TA, TB);
-                            if (jt + 1 < j1) tile(jt + 1, TB, TA);
-                        }
-                    }
-                };
-                if (tracker.active && !walker.done())
-                    score_loop(std::true_type{});
-                else
-                    score_loop(std::false_type{});
-                // lane l takes particle kbase + l: tile q = l / 16, summed
-                // over the four source quarters; its reference is the one of
-                // column l % 16 of tile q, which lane l holds
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    osum[i] = sum_quarters_scatter(O4[0][0][i], O4[0][1][i], O4[0][2][i], O4[0][3][i]);
-                    if (!K4)
-                        osum[4 + i] = sum_quarters_scatter(O4[NGS - 1][0][i], O4[NGS - 1][1][i], O4[NGS - 1][2][i],
-                                                           O4[NGS - 1][3][i]);
-                }
-                if (K4) {
-                    // the sum of e sits in row 3; rows 3..6 carry nothing
-                    osum[7] = osum[3];
-#pragma unroll
-                    for (int i = 3; i < 7; ++i) osum[i] = 0.f;
-                }
-                const int qq = lane >> 4;
-                float cref = cm[0][0];
-#pragma unroll
-                for (int q = 1; q < kTilesPerWave; ++q) cref = qq == q ? cm[q][0] : cref;
-                sref = -cref;
+        // (1) scores
+        float os[NC], sref = 0.f;
+        const int sp = SPLIT ? wave / ntasks : 0;
+        if constexpr (SPLIT) {
+            // this wave's split of its task's sources
+            if (a.trans_mode == 0 && sp < L.ns_sc) {
+                const int nb = nppad / 32;
+                score_sums(tbase + wave % ntasks * kTask, sp * nb / L.ns_sc, (sp + 1) * nb / L.ns_sc, negref[0], os, sref);
             }
-        };
-        if (split) {
-            // this wave's split of its task's sources: partial sums to LDS,
-            // merged per particle once h is known
-            if (a.trans_mode == 0 && wave < ntasks * L.ns_sc) {
-                const int task = wave % ntasks, sp = wave / ntasks;
-                float osum[8], sref;
-                score_sums(tbase + task * 64, sp * njt / L.ns_sc, (sp + 1) * njt / L.ns_sc, osum, sref);
-                float *pp = PART + ((long)sp * ntasks * 64 + task * 64 + lane) * kPartStride;
+        } else {
 #pragma unroll
-                for (int c = 0; c < 8; ++c) pp[c] = osum[c];
-                pp[8] = sref;
-            }
-        }
-        for (int task = wave; !split && task < ntasks; task += nwaves) {
-            const int kbase = task * 64;
-            float osum[8];  // trans_mode 0: sum_j e_kj [2 mh_j, 1] of this lane's particle kbase + lane
-            if (a.trans_mode == 0) {
-                float sref;
-                score_sums(kbase, 0, njt, osum, sref);
-            }
-            {
-                const int k = kbase + lane;
-                float srow[8];
-#pragma unroll
-                for (int c = 0; c < 8; ++c) srow[c] = 0.f;
-                srow[7] = 1.f;  // the Stein pass sums kappa through this column
+            for (int ts = 0; ts < TS; ++ts) {
+                const int task = wave + ts * nwaves;
+                if (task >= ntasks) break;
+                if (a.trans_mode == 0) score_sums(task * kTask, 0, nppad / 32, negref[ts], os, sref);
+                const int k = task * kTask + lane;
                 if (k < n) {
-                    float xt[D], xa[D], gr[D];
-#pragma unroll
-                    for (int c = 0; c < D; ++c) {
-                        xt[c] = X8[(long)k * 8 + c];
-                        xa[c] = xt[c] + ref[c];
-                    }
-                    F::grad(m, sz, mk, xa, gr);
-                    if (a.trans_mode == 0) {
-                        const float inv_sum = 1.f / osum[7];
-#pragma unroll
-                        for (int c = 0; c < D; ++c) {
-                            const float mb = osum[c] * inv_sum * 0.5f / rs[c];
-                            srow[c] = gr[c] - (xt[c] - mb) * m.inv_q[c];
-                        }
-                    } else {
-#pragma unroll
-                        for (int c = 0; c < D; ++c) srow[c] = gr[c] - (xt[c] - mbar_all[c]) * m.inv_q[c];
-                    }
+                    float xt[D];
+                    score_grad(k, srow[ts], xt);
+                    score_transition(os, xt, srow[ts]);
+                    note_max(srow[ts], xt);
                 }
-#pragma unroll
-                for (int c = 0; c < 8; ++c) S8[(long)k * 8 + c] = srow[c];
             }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
-        __builtin_amdgcn_s_setprio(0);
-        if (tracker.active) {
-            while (!walker.done()) walk_step();
-            walker.diagonals(X8, g, col, [&](const f32x4 &Dd, bool dg) { tracker.visit(Dd, dg, wregion); });
+        have_ref = true;
+
+        // (2) the bandwidth needs the exact lower median of the squared
+        // distances of the current particles: their window pass
+        if (window) window_walk();
+        // (the multi-workgroup mode keeps the partial sums over the sums' tables)
+        if (COOP) __syncthreads();
+        if constexpr (SPLIT) {
+            // partial sums of the splits to LDS
+            if (a.trans_mode == 0 && sp < L.ns_sc && lane < kTask) {
+                float *pp = PART + ((long)sp * ntl + wave % ntasks * kTask + lane) * kPart;
+#pragma unroll
+                for (int c = 0; c < NC; ++c) pp[c] = os[c];
+                pp[NC] = sref;
+            }
         }
         __syncthreads();
+        bool found = !COOP && window && in_window();
+        // the last wave ranks the window's values while the first ones merge
+        // the splits
+        if (found && red[10] <= kSelectMax && wave == nwaves - 1) select_by_wave();
+        if constexpr (SPLIT) {
+            if (tid < ntl && tbase + tid < n) {
+                if (a.trans_mode == 0) merge_part(tid, L.ns_sc, true, os);
+                float xt[D];
+                score_grad(tbase + tid, srow[0], xt);
+                score_transition(os, xt, srow[0]);
+                if (!COOP) note_max(srow[0], xt);
+            }
+        }
         if constexpr (COOP) {
-            // score rows of this workgroup's targets from the splits' partial
-            // sums (rebased to their largest reference, summed in split
-            // order), to the exchange area: the largest reference per target,
-            // the rebased sums per (target, row) into S8, then the rows
-            const int ntl = ntasks * 64;
-            float *mref = (float *)hist;  // [ntl] (the radix histogram is free here)
-            if (a.trans_mode == 0) {
-                for (int kl = tid; kl < ntl; kl += nt) {
-                    float mx = -inf;
-                    for (int sp = 0; sp < L.ns_sc; ++sp)
-                        mx = fmax_(mx, PART[((long)sp * ntl + kl) * kPartStride + 8]);
-                    mref[kl] = mx;
-                }
-                __syncthreads();
-                for (int e = tid; e < ntl * 8; e += nt) {
-                    const int kl = e >> 3, c = e & 7;
-                    const float mx = mref[kl];
-                    float acc = 0.f;
-                    for (int sp = 0; sp < L.ns_sc; ++sp) {
-                        const float *pp = PART + ((long)sp * ntl + kl) * kPartStride;
-                        acc += pp[c] * R::exp2_(pp[8] - mx);
-                    }
-                    S8[(long)(tbase + kl) * 8 + c] = acc;
-                }
-                __syncthreads();
+            // this workgroup's score rows and its share of the window pass to
+            // the exchange area
+            if (tid < ntl) {
+                float *cs = cS + (long)(tbase + tid) * 8;
+#pragma unroll
+                for (int c = 0; c < D; ++c) cs[c] = tbase + tid < n ? srow[0][c] : 0.f;
             }
-            for (int kl = tid; kl < ntl; kl += nt) {
-                const int k = tbase + kl;
-                float srow[8];
-#pragma unroll
-                for (int c = 0; c < 8; ++c) srow[c] = 0.f;
-                srow[7] = 1.f;
-                if (k < n) {
-                    float xt[D], xa[D], gr[D];
-#pragma unroll
-                    for (int c = 0; c < D; ++c) {
-                        xt[c] = X8[(long)k * 8 + c];
-                        xa[c] = xt[c] + ref[c];
-                    }
-                    F::grad(m, sz, mk, xa, gr);
-                    if (a.trans_mode == 0) {
-                        const float inv_sum = 1.f / S8[(long)k * 8 + 7];
-#pragma unroll
-                        for (int c = 0; c < D; ++c) {
-                            const float mb = S8[(long)k * 8 + c] * inv_sum * 0.5f / rs[c];
-                            srow[c] = gr[c] - (xt[c] - mb) * m.inv_q[c];
-                        }
-                    } else {
-#pragma unroll
-                        for (int c = 0; c < D; ++c) srow[c] = gr[c] - (xt[c] - mbar_all[c]) * m.inv_q[c];
-                    }
-                }
-#pragma unroll
-                for (int c = 0; c < 8; ++c) cS[(long)k * 8 + c] = srow[c];
-            }
-            // this workgroup's share of the window pass: counts, its kept
-            // distances in wave order, its histogram
-            if (need_median && tracker.active) {
-                if (lane == 0) {
-                    red[26 + wave] = tracker.below;
-                    red[10 + wave] = tracker.kept;
-                }
-                __syncthreads();
-                uint32_t below = 0, kept = 0, off_w = 0;
-                bool ovf = false;
-                for (int q = 0; q < nwaves; ++q) {
-                    const uint32_t c = red[10 + q];
-                    ovf |= c > (uint32_t)L.win_region;
-                    if (q < wave) off_w += c;
-                    below += red[26 + q];
-                    kept += c;
-                }
-                if (!ovf)
-                    for (uint32_t q = lane; q < tracker.kept; q += kWave)
-                        cvals[(long)gi * kCoopWinCap + off_w + q] = wregion[q];
-                for (int q = tid; q < 256; q += nt) cwhist[gi * 256 + q] = whist[q];
-                if (tid == 0) {
-                    cinfo[gi * 4 + 0] = below;
-                    cinfo[gi * 4 + 1] = ovf ? 0u : kept;
-                    cinfo[gi * 4 + 2] = ovf ? 1u : 0u;
-                }
-            }
+            if (window) publish_window();
             coop_barrier(cctr, ++epoch * (uint32_t)G, a.status);
-            // every score row
-            for (int k = tid; k < npad; k += nt)
+            // every score row: thread tid takes particle tid
+            if (tid < n) {
+                float xt[D];
+                PieceRow<K4> p;
+                p.load(smem, L.off_x, npad, tid);
 #pragma unroll
-                for (int c = 0; c < 8; ++c) S8[(long)k * 8 + c] = cS[(long)k * 8 + c];
-            if (need_median) {
-                // the median from every workgroup's share: the same value in all
-                const uint32_t M = (uint32_t)((long)n * (n - 1) / 2);
-                const uint32_t rank = M > 0 ? (M - 1) / 2 : 0u;
-                float med = __builtin_nanf("");
-                bool done = M == 0;
-                if (!done && tracker.active) {
-                    // the workgroups' counts, staged in LDS (one global round trip)
-                    uint32_t *ci = (uint32_t *)redf;  // [16] kept, [16] below, [16] overflow
-                    if (tid < G) {
-                        ci[tid] = cinfo[tid * 4 + 1];
-                        ci[16 + tid] = cinfo[tid * 4 + 0];
-                        ci[32 + tid] = cinfo[tid * 4 + 2];
-                    }
-                    __syncthreads();
-                    uint32_t below = 0, nin = 0;
-                    bool ovf = false;
-                    for (int q = 0; q < G; ++q) {
-                        below += ci[16 + q];
-                        nin += ci[q];
-                        ovf |= ci[32 + q] != 0u;
-                    }
-                    tracker.density = uniform((float)nin / (tracker.hi - tracker.lo));
-                    if (!ovf && rank >= below && rank < below + nin && nin <= (uint32_t)L.win_cap) {
-                        // every workgroup's kept distances into this one's window
-                        // buffer (workgroup order), their histogram, then the
-                        // window selection of the one-workgroup kernel
-                        for (uint32_t e = tid; e < nin; e += nt) {
-                            uint32_t off = 0;
-                            int gg = 0;
-                            while (e >= off + ci[gg]) {
-                                off += ci[gg];
-                                ++gg;
-                            }
-                            WIN[e] = cvals[(long)gg * kCoopWinCap + (e - off)];
-                        }
-                        for (int q = tid; q < 256; q += nt) whist[q] = 0;
-                        if (tid == 0) red[10] = nin;
-                        __syncthreads();
-                        const uint32_t klo = __float_as_uint(tracker.lo);
-                        for (uint32_t e = tid; e < nin; e += nt)
-                            atomicAdd(&whist[(__float_as_uint(WIN[e]) - klo) >> tracker.wshift], 1u);
-                        __syncthreads();
-                        med = window_select(WIN, red + 10, 1, L.win_cap, rank - below, klo,
-                                            __float_as_uint(tracker.hi), tracker.wshift, whist, red, (float *)whist);
-                        done = true;
-                    } else if (!ovf && rank >= below && rank < below + nin) {
-                        // more kept distances than this buffer holds: the summed
-                        // histograms locate the median's bin, and only that bin's
-                        // distances are gathered
-                        const uint32_t r = rank - below;
-                        for (int q = tid; q < 256; q += nt) {
-                            uint32_t c = 0;
-                            for (int gg = 0; gg < G; ++gg) c += cwhist[gg * 256 + q];
-                            whist[q] = c;
-                        }
-                        __syncthreads();
-                        if (wave == 0) {
-                            typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-                            const u32x4_t c = *(const u32x4_t *)(whist + lane * 4);
-                            const uint32_t cnt = c[0] + c[1] + c[2] + c[3];
-                            const uint32_t incl = wave_incl_scan(cnt, lane);
-                            const uint32_t excl = incl - cnt;
-                            if (r >= excl && r < incl) {
-                                uint32_t rr = r - excl;
-#pragma unroll
-                                for (int q = 0; q < 4; ++q) {
-                                    if (rr < c[q]) {
-                                        red[2] = (uint32_t)(lane * 4 + q);
-                                        red[3] = rr;
-                                        red[4] = c[q];
-                                        break;
-                                    }
-                                    rr -= c[q];
-                                }
-                            }
-                            if (lane == 0) red[6] = 0;
-                        }
-                        __syncthreads();
-                        const uint32_t bin = red[2], rr = red[3], cb = red[4];
-                        if (cb <= (uint32_t)kWave) {
-                            float *cand = (float *)whist;  // the histogram is dead once the bin is known
-                            const uint32_t klo = __float_as_uint(tracker.lo);
-                            for (int gg = 0; gg < G; ++gg) {
-                                const uint32_t cnt = ci[gg];
-                                for (uint32_t q = tid; q < cnt; q += nt) {
-                                    const float v = cvals[(long)gg * kCoopWinCap + q];
-                                    if (((__float_as_uint(v) - klo) >> tracker.wshift) == bin)
-                                        cand[atomicAdd(&red[6], 1u)] = v;
-                                }
-                            }
-                            __syncthreads();
-                            if (wave == 0 && (uint32_t)lane < cb) {
-                                const float v = cand[lane];
-                                uint32_t less = 0, leq = 0;
-                                for (uint32_t q = 0; q < cb; ++q) {
-                                    const float u = cand[q];
-                                    less += u < v ? 1u : 0u;
-                                    leq += u <= v ? 1u : 0u;
-                                }
-                                if (less <= rr && rr < leq) red[5] = __float_as_uint(v);
-                            }
-                            __syncthreads();
-                            med = __uint_as_float(red[5]);
-                            done = true;
-                        }
-                        // a bin of more than 64 (heavy ties): the radix selection below
-                    }
+                for (int c = 0; c < D; ++c) {
+                    srow[0][c] = cS[(long)tid * 8 + c];
+                    xt[c] = p.at(c);
                 }
-                if (!done) {
-                    // radix selection (digits of 11, 11 and 10 bits) over every
-                    // workgroup's share of the distances, one barrier per digit
-                    uint32_t prefix = 0, pmask = 0, rk = rank;
-                    for (int pass = 0; pass < 3; ++pass) {
-                        const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
-                        const uint32_t dmask = pass == 2 ? 0x3ffu : 0x7ffu;
-                        for (int q = tid; q < kBins; q += nt) hist[q] = 0;
-                        __syncthreads();
-                        auto count = [&](const f32x4 &Dv, bool diag) {
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) {
-                                const uint32_t key = __float_as_uint(fmax_(Dv[r], 0.f));
-                                const bool valid = !diag || ((diag_lanes(r) >> lane) & 1ull);
-                                if (valid && (key & pmask) == prefix) atomicAdd(&hist[(key >> shift) & dmask], 1u);
-                            }
-                        };
-                        TileWalker<K4, true> rw;
-                        rw.start(X8, npad, g, col, gi * nwaves + wave, G * nwaves);
-                        while (!rw.done()) {
-                            f32x4 D0, D1;
-                            rw.issue(X8, g, col, D0, D1);
-                            count(D0, false);
-                            if (rw.second()) count(D1, false);
-                            rw.advance(X8, g, col);
-                        }
-                        rw.diagonals(X8, g, col, count);
-                        __syncthreads();
-                        uint32_t *rh = crhist + (long)(pass & 1) * G * kBins;
-                        for (int q = tid; q < kBins; q += nt) rh[(long)gi * kBins + q] = hist[q];
-                        coop_barrier(cctr, ++epoch * (uint32_t)G, a.status);
-                        for (int q = tid; q < kBins; q += nt) {
-                            uint32_t c = 0;
-                            for (int gg = 0; gg < G; ++gg) c += rh[(long)gg * kBins + q];
-                            hist[q] = c;
-                        }
-                        __syncthreads();
-                        if (wave == 0) {
-                            constexpr int per = kBins / kWave;
-                            uint32_t cnt = 0;
-                            for (int q = 0; q < per; ++q) cnt += hist[lane * per + q];
-                            const uint32_t incl = wave_incl_scan(cnt, lane);
-                            const uint32_t excl = incl - cnt;
-                            if (lane == 0) { red[0] = 0; red[1] = 0; }
-                            __builtin_amdgcn_wave_barrier();
-                            if (rk >= excl && rk < incl) {
-                                uint32_t r2 = rk - excl;
-                                for (int q = 0; q < per; ++q) {
-                                    const uint32_t hq = hist[lane * per + q];
-                                    if (r2 < hq) { red[0] = (uint32_t)(lane * per + q); red[1] = r2; break; }
-                                    r2 -= hq;
-                                }
-                            }
-                        }
-                        __syncthreads();
-                        prefix |= red[0] << shift;
-                        rk = red[1];
-                        pmask |= dmask << shift;
-                        __syncthreads();
-                    }
-                    med = __uint_as_float(prefix);
-                }
-                med = uniform(med);
-                tracker.med2 = tracker.med1;
-                tracker.med1 = med;
-                tracker.have = tracker.have < 2 ? tracker.have + 1 : 2;
-                tracker.active = false;
-                h = uniform(bandwidth_from_median(med, n, a.bw_scale));
+                note_max(srow[0], xt);
             }
-        } else if (need_median) {
-            const float med = tracker.finish<K4>(X8, n, npad, WIN, hist, red);
-            h = uniform(bandwidth_from_median(med, n, a.bw_scale));
+            if (window) {
+                collect_window();
+                found = in_window();
+                if (found && red[10] <= kSelectMax && wave == nwaves - 1) select_by_wave();
+            }
+        }
+        // the largest |s| and |x| bound the Stein sums' operands
+        smax = wave_max_abs(smax);
+        xmax = wave_max_abs(xmax);
+        if (lane == 0) {
+            redf[32 + wave] = smax;
+            redf[48 + wave] = xmax;
+        }
+        __syncthreads();
+        if (need_median || it == 0) {
+            float med = __builtin_nanf("");
+            if (need_median) {
+                if (window) tracker.density = uniform((float)min(red[10], cap) / tracker.width);
+                if (found && red[10] <= kSelectMax) med = __uint_as_float(red[5]);
+                else if (found) med = buffer_select(WIN, red[10], rank - red[11], tracker.lo, tracker.lo + tracker.width, whist, red);
+                else med = median_from_range();
+                med = uniform(med);
+                tracker.record(med);
+            }
+            h = uniform(bandwidth_from_median(2.f * med, n, a.bw_scale));
         }
         if (a.h_out && tid == 0 && gi == 0) a.h_out[(long)b * a.h_stride + it] = h;
         const float beta = uniform((float)kLog2e / h);
@@ -1447,279 +1585,191 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
         //   v_k = s_k - c2 x_k, c2 = 2 / h
         // (the kernel-gradient term of the update folded into the score
         // rows, so one contraction of kappa with [v, 1] gives both sums).
-        // The score rows become v in place; column kOne holds the 1.
         const float twob = 2.f * beta;
         const float c2 = 2.f / h;
-        constexpr int NG = D <= 3 ? 1 : 2;       // row groups of four in the sums
-        constexpr int kOne = NG == 1 ? 3 : 7;    // row that sums kappa
-        for (int k = tid; k < npad; k += nt) {
-            if (split && !COOP) {
-                // the score row of particle k from the splits' partial sums
-                // (rebased to their largest reference, summed in split order)
-                float srow[8];
+        smax = wave_max_abs((lane & 15) < nwaves ? redf[32 + (lane & 15)] : 0.f);
+        xmax = wave_max_abs((lane & 15) < nwaves ? redf[48 + (lane & 15)] : 0.f);
+        // B = [2 beta x_i, -2 beta], constant 14 - beta n_i: a tile holds the
+        // exponent -beta |x_k - x_i|^2 + 14 of kappa
+        auto stein_target = [&](const PieceRow<K4> &p, float (&v)[NC], float &cst) {
 #pragma unroll
-                for (int c = 0; c < 8; ++c) srow[c] = 0.f;
-                srow[7] = 1.f;
-                if (k < n) {
-                    float xt[D], xa[D], gr[D];
-#pragma unroll
-                    for (int c = 0; c < D; ++c) {
-                        xt[c] = X8[(long)k * 8 + c];
-                        xa[c] = xt[c] + ref[c];
-                    }
-                    F::grad(m, sz, mk, xa, gr);
-                    if (a.trans_mode == 0) {
-                        float mx = -inf;
-                        for (int sp = 0; sp < L.ns_sc; ++sp)
-                            mx = fmax_(mx, PART[((long)sp * ntasks * 64 + k) * kPartStride + 8]);
-                        float os[8];
-#pragma unroll
-                        for (int c = 0; c < 8; ++c) os[c] = 0.f;
-                        for (int sp = 0; sp < L.ns_sc; ++sp) {
-                            const float *pp = PART + ((long)sp * ntasks * 64 + k) * kPartStride;
-                            const float w = R::exp2_(pp[8] - mx);
-#pragma unroll
-                            for (int c = 0; c < 8; ++c) os[c] += pp[c] * w;
-                        }
-                        const float inv_sum = 1.f / os[7];
-#pragma unroll
-                        for (int c = 0; c < D; ++c) {
-                            const float mb = os[c] * inv_sum * 0.5f / rs[c];
-                            srow[c] = gr[c] - (xt[c] - mb) * m.inv_q[c];
-                        }
-                    } else {
-#pragma unroll
-                        for (int c = 0; c < D; ++c) srow[c] = gr[c] - (xt[c] - mbar_all[c]) * m.inv_q[c];
-                    }
-                }
-#pragma unroll
-                for (int c = 0; c < 8; ++c) S8[(long)k * 8 + c] = srow[c];
-            }
-#pragma unroll
-            for (int c = 0; c < D; ++c) S8[(long)k * 8 + c] -= c2 * X8[(long)k * 8 + c];
-            if (kOne != 7) S8[(long)k * 8 + kOne] = 1.f;
-        }
-        __syncthreads();
-        float phi[TS][kTilesPerWave][2];  // kept in registers until every wave is done
-        // source tiles [k0, k1) of this wave (split: its share of its task's)
-        const int sp_st = split ? wave / ntasks : 0;
-        const int k0 = split ? sp_st * nkt / L.ns_st : 0;
-        const int k1 = split ? (sp_st + 1) * nkt / L.ns_st : nkt;
+            for (int c = 0; c < NC; ++c) v[c] = c == kLast ? -twob : c < D ? twob * p.at(c) : 0.f;
+            const float half = p.at(kLast);
+            cst = kKapShift - (half < 0.5f * kPadHalfNorm ? twob * half : 0.f);
+        };
+        float v_scale, v_inv;
+        f16_scale(uniform(smax + c2 * xmax), v_scale, v_inv);
+        v_inv *= inv_n * 6.103515625e-05f;  // 2^-14 of kappa
+        const float k_inv = inv_n * 6.103515625e-05f;
 #pragma unroll
         for (int ts = 0; ts < TS; ++ts) {
-            const int task = split ? (ts == 0 && sp_st < L.ns_st ? wave % ntasks : ntasks) : wave + ts * nwaves;
-            if (task >= ntasks) break;
-            const int ibase = tbase + task * 64;
-            // B columns (2 beta x_i, -beta in K-row 7); the accumulator starts
-            // at -beta n_i, so a Gram tile holds the exponent
-            // -beta |x_k - x_i|^2 of kappa directly
-            float bi0[kTilesPerWave], bi1[kTilesPerWave];
-            f32x4 cb[kTilesPerWave];
-            // Sums on the 4x4x1 (16-block) MFMA straight from the Gram tile
-            // layout: register r of lane l holds kappa of source
-            // 16 kt + 4 (l / 16) + r and target 16 q + l % 16, so block
-            // b = l / 4 takes B = that register and A = rows 4 gg + l % 4 of
-            // v for its source; lane l of O4[gg][q] accumulates rows
-            // 4 gg + i (register i) of target 16 q + l % 16 over the source
-            // quarter l / 16, summed across quarters after the pass
-            f32x4 O4[NG][kTilesPerWave];
+            const int k = tid + ts * nt;
+            if (k >= npad) break;
+            PieceRow<K4> p;
+            p.load(smem, L.off_x, npad, k);
+            float v[NC];
 #pragma unroll
-            for (int q = 0; q < kTilesPerWave; ++q) {
-                const int ii = ibase + 16 * q + col;
-                bi0[q] = K4 && g == 3 ? -beta : twob * X8[(long)ii * 8 + g];
-                bi1[q] = g == 3 ? -beta : twob * X8[(long)ii * 8 + 4 + g];
-                const float nb = -beta * X8[(long)ii * 8 + 7];
-                cb[q] = f32x4{nb, nb, nb, nb};
+            for (int c = 0; c < NC; ++c) v[c] = 0.f;
+            if (k < n) {
 #pragma unroll
-                for (int gg = 0; gg < NG; ++gg) O4[gg][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int c = 0; c < D; ++c) v[c] = (srow[ts][c] - c2 * p.at(c)) * v_scale;
+                v[kLast] = 1.f;
             }
-            const float *vbase = S8 + (long)(4 * g) * 8 + (lane & 3);
-            // Gram tiles: A rows (x_k, n_k in the last K-row)
-            const int ka = gram_col<K4>(g);
-            auto gram = [&](int kt, f32x4 (&Go)[kTilesPerWave]) {
-                const float *xr = X8 + (long)(kt * 16 + col) * 8;
-                const float ak0 = xr[ka];
-#pragma unroll
-                for (int q = 0; q < kTilesPerWave; ++q) Go[q] = mfma16(ak0, bi0[q], cb[q]);
-                if (!K4) {
-                    const float ak1 = xr[4 + g];
-#pragma unroll
-                    for (int q = 0; q < kTilesPerWave; ++q) Go[q] = mfma16(ak1, bi1[q], Go[q]);
-                }
-            };
-            // one source tile: the Gram tiles of kt + 1 are issued before the
-            // exponentials of tile kt (the last tile repeats, unused); the two
-            // buffers alternate
-            auto tile = [&](int kt, f32x4 (&G)[kTilesPerWave], f32x4 (&Gn)[kTilesPerWave]) {
-                const float *vb = vbase + (long)(kt * 16) * 8;
-                float av[4][NG];
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-#pragma unroll
-                    for (int gg = 0; gg < NG; ++gg) av[r][gg] = vb[r * 8 + 4 * gg];
-                gram(min(kt + 1, k1 - 1), Gn);
-#pragma unroll
-                for (int q = 0; q < kTilesPerWave; ++q)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) G[q][r] = R::exp2_(G[q][r]);
-                // independent accumulators back to back
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-#pragma unroll
-                    for (int q = 0; q < kTilesPerWave; ++q)
-#pragma unroll
-                        for (int gg = 0; gg < NG; ++gg)
-                            O4[gg][q] = __builtin_amdgcn_mfma_f32_4x4x1f32(av[r][gg], G[q][r], O4[gg][q], 0, 0, 0);
-            };
-            f32x4 GA[kTilesPerWave], GB[kTilesPerWave];
-            gram(k0, GA);
-            for (int kt = k0; kt < k1; kt += 2) {
-                if (kBalance) bal.step();
-                tile(kt, GA, GB);
-                if (kt + 1 < k1) tile(kt + 1, GB, GA);
-            }
-            // lane (col, g): target ibase + 16 q + col, coordinates g, 4 + g
-#pragma unroll
-            for (int q = 0; q < kTilesPerWave; ++q) {
-                const int ii = ibase + 16 * q + col;
-                const float ksum = sum_row_quarters(O4[NG - 1][q][kOne - 4 * (NG - 1)]);
-                float *pp = PART + ((long)sp_st * ntasks * 64 + (ii - tbase)) * kPartStride;
-                if (split && g == 0) pp[8] = ksum;
-#pragma unroll
-                for (int h2 = 0; h2 < 2; ++h2) {
-                    const int c = g + 4 * h2;
-                    float v = 0.f;
-                    if (h2 < NG) {
-                        // row c = 4 h2 + g: register g of the lane's row
-                        const f32x4 &o = O4[h2 < NG ? h2 : 0][q];
-                        const float sv = sum_quarters_scatter(o[0], o[1], o[2], o[3]);
-                        if (split) {
-                            if (c < D) pp[c] = sv;
-                        } else if (c < D) {
-                            v = (sv + c2 * X8[(long)ii * 8 + c] * ksum) * inv_n;
-                        }
-                    }
-                    phi[ts][q][h2] = v;
-                }
-            }
-        }
-        __builtin_amdgcn_s_setprio(0);
-        __syncthreads();
-        // the window histogram starts the next walk at zero (the barrier at
-        // the end of the iteration orders this before it)
-        for (int q = tid; q < 256; q += nt) whist[q] = 0;
-        if (split) {
-            // synchronous update from the splits' partial sums (split order):
-            // the sums per (target, row) into S8 (dead after the Stein pass),
-            // then per target the update and the squared norm of the moved
-            // particle (the workgroup's targets; in COOP also to the exchange
-            // area)
-            const int ntl = ntasks * 64;
-            for (int e = tid; e < ntl * 8; e += nt) {
-                const int il = e >> 3, c = e & 7;
-                const int cc = c < D ? c : 8;  // row 7 (or the first unused one) carries the kernel sum
-                if (c < D || c == 7) {
-                    float acc = 0.f;
-                    for (int sp = 0; sp < L.ns_st; ++sp) acc += PART[((long)sp * ntl + il) * kPartStride + cc];
-                    S8[(long)(tbase + il) * 8 + c] = acc;
-                }
-            }
-            __syncthreads();
-            for (int il = tid; il < ntl; il += nt) {
-                const int i = tbase + il;
-                if (i >= n) continue;
-                const float ks = S8[(long)i * 8 + 7];
-                float nrm = 0.f;
-#pragma unroll
-                for (int c = 0; c < D; ++c) {
-                    const float xc = X8[(long)i * 8 + c];
-                    const float v = xc + a.step * ((S8[(long)i * 8 + c] + c2 * xc * ks) * inv_n);
-                    X8[(long)i * 8 + c] = v;
-                    nrm += v * v;
-                }
-                X8[(long)i * 8 + 7] = nrm;
-                if (COOP)
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) cX[(long)i * 8 + c] = X8[(long)i * 8 + c];
-            }
-        }
-        // synchronous update, then unscaled squared norms for the next median
-#pragma unroll
-        for (int ts = 0; ts < TS; ++ts) {
-            const int task = wave + ts * nwaves;
-            if (split || task >= ntasks) break;
-#pragma unroll
-            for (int q = 0; q < kTilesPerWave; ++q) {
-                const int ii = task * 64 + 16 * q + col;
-                if (ii < n) {
-#pragma unroll
-                    for (int h2 = 0; h2 < 2; ++h2) {
-                        const int c = g + 4 * h2;
-                        if (c < D) X8[(long)ii * 8 + c] += a.step * phi[ts][q][h2];
-                    }
-                }
-            }
-        }
-        // a wave's particles were written by its own lanes only
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-        for (int ts = 0; ts < TS; ++ts) {
-            const int task = wave + ts * nwaves;
-            if (split || task >= ntasks) break;
-            const int i = task * 64 + lane;
-            if (i < n) {
-                float nrm = 0.f;
-#pragma unroll
-                for (int c = 0; c < D; ++c) { const float v = X8[(long)i * 8 + c]; nrm += v * v; }
-                X8[(long)i * 8 + 7] = nrm;
+            put_sum_row<K4>(smem, L.off_v, k, v);
+            if (SPLIT && L.b_table && k >= tbase && k < tbase + ntl) {
+                float cst;
+                stein_target(p, v, cst);
+                put_target<K4>(smem, L.off_b, ntl, k - tbase, v, cst);
             }
         }
         __syncthreads();
+        if (tid < 2) red[10 + tid] = 0;  // the next walk's counters (past the last read)
+        // sums over the source blocks [blk0, blk1) for the targets of a task
+        auto stein_sums = [&](int ibase, int blk0, int blk1, float (&so)[NC]) {
+            const int lane = fresh_tid() & 63, g = lane >> 4, col = lane & 15;
+            u32x4 b0[QT], b1[QT];
+            f32x4 O[QT];
+            SourceRows<K4> src;
+            src.init(L.off_x, npad, L.off_ones, g, col);
+#pragma unroll
+            for (int q = 0; q < QT; ++q) {
+                b1[q] = u32x4{0u, 0u, 0u, 0u};
+                if (SPLIT && L.b_table) {
+                    load_target<K4>(smem, L.off_b, ntl, ibase - tbase + 16 * q + col, g, b0[q], b1[q]);
+                } else {
+                    PieceRow<K4> p;
+                    p.load(smem, L.off_x, npad, ibase + 16 * q + col);
+                    float v[NC], cst;
+                    stein_target(p, v, cst);
+                    target_row(v, cst, g, b0[q], b1[q]);
+                }
+            }
+            weighted_sums(src, L.off_v, b0, b1, blk0, blk1, O);
+            collect_rows<K4, QT>(O, so);
+        };
+        // the moved particle and half its squared norm
+        auto move = [&](int i, const float *so, float (&xn)[NC]) {
+            PieceRow<K4> p;
+            p.load(smem, L.off_x, npad, i);
+            float nrm = 0.f;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) xn[c] = 0.f;
+#pragma unroll
+            for (int c = 0; c < D; ++c) {
+                const float xc = p.at(c);
+                const float v = xc + a.step * (so[c] * v_inv + c2 * xc * (so[kLast] * k_inv));
+                xn[c] = v;
+                nrm += v * v;
+            }
+            xn[kLast] = 0.5f * nrm;
+        };
+        float so[TS][NC];
+        if constexpr (SPLIT) {
+            const int nb = npad / 32;
+            if (sp < L.ns_st)
+                stein_sums(tbase + wave % ntasks * kTask, sp * nb / L.ns_st, (sp + 1) * nb / L.ns_st, so[0]);
+            if (COOP) __syncthreads();
+            if (sp < L.ns_st && lane < kTask) {
+                float *pp = PART + ((long)sp * ntl + wave % ntasks * kTask + lane) * kPart;
+#pragma unroll
+                for (int c = 0; c < NC; ++c) pp[c] = so[0][c];
+            }
+        } else {
+#pragma unroll
+            for (int ts = 0; ts < TS; ++ts) {
+                const int task = wave + ts * nwaves;
+                if (task >= ntasks) break;
+                stein_sums(task * kTask, 0, npad / 32, so[ts]);
+            }
+        }
+        __syncthreads();
+        // synchronous update: every thread its particles (SPLIT: the first
+        // threads, from the splits' partial sums)
+#pragma unroll
+        for (int ts = 0; ts < TS; ++ts) {
+            const int il = tid + ts * nt;
+            const int i = tbase + il;
+            if (il >= ntl) break;
+            if (SPLIT && L.b_table && i >= n) {
+                // (a pad's Stein operand makes way for its score operand)
+                const float none[NC] = {};
+                put_score_target(i, none);
+            }
+            if (i >= n) break;
+            if (SPLIT) merge_part(il, L.ns_st, false, so[ts]);
+            float xn[NC];
+            move(i, so[ts], xn);
+            put_score_target(i, xn);
+            if constexpr (COOP) {
+#pragma unroll
+                for (int c = 0; c < NC; ++c) cX[(long)i * 8 + c] = xn[c];
+            } else {
+                put_row<K4>(smem, L.off_x, npad, i, xn);
+            }
+        }
         if constexpr (COOP) {
             // every workgroup's moved particles
             coop_barrier(cctr, ++epoch * (uint32_t)G, a.status);
-            for (int i = tid; i < n; i += nt)
+            if (tid < n) {
+                float xn[NC];
 #pragma unroll
-                for (int c = 0; c < 8; ++c) X8[(long)i * 8 + c] = cX[(long)i * 8 + c];
-            __syncthreads();
+                for (int c = 0; c < NC; ++c) xn[c] = cX[(long)tid * 8 + c];
+                put_row<K4>(smem, L.off_x, npad, tid, xn);
+            }
         }
+        // the sums' tables share their region where LDS is short
+        if (L.ms_shared) build_ms();
+        __syncthreads();
     }
 
     bool bad = false;
-    const int i_lo = COOP ? tbase : 0, i_hi = COOP ? min(n, tbase + ntasks * 64) : n;
+    const int i_lo = COOP ? tbase : 0, i_hi = COOP ? min(n, tbase + ntl) : n;
     for (int i = i_lo + tid; a.do_svgd && i < i_hi; i += nt) {
+        PieceRow<K4> p;
+        p.load(smem, L.off_x, npad, i);
 #pragma unroll
         for (int c = 0; c < D; ++c) {
-            const float v = X8[(long)i * 8 + c] + ref[c];
+            const float v = p.at(c) + ref[c];
             bad |= !R::finite(v);
             xg[(long)i * D + c] = v;
         }
     }
 
     if (a.do_viterbi) {
-        for (int j = tid; j < np; j += nt) PHP[j] = a.phi_prev ? a.phi_prev[(long)b * a.phi_prev_stride + j] : 0.f;
+        // rows [mh_j, phi_{t-1}(j)] over the sums' table (dead by now)
+        float *VF = (float *)(smem + L.off_ms);
+        for (int j = tid; j < np; j += nt) {
+            PieceRow<K4> p;
+            p.load(smem, L.off_vt, nppad, j);
+#pragma unroll
+            for (int c = 0; c < kLast; ++c) VF[(long)j * NC + c] = 0.5f * p.at(c);
+            VF[(long)j * NC + kLast] = a.phi_prev ? a.phi_prev[(long)b * a.phi_prev_stride + j] : 0.f;
+        }
         __syncthreads();
         for (int i = i_lo + tid; i < i_hi; i += nt) {
             float xs[D], xa[D];
+            PieceRow<K4> p;
+            p.load(smem, L.off_x, npad, i);
 #pragma unroll
             for (int c = 0; c < D; ++c) {
-                const float xt = X8[(long)i * 8 + c];
+                const float xt = p.at(c);
                 xs[c] = xt * rs[c];
                 xa[c] = xt + ref[c];
             }
             ArgBest<float> ab{-inf, -inf, 0};
             bool nan_seen = false;
             for (int j = 0; j < np; ++j) {
+                float mj[NC];
+#pragma unroll
+                for (int c = 0; c < NC; ++c) mj[c] = VF[(long)j * NC + c];
                 float q2 = 0.f;
 #pragma unroll
                 for (int c = 0; c < D; ++c) {
-                    const float r = xs[c] - 0.5f * VT[(long)c * nppad + j];
+                    const float r = xs[c] - mj[c];
                     q2 += r * r;
                 }
                 const float A = m.log_z - (float)kLn2 * q2;
-                const float cij = A + PHP[j];
+                const float cij = A + mj[kLast];
                 nan_seen |= (cij != cij);
                 if (j == 0) { ab.best = cij; ab.arg = 0; }
                 else argbest_push(ab, cij, j);
