@@ -106,6 +106,11 @@ template <typename T> DevModel<T> make_dev_model(const smsq_model_desc_t &d)
     m.log_z = (T)(-0.5 * lz);
     for (int c = 0; c < 64; ++c) m.p[c] = (T)d.params[c];
     if (d.kind == SMSQ_MODEL_RANGE2D) m.aux[0] = (T)(1.0 / d.params[0]);
+    if (d.kind == SMSQ_MODEL_CV4D) {
+        m.aux[0] = (T)(1.0 / d.params[1]);
+        m.aux[1] = (T)std::log((1.0 - d.params[2]) / d.params[3]);
+        m.aux[2] = (T)std::log(d.params[2] / (2.0 * kPi * d.params[1]));
+    }
     if (d.kind == SMSQ_MODEL_ARM7 || d.kind == SMSQ_MODEL_ARM14)
         for (int i = 0; i < 7; ++i) {
             m.aux[i] = (T)std::cos(d.params[8 + i]);

@@ -958,6 +958,10 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
 #pragma unroll
     for (int c = 0; c < 8; ++c) rs[c] = c < D ? m.rs[c] : 0.f;
 
+    float half_irs[D];   // 2 mh back to the state's units
+#pragma unroll
+    for (int c = 0; c < D; ++c) half_irs[c] = uniform(0.5f / rs[c]);
+
     // reference point: mean of the transition means
     float ref[D];
     for (int c = 0; c < D; ++c) {
@@ -1077,7 +1081,7 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
             for (int j = tid; j < np; j += nt) {
                 PieceRow<K4> p;
                 p.load(smem, L.off_vt, nppad, j);
-                part += p.at(c) * 0.5f / rs[c];
+                part += p.at(c) * half_irs[c];
             }
             part = wave_sum(part);
             if (lane == 0) redf[wave] = part;
@@ -1276,7 +1280,7 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
             const float inv_sum = ms_inv / os[kLast];
 #pragma unroll
             for (int c = 0; c < D; ++c) {
-                const float mb = os[c] * inv_sum * 0.5f / rs[c];
+                const float mb = os[c] * inv_sum * half_irs[c];
                 s[c] -= (xt[c] - mb) * m.inv_q[c];
             }
         } else {
@@ -1490,7 +1494,7 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
                 const int task = wave + ts * nwaves;
                 if (task >= ntasks) break;
                 if (a.trans_mode == 0) score_sums(task * kTask, 0, nppad / 32, negref[ts], os, sref);
-                const int k = task * kTask + lane;
+                const int k = task * kTask + (fresh_tid() & 63);
                 if (k < n) {
                     float xt[D];
                     score_grad(k, srow[ts], xt);
@@ -1521,10 +1525,11 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
         // the splits
         if (found && red[10] <= kSelectMax && wave == nwaves - 1) select_by_wave();
         if constexpr (SPLIT) {
-            if (tid < ntl && tbase + tid < n) {
-                if (a.trans_mode == 0) merge_part(tid, L.ns_sc, true, os);
+            const int il = fresh_tid();
+            if (il < ntl && tbase + il < n) {
+                if (a.trans_mode == 0) merge_part(il, L.ns_sc, true, os);
                 float xt[D];
-                score_grad(tbase + tid, srow[0], xt);
+                score_grad(tbase + il, srow[0], xt);
                 score_transition(os, xt, srow[0]);
                 if (!COOP) note_max(srow[0], xt);
             }
@@ -1603,7 +1608,7 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
         const float k_inv = inv_n * 6.103515625e-05f;
 #pragma unroll
         for (int ts = 0; ts < TS; ++ts) {
-            const int k = tid + ts * nt;
+            const int k = fresh_tid() + ts * nt;
             if (k >= npad) break;
             PieceRow<K4> p;
             p.load(smem, L.off_x, npad, k);
@@ -1687,7 +1692,7 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
         // threads, from the splits' partial sums)
 #pragma unroll
         for (int ts = 0; ts < TS; ++ts) {
-            const int il = tid + ts * nt;
+            const int il = fresh_tid() + ts * nt;
             const int i = tbase + il;
             if (il >= ntl) break;
             if (SPLIT && L.b_table && i >= n) {

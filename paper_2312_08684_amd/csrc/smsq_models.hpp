@@ -19,7 +19,8 @@ template <typename T> struct DevModel {
     T rs[16];      // sqrt(log2(e) / (2 q)): x * rs puts -(x-m)^2/(2q) in log2 units
     T log_z;       // -1/2 sum_d log(2 pi q_d)
     T p[64];       // family parameters
-    T aux[16];     // family constants (RANGE2D: 1/r_var; ARM7: cos alpha_i, sin alpha_i;
+    T aux[16];     // family constants (RANGE2D: 1/r_var; CV4D: 1/r_var, log((1-P_D)/V),
+                   // log(P_D / (2 pi r_var)); ARM7: cos alpha_i, sin alpha_i;
                    // SE2: 1/r_var, 1/b_var, log-density constant of one landmark)
     double grow[3]; // GROWTH1D cosine term c, omega, phase; ARM14 input amplitude,
                     // frequency, phase step (kept in double)
@@ -87,8 +88,11 @@ template <typename T> struct Family<T, RANGE2D, 2> {
 
 // ---------------------------------------------------------------------------
 // Detection / clutter mixture: p(Z|x) = V^-(M-1) [(1-P_D)/V + (P_D/M) sum_m
-// N(z_m; (px,py), r I)].  Evaluated as a running-max log-sum-exp over the
-// clutter term and the M detection terms.
+// N(z_m; (px,py), r I)].  Evaluated as a log-sum-exp over the clutter term and
+// the M detection terms: the largest term first, then the sums, so that the
+// detections do not wait for one another (a running maximum with a rescaling
+// branch per detection took the gradients of 512 particles 13,800 cycles of
+// an iteration's 120,000).
 template <typename T> struct Family<T, CV4D, 4> {
     static __device__ void mean(const DevModel<T> &m, int, const T *x, T *out)
     {
@@ -103,32 +107,34 @@ template <typename T> struct Family<T, CV4D, 4> {
         for (int k = 0; k < m.n_obs; ++k) M += (mask == nullptr || mask[k]) ? 1 : 0;
         return M;
     }
-    // Running log-sum-exp: returns (mx, s) with log sum = mx + log s, and the
-    // responsibility-weighted residual sums gx, gy (scaled like s).
+    // log sum = mx + log s, and the responsibility-weighted residual sums gx,
+    // gy (scaled like s).  aux: 1 / r, log((1-P_D)/V), log(P_D / (2 pi r)).
     static __device__ void accumulate(const DevModel<T> &m, const T *z, const uint8_t *mask, const T *x,
                                       int M, T &mx, T &s, T &gx, T &gy)
     {
-        const T rv = m.p[1], pd = m.p[2], V = m.p[3];
-        mx = RealOps<T>::log_(((T)1 - pd) / V);
-        s = (T)1;
-        gx = gy = (T)0;
-        const T ldet = RealOps<T>::log_(pd / (T)M) - RealOps<T>::log_((T)(2.0 * kPi) * rv);
+        const T w = (T)0.5 * m.aux[0], ldet = m.aux[2] - RealOps<T>::log_((T)M);
+        mx = m.aux[1];
+#pragma unroll 4
         for (int k = 0; k < m.n_obs; ++k) {
-            if (mask && !mask[k]) continue;
             const T ex = z[2 * k] - x[0], ey = z[2 * k + 1] - x[1];
-            const T v = ldet - (T)0.5 * (ex * ex + ey * ey) / rv;
-            if (v > mx) {
-                const T sf = RealOps<T>::exp_(mx - v);
-                s = s * sf + (T)1;
-                gx = gx * sf + ex;
-                gy = gy * sf + ey;
-                mx = v;
-            } else {
-                const T e = RealOps<T>::exp_(v - mx);
-                s += e;
-                gx += e * ex;
-                gy += e * ey;
+            T v = ldet - w * (ex * ex + ey * ey);
+            if (mask) v = mask[k] ? v : -RealOps<T>::inf();
+            mx = v > mx ? v : mx;
+        }
+        s = RealOps<T>::exp_(m.aux[1] - mx);
+        gx = gy = (T)0;
+#pragma unroll 4
+        for (int k = 0; k < m.n_obs; ++k) {
+            T ex = z[2 * k] - x[0], ey = z[2 * k + 1] - x[1];
+            T v = ldet - w * (ex * ex + ey * ey);
+            if (mask && !mask[k]) {  // (a dropped detection may hold anything)
+                v = -RealOps<T>::inf();
+                ex = ey = (T)0;
             }
+            const T e = RealOps<T>::exp_(v - mx);
+            s += e;
+            gx += e * ex;
+            gy += e * ey;
         }
     }
     static __device__ T loglik(const DevModel<T> &m, const T *z, const uint8_t *mask, const T *x)
@@ -146,7 +152,7 @@ template <typename T> struct Family<T, CV4D, 4> {
         if (M == 0) return;
         T mx, s, gx, gy;
         accumulate(m, z, mask, x, M, mx, s, gx, gy);
-        const T sc = (T)1 / (s * m.p[1]);
+        const T sc = m.aux[0] / s;
         g[0] = gx * sc;
         g[1] = gy * sc;
     }
@@ -155,59 +161,42 @@ template <typename T> struct Family<T, CV4D, 4> {
 // ---------------------------------------------------------------------------
 // Standard-DH 7-joint chain; the gradient is J^T (z - p) / r with the
 // geometric Jacobian column z_{i-1} x (p - o_{i-1}) of each revolute joint.
-// Two forward sweeps: the first finds the end-effector position p, the
-// second rebuilds each frame (from the cached sines / cosines) and
-// accumulates the Jacobian-transpose product, so no frame is stored.
+// No frame is built: going back from the end effector, v_{i-1} = A_i v_i is
+// the vector p - o_{i-1} in the coordinates of frame i-1 (v_7 = 0, p = v_0);
+// going forward, the residual e turns into each frame by the transpose of its
+// rotation, and the joint's gradient there is (z x v) . e = v_x e_y - v_y e_x.
+// 10 + 8 operations a joint; two sweeps over the frames themselves (rotation
+// matrices and origins) took 75 a joint, and the gradients of 1024 particles
+// 12% of an iteration of the matrix-core step.
 template <typename T> struct Family<T, ARM7, 7> {
     static __device__ void mean(const DevModel<T> &, int, const T *x, T *out)
     {
 #pragma unroll
         for (int a = 0; a < 7; ++a) out[a] = x[a];
     }
-    struct Frame {
-        T R00, R01, R02, R10, R11, R12, R20, R21, R22, o0, o1, o2;
-        __device__ void reset()
-        {
-            R00 = 1; R01 = 0; R02 = 0; R10 = 0; R11 = 1; R12 = 0; R20 = 0; R21 = 0; R22 = 1;
-            o0 = o1 = o2 = 0;
-        }
-        // frame <- frame * A_i with A_i = Rz(q) Tz(dd) Tx(a) Rx(alpha)
-        __device__ void advance(T ct, T st, T ca, T sa, T a, T dd)
-        {
-            const T A00 = ct, A01 = -st * ca, A02 = st * sa;
-            const T A10 = st, A11 = ct * ca, A12 = -ct * sa;
-            const T A21 = sa, A22 = ca;
-            const T t0 = a * ct, t1 = a * st, t2 = dd;
-            o0 += R00 * t0 + R01 * t1 + R02 * t2;
-            o1 += R10 * t0 + R11 * t1 + R12 * t2;
-            o2 += R20 * t0 + R21 * t1 + R22 * t2;
-            const T n00 = R00 * A00 + R01 * A10, n01 = R00 * A01 + R01 * A11 + R02 * A21,
-                    n02 = R00 * A02 + R01 * A12 + R02 * A22;
-            const T n10 = R10 * A00 + R11 * A10, n11 = R10 * A01 + R11 * A11 + R12 * A21,
-                    n12 = R10 * A02 + R11 * A12 + R12 * A22;
-            const T n20 = R20 * A00 + R21 * A10, n21 = R20 * A01 + R21 * A11 + R22 * A21,
-                    n22 = R20 * A02 + R21 * A12 + R22 * A22;
-            R00 = n00; R01 = n01; R02 = n02;
-            R10 = n10; R11 = n11; R12 = n12;
-            R20 = n20; R21 = n21; R22 = n22;
-        }
-    };
-    static __device__ void end_effector(const DevModel<T> &m, const T *q, T *st, T *ct, T *p)
+    // v_{i-1} (x, y parts in vx, vy if wanted) of every joint, with
+    // A_i = Rz(q_i) Tz(d_i) Tx(a_i) Rx(alpha_i); p = v_0
+    static __device__ void end_effector(const DevModel<T> &m, const T *q, T *st, T *ct, T *vx, T *vy, T *p)
     {
-        Frame f;
-        f.reset();
+        T x = 0, y = 0, w = 0;
 #pragma unroll
-        for (int i = 0; i < 7; ++i) {
+        for (int i = 6; i >= 0; --i) {
+            const T ca = m.aux[i], sa = m.aux[7 + i];
             RealOps<T>::sincos_(q[i], &st[i], &ct[i]);
-            f.advance(ct[i], st[i], m.aux[i], m.aux[7 + i], m.p[1 + i], m.p[15 + i]);
+            const T ux = x + m.p[1 + i], uy = ca * y - sa * w, uz = sa * y + ca * w;
+            x = ct[i] * ux - st[i] * uy;
+            y = st[i] * ux + ct[i] * uy;
+            w = uz + m.p[15 + i];
+            vx[i] = x;
+            vy[i] = y;
         }
-        p[0] = f.o0; p[1] = f.o1; p[2] = f.o2;
+        p[0] = x; p[1] = y; p[2] = w;
     }
     static __device__ T loglik(const DevModel<T> &m, const T *z, const uint8_t *mask, const T *x)
     {
         if (mask && !mask[0]) return (T)0;
-        T st[7], ct[7], p[3];
-        end_effector(m, x, st, ct, p);
+        T st[7], ct[7], vx[7], vy[7], p[3];
+        end_effector(m, x, st, ct, vx, vy, p);
         const T e0 = z[0] - p[0], e1 = z[1] - p[1], e2 = z[2] - p[2];
         return (T)-0.5 * (e0 * e0 + e1 * e1 + e2 * e2) / m.p[0]
                - (T)1.5 * RealOps<T>::log_((T)(2.0 * kPi) * m.p[0]);
@@ -217,22 +206,18 @@ template <typename T> struct Family<T, ARM7, 7> {
 #pragma unroll
         for (int a = 0; a < 7; ++a) g[a] = (T)0;
         if (mask && !mask[0]) return;
-        T st[7], ct[7], p[3];
-        end_effector(m, x, st, ct, p);
+        T st[7], ct[7], vx[7], vy[7], p[3];
+        end_effector(m, x, st, ct, vx, vy, p);
         const T ir = (T)1 / m.p[0];
-        const T e0 = (z[0] - p[0]) * ir, e1 = (z[1] - p[1]) * ir, e2 = (z[2] - p[2]) * ir;
-        Frame f;
-        f.reset();
+        T e0 = (z[0] - p[0]) * ir, e1 = (z[1] - p[1]) * ir, e2 = (z[2] - p[2]) * ir;
 #pragma unroll
         for (int i = 0; i < 7; ++i) {
-            // joint i+1 turns about the z axis of frame i through its origin
-            const T v0 = p[0] - f.o0, v1 = p[1] - f.o1, v2 = p[2] - f.o2;
-            const T z0 = f.R02, z1 = f.R12, z2 = f.R22;
-            const T c0 = z1 * v2 - z2 * v1;
-            const T c1 = z2 * v0 - z0 * v2;
-            const T c2 = z0 * v1 - z1 * v0;
-            g[i] = c0 * e0 + c1 * e1 + c2 * e2;
-            f.advance(ct[i], st[i], m.aux[i], m.aux[7 + i], m.p[1 + i], m.p[15 + i]);
+            g[i] = vx[i] * e1 - vy[i] * e0;
+            const T ca = m.aux[i], sa = m.aux[7 + i];
+            const T f0 = ct[i] * e0 + st[i] * e1, f1 = ct[i] * e1 - st[i] * e0;
+            e0 = f0;
+            e1 = ca * f1 + sa * e2;
+            e2 = ca * e2 - sa * f1;
         }
     }
 };
