@@ -195,7 +195,7 @@ constexpr float kPadHalfNorm = 8.507059173023462e37f;  // 2^126
 // The two sums' tables share one region where LDS is short (1024 particles of
 // d >= 4): the transition one is then rebuilt each iteration.
 struct MfmaLds {
-    long off_x, off_vt, off_v, off_ms, off_b, off_win, off_z, off_mask, off_red, off_ones, off_part, total;
+    long off_x, off_vt, off_v, off_ms, off_b, off_win, off_z, off_red, off_ones, off_part, total;
     int npad, nppad, nwaves, task, ntasks, ns_sc, ns_st, ns_max, win_cap;
     bool split, ms_shared, b_table;
     __host__ __device__ MfmaLds(bool k4, int n, int n_prev, int waves = kMaxWaves, int targets_local = 0)
@@ -224,7 +224,7 @@ struct MfmaLds {
         const long vb = (long)npad * 2 * row, mb = (long)nppad * 2 * row;
         // target operands: four planes (k4: three) of 16 bytes per target
         const long bb = (long)targets * (k4 ? 48 : 64);
-        const long fixed = 3 * row * (npad + nppad) + 128 + 64 + 512 + 16 + (alias ? 0 : part) + 1024;
+        const long fixed = 3 * row * (npad + nppad) + 128 + 512 + 16 + (alias ? 0 : part) + 1024;
         // what fits, in the order of what it saves: target operands in a table
         // (several waves share each task), the sums' tables apart (else the
         // transition one is rebuilt each iteration), a window buffer of 4096
@@ -249,7 +249,6 @@ struct MfmaLds {
         off_b = o; o += b_table ? bb : 0;
         off_win = o; o += 4L * win_cap + 1024;  // window buffer, bins of its selection
         off_z = o; o += 128;
-        off_mask = o; o += 64;
         off_red = o; o += 512;  // uint slots 0..63, float slots from byte 256
         off_ones = o; o += 16;
         total = o;
@@ -742,7 +741,8 @@ struct MedianTracker {
     {
         if (have == 0 || !(med1 > 0.f)) return false;
         const float move = fabsf(med1 - med2);
-        float w = density > 0.f ? 0.5f * (float)kWinTarget / density : 1e-3f * med1;
+        const float target = fminf((float)kWinTarget, fmaxf((float)(M / 64), 32.f));
+        float w = density > 0.f ? 0.5f * target / density : 1e-3f * med1;
         pred = have >= 2 ? med1 + (med1 - med2) : med1;
         // one median: as wide as the buffer holds (at the densest, 0.7 of the
         // pairs per unit of relative distance), up to a hundredth
@@ -889,6 +889,12 @@ __device__ __forceinline__ void coop_barrier(uint32_t *ctr, uint32_t target, uin
     }
     __syncthreads();
 }
+// Step arguments in the constant address space (a kernel's own arguments, or a
+// plan's items, which an earlier launch wrote): read by scalar loads where they
+// are used.  As ordinary references the compiler copied them to scratch and
+// read them lane by lane.
+using ConstStepArgs = const __attribute__((address_space(4))) StepArgs<float>;
+
 // SPLIT: the layout splits the sources of each task among waves (MfmaLds
 // split); a separate instantiation, so the unsplit path keeps its
 // registers.  COOP (with SPLIT): one of the G workgroups of sequence b in
@@ -899,8 +905,9 @@ __device__ __forceinline__ void coop_barrier(uint32_t *ctr, uint32_t target, uin
 // from the score pass to the bandwidth, and moves them.  In the passes a wave
 // covers a task of 64 targets, one per lane once its sums are collected.
 template <int KIND, int D, int TS, bool SPLIT, bool COOP = false>
-__device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const int b, const CoopArgs cx = CoopArgs{})
+__device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const int b, const CoopArgs cx = CoopArgs{})
 {
+    const StepArgs<float> &a = *(const StepArgs<float> *)ap;
     using F = Family<float, KIND, D>;
     using R = RealOps<float>;
     static_assert(D <= 7, "component 7 carries the norms");
@@ -934,7 +941,6 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
     float *WIN = (float *)(smem + L.off_win);                    // median window buffer, radix histogram
     uint32_t *whist = (uint32_t *)(smem + L.off_win) + L.win_cap;  // 256 bins of buffer_select
     float *sz = (float *)(smem + L.off_z);
-    uint8_t *smask = smem + L.off_mask;
     uint32_t *red = (uint32_t *)(smem + L.off_red);
     float *redf = (float *)(smem + L.off_red + 256);
 
@@ -949,11 +955,9 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
 
     if (tid == 0) *(u32x4 *)(smem + L.off_ones) = u32x4{0x3f803f80u, 0x3f80u, 0u, 0u};
     for (int o = tid; o < m.obs_dim; o += nt) sz[o] = a.z[(long)b * a.z_stride + o];
-    const uint8_t *mk = nullptr;
-    if (a.mask) {
-        for (int o = tid; o < m.n_obs; o += nt) smask[o] = a.mask[(long)b * a.mask_stride + o];
-        mk = smask;
-    }
+    static_assert(kMaxObs <= kWave, "one lane per element of an observation");
+    const bool on = lane < m.n_obs && (!a.mask || a.mask[(long)b * a.mask_stride + lane]);
+    const ObsBits mk{__builtin_amdgcn_ballot_w64(on)};
     float rs[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) rs[c] = c < D ? m.rs[c] : 0.f;
@@ -1114,6 +1118,12 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
         asm volatile("" : "+v"(t));
         return t;
     };
+    // The model, likewise: read again by scalar loads instead of held.
+    auto fresh_model = [&]() -> const DevModel<float> & {
+        ConstStepArgs *q = ap;
+        asm volatile("" : "+s"(q));
+        return ((const StepArgs<float> *)q)->m;
+    };
     constexpr uint32_t kSumBlock = 2 * NC * 64;
     // O[q] = the sums over the source blocks [blk0, blk1) of 2^(exponent) times
     // the rows of a sums' table (at byte `table`), for the 16-target
@@ -1262,20 +1272,22 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
         if (os[kLast] > 0.f && os[kLast] < 1e30f) nref += kRefShift - __builtin_amdgcn_logf(os[kLast]);
         else if (nref == 0.f) sref = kNoSource;  // nothing to merge
     };
-    // score row of particle k: the observation's gradient, then the transition
+    // score row of a particle: the observation's gradient, then the transition
     // term from its softmax sums
-    auto score_grad = [&](int k, float (&s)[D], float (&xt)[D]) {
+    auto target_x = [&](int k, float (&xt)[D]) {
         PieceRow<K4> p;
         p.load(smem, L.off_x, npad, k);
+#pragma unroll
+        for (int c = 0; c < D; ++c) xt[c] = p.at(c);
+    };
+    auto score_grad = [&](const float (&xt)[D], float (&s)[D]) {
         float xa[D];
 #pragma unroll
-        for (int c = 0; c < D; ++c) {
-            xt[c] = p.at(c);
-            xa[c] = xt[c] + ref[c];
-        }
-        F::grad(m, sz, mk, xa, s);
+        for (int c = 0; c < D; ++c) xa[c] = xt[c] + ref[c];
+        F::grad(fresh_model(), sz, mk, xa, s);
     };
     auto score_transition = [&](const float *os, const float (&xt)[D], float (&s)[D]) {
+        const DevModel<float> &m = fresh_model();
         if (a.trans_mode == 0) {
             const float inv_sum = ms_inv / os[kLast];
 #pragma unroll
@@ -1497,7 +1509,8 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
                 const int k = task * kTask + (fresh_tid() & 63);
                 if (k < n) {
                     float xt[D];
-                    score_grad(k, srow[ts], xt);
+                    target_x(k, xt);
+                    score_grad(xt, srow[ts]);
                     score_transition(os, xt, srow[ts]);
                     note_max(srow[ts], xt);
                 }
@@ -1529,7 +1542,8 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
             if (il < ntl && tbase + il < n) {
                 if (a.trans_mode == 0) merge_part(il, L.ns_sc, true, os);
                 float xt[D];
-                score_grad(tbase + il, srow[0], xt);
+                target_x(tbase + il, xt);
+                score_grad(xt, srow[0]);
                 score_transition(os, xt, srow[0]);
                 if (!COOP) note_max(srow[0], xt);
             }
@@ -1606,13 +1620,22 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
         f16_scale(uniform(smax + c2 * xmax), v_scale, v_inv);
         v_inv *= inv_n * 6.103515625e-05f;  // 2^-14 of kappa
         const float k_inv = inv_n * 6.103515625e-05f;
+        // (a workgroup that splits has two threads or more per particle: the
+        // second puts the target operands)
+        constexpr bool kOther = SPLIT && !COOP;
 #pragma unroll
         for (int ts = 0; ts < TS; ++ts) {
             const int k = fresh_tid() + ts * nt;
-            if (k >= npad) break;
             PieceRow<K4> p;
-            p.load(smem, L.off_x, npad, k);
             float v[NC];
+            if (kOther && L.b_table && k >= npad && k < 2 * npad) {
+                float cst;
+                p.load(smem, L.off_x, npad, k - npad);
+                stein_target(p, v, cst);
+                put_target<K4>(smem, L.off_b, ntl, k - npad, v, cst);
+            }
+            if (k >= npad) break;
+            p.load(smem, L.off_x, npad, k);
 #pragma unroll
             for (int c = 0; c < NC; ++c) v[c] = 0.f;
             if (k < n) {
@@ -1621,7 +1644,7 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
                 v[kLast] = 1.f;
             }
             put_sum_row<K4>(smem, L.off_v, k, v);
-            if (SPLIT && L.b_table && k >= tbase && k < tbase + ntl) {
+            if (SPLIT && !kOther && L.b_table && k >= tbase && k < tbase + ntl) {
                 float cst;
                 stein_target(p, v, cst);
                 put_target<K4>(smem, L.off_b, ntl, k - tbase, v, cst);
@@ -1689,14 +1712,29 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
         }
         __syncthreads();
         // synchronous update: every thread its particles (SPLIT: the first
-        // threads, from the splits' partial sums)
+        // threads, from the splits' partial sums; the next ones in line move
+        // the same particles for the score operands)
+        if constexpr (SPLIT && !COOP) {
+            const int il = fresh_tid(), i = il < ntl ? il : il - ntl;
+            const bool mine = i < n && (il < ntl || L.b_table);
+            float xn[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) xn[c] = 0.f;
+            if (mine) {
+                merge_part(i, L.ns_st, false, so[0]);
+                move(i, so[0], xn);
+            }
+            __syncthreads();
+            if (mine && il < ntl) put_row<K4>(smem, L.off_x, npad, i, xn);
+            // (a pad's Stein operand makes way for its score operand)
+            if (il >= ntl && i < ntl) put_score_target(i, xn);
+        } else
 #pragma unroll
         for (int ts = 0; ts < TS; ++ts) {
             const int il = fresh_tid() + ts * nt;
             const int i = tbase + il;
             if (il >= ntl) break;
             if (SPLIT && L.b_table && i >= n) {
-                // (a pad's Stein operand makes way for its score operand)
                 const float none[NC] = {};
                 put_score_target(i, none);
             }
@@ -1795,10 +1833,16 @@ __device__ __forceinline__ void step_mfma_body(const StepArgs<float> &a, const i
     if (bad) atomicOr(a.status, STATUS_NONFINITE);
 }
 
+// the step's arguments, the first of its kernel's
+__device__ __forceinline__ ConstStepArgs *kernel_args()
+{
+    return (ConstStepArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
 template <int KIND, int D, bool SPLIT>
 __global__ __launch_bounds__(kMaxWaves * 64) void k_step_mfma(StepArgs<float> a)
 {
-    step_mfma_body<KIND, D, kMaxParticles / 64 / kMaxWaves, SPLIT>(a, blockIdx.x);
+    step_mfma_body<KIND, D, kMaxParticles / 64 / kMaxWaves, SPLIT>(kernel_args(), blockIdx.x);
 }
 
 // Multi-workgroup step: workgroup blockIdx.x is group blockIdx.x % G of
@@ -1807,7 +1851,7 @@ template <int KIND, int D>
 __global__ __launch_bounds__(kMaxWaves * 64) void k_step_mfma_coop(StepArgs<float> a, CoopArgs c)
 {
     c.gi = (int)(blockIdx.x % (unsigned)c.G);
-    step_mfma_body<KIND, D, 1, true, true>(a, (int)(blockIdx.x / (unsigned)c.G), c);
+    step_mfma_body<KIND, D, 1, true, true>(kernel_args(), (int)(blockIdx.x / (unsigned)c.G), c);
 }
 
 } // namespace smsq

@@ -28,24 +28,40 @@ template <typename T> struct DevModel {
 
 template <typename T, int KIND, int D> struct Family;
 
+// The observed elements: as bits (a wave's uniform value, where a loop over
+// them needs no load or branch), or as a caller's byte array, which may be
+// null (all observed).
+struct ObsBits { uint64_t bits; };
+__device__ __forceinline__ bool observed(ObsBits mask, int k) { return (mask.bits >> k) & 1; }
+__device__ __forceinline__ bool observed(const uint8_t *mask, int k) { return mask == nullptr || mask[k]; }
+__device__ __forceinline__ int observed_count(ObsBits mask, int) { return __builtin_popcountll(mask.bits); }
+__device__ __forceinline__ int observed_count(const uint8_t *mask, int n)
+{
+    int M = 0;
+    for (int k = 0; k < n; ++k) M += observed(mask, k) ? 1 : 0;
+    return M;
+}
+
 // ---------------------------------------------------------------------------
 template <typename T> struct Family<T, GROWTH1D, 1> {
-    static __device__ void mean(const DevModel<T> &m, int t, const T *x, T *out)
+    static __device__ __forceinline__ void mean(const DevModel<T> &m, int t, const T *x, T *out)
     {
         const T v = x[0];
         const T c = (T)(m.grow[0] * cos(m.grow[1] * (double)t + m.grow[2]));
         out[0] = m.p[0] * v + m.p[1] * v / ((T)1 + v * v) + c;
     }
-    static __device__ T loglik(const DevModel<T> &m, const T *z, const uint8_t *mask, const T *x)
+    template <class Mask>
+    static __device__ __forceinline__ T loglik(const DevModel<T> &m, const T *z, Mask mask, const T *x)
     {
-        if (mask && !mask[0]) return (T)0;
+        if (!observed(mask, 0)) return (T)0;
         const T r = z[0] - m.p[5] * x[0] * x[0];
         return (T)-0.5 * r * r / m.p[6] - (T)0.5 * RealOps<T>::log_((T)(2.0 * kPi) * m.p[6]);
     }
-    static __device__ void grad(const DevModel<T> &m, const T *z, const uint8_t *mask, const T *x, T *g)
+    template <class Mask>
+    static __device__ __forceinline__ void grad(const DevModel<T> &m, const T *z, Mask mask, const T *x, T *g)
     {
         g[0] = (T)0;
-        if (mask && !mask[0]) return;
+        if (!observed(mask, 0)) return;
         const T r = z[0] - m.p[5] * x[0] * x[0];
         g[0] = r / m.p[6] * ((T)2 * m.p[5] * x[0]);
     }
@@ -53,35 +69,37 @@ template <typename T> struct Family<T, GROWTH1D, 1> {
 
 // ---------------------------------------------------------------------------
 template <typename T> struct Family<T, RANGE2D, 2> {
-    static __device__ void mean(const DevModel<T> &, int, const T *x, T *out)
+    static __device__ __forceinline__ void mean(const DevModel<T> &, int, const T *x, T *out)
     {
         out[0] = x[0];
         out[1] = x[1];
     }
-    static __device__ T loglik(const DevModel<T> &m, const T *z, const uint8_t *mask, const T *x)
+    template <class Mask>
+    static __device__ __forceinline__ T loglik(const DevModel<T> &m, const T *z, Mask mask, const T *x)
     {
         const int nb = m.n_obs;
         const T lc = (T)0.5 * RealOps<T>::log_((T)(2.0 * kPi) * m.p[0]);
         T s = 0;
         for (int b = 0; b < nb; ++b) {
-            if (mask && !mask[b]) continue;
+            if (!observed(mask, b)) continue;
             const T dx = x[0] - m.p[2 + 2 * b], dy = x[1] - m.p[3 + 2 * b];
             const T e = z[b] - RealOps<T>::sqrt_(dx * dx + dy * dy);
             s += (T)-0.5 * e * e / m.p[0] - lc;
         }
         return s;
     }
-    static __device__ void grad(const DevModel<T> &m, const T *z, const uint8_t *mask, const T *x, T *g)
+    template <class Mask>
+    static __device__ __forceinline__ void grad(const DevModel<T> &m, const T *z, Mask mask, const T *x, T *g)
     {
         g[0] = g[1] = (T)0;
+#pragma unroll 4
         for (int b = 0; b < m.n_obs; ++b) {
-            if (mask && !mask[b]) continue;
             const T dx = x[0] - m.p[2 + 2 * b], dy = x[1] - m.p[3 + 2 * b];
             const T r = RealOps<T>::sqrt_(dx * dx + dy * dy);
-            if (r < (T)1e-12) continue;
             const T w = (z[b] - r) * m.aux[0] / r;  // aux[0] = 1 / r_var
-            g[0] += w * dx;
-            g[1] += w * dy;
+            const bool skip = !observed(mask, b) || r < (T)1e-12;
+            g[0] += skip ? (T)0 : w * dx;
+            g[1] += skip ? (T)0 : w * dy;
         }
     }
 };
@@ -94,61 +112,53 @@ template <typename T> struct Family<T, RANGE2D, 2> {
 // branch per detection took the gradients of 512 particles 13,800 cycles of
 // an iteration's 120,000).
 template <typename T> struct Family<T, CV4D, 4> {
-    static __device__ void mean(const DevModel<T> &m, int, const T *x, T *out)
+    static __device__ __forceinline__ void mean(const DevModel<T> &m, int, const T *x, T *out)
     {
         out[0] = x[0] + m.p[0] * x[2];
         out[1] = x[1] + m.p[0] * x[3];
         out[2] = x[2];
         out[3] = x[3];
     }
-    static __device__ int count(const DevModel<T> &m, const uint8_t *mask)
-    {
-        int M = 0;
-        for (int k = 0; k < m.n_obs; ++k) M += (mask == nullptr || mask[k]) ? 1 : 0;
-        return M;
-    }
     // log sum = mx + log s, and the responsibility-weighted residual sums gx,
     // gy (scaled like s).  aux: 1 / r, log((1-P_D)/V), log(P_D / (2 pi r)).
-    static __device__ void accumulate(const DevModel<T> &m, const T *z, const uint8_t *mask, const T *x,
-                                      int M, T &mx, T &s, T &gx, T &gy)
+    template <class Mask>
+    static __device__ __forceinline__ void accumulate(const DevModel<T> &m, const T *z, Mask mask, const T *x,
+                                                      int M, T &mx, T &s, T &gx, T &gy)
     {
         const T w = (T)0.5 * m.aux[0], ldet = m.aux[2] - RealOps<T>::log_((T)M);
         mx = m.aux[1];
 #pragma unroll 4
         for (int k = 0; k < m.n_obs; ++k) {
             const T ex = z[2 * k] - x[0], ey = z[2 * k + 1] - x[1];
-            T v = ldet - w * (ex * ex + ey * ey);
-            if (mask) v = mask[k] ? v : -RealOps<T>::inf();
+            const T v = observed(mask, k) ? ldet - w * (ex * ex + ey * ey) : -RealOps<T>::inf();
             mx = v > mx ? v : mx;
         }
         s = RealOps<T>::exp_(m.aux[1] - mx);
         gx = gy = (T)0;
 #pragma unroll 4
         for (int k = 0; k < m.n_obs; ++k) {
-            T ex = z[2 * k] - x[0], ey = z[2 * k + 1] - x[1];
-            T v = ldet - w * (ex * ex + ey * ey);
-            if (mask && !mask[k]) {  // (a dropped detection may hold anything)
-                v = -RealOps<T>::inf();
-                ex = ey = (T)0;
-            }
-            const T e = RealOps<T>::exp_(v - mx);
+            const bool on = observed(mask, k);  // (a dropped detection may hold anything)
+            const T ex = on ? z[2 * k] - x[0] : (T)0, ey = on ? z[2 * k + 1] - x[1] : (T)0;
+            const T e = on ? RealOps<T>::exp_(ldet - w * (ex * ex + ey * ey) - mx) : (T)0;
             s += e;
             gx += e * ex;
             gy += e * ey;
         }
     }
-    static __device__ T loglik(const DevModel<T> &m, const T *z, const uint8_t *mask, const T *x)
+    template <class Mask>
+    static __device__ __forceinline__ T loglik(const DevModel<T> &m, const T *z, Mask mask, const T *x)
     {
-        const int M = count(m, mask);
+        const int M = observed_count(mask, m.n_obs);
         if (M == 0) return RealOps<T>::log_((T)1 - m.p[2]);
         T mx, s, gx, gy;
         accumulate(m, z, mask, x, M, mx, s, gx, gy);
         return -(T)(M - 1) * RealOps<T>::log_(m.p[3]) + mx + RealOps<T>::log_(s);
     }
-    static __device__ void grad(const DevModel<T> &m, const T *z, const uint8_t *mask, const T *x, T *g)
+    template <class Mask>
+    static __device__ __forceinline__ void grad(const DevModel<T> &m, const T *z, Mask mask, const T *x, T *g)
     {
         g[0] = g[1] = g[2] = g[3] = (T)0;
-        const int M = count(m, mask);
+        const int M = observed_count(mask, m.n_obs);
         if (M == 0) return;
         T mx, s, gx, gy;
         accumulate(m, z, mask, x, M, mx, s, gx, gy);
@@ -169,14 +179,14 @@ template <typename T> struct Family<T, CV4D, 4> {
 // matrices and origins) took 75 a joint, and the gradients of 1024 particles
 // 12% of an iteration of the matrix-core step.
 template <typename T> struct Family<T, ARM7, 7> {
-    static __device__ void mean(const DevModel<T> &, int, const T *x, T *out)
+    static __device__ __forceinline__ void mean(const DevModel<T> &, int, const T *x, T *out)
     {
 #pragma unroll
         for (int a = 0; a < 7; ++a) out[a] = x[a];
     }
     // v_{i-1} (x, y parts in vx, vy if wanted) of every joint, with
     // A_i = Rz(q_i) Tz(d_i) Tx(a_i) Rx(alpha_i); p = v_0
-    static __device__ void end_effector(const DevModel<T> &m, const T *q, T *st, T *ct, T *vx, T *vy, T *p)
+    static __device__ __forceinline__ void end_effector(const DevModel<T> &m, const T *q, T *st, T *ct, T *vx, T *vy, T *p)
     {
         T x = 0, y = 0, w = 0;
 #pragma unroll
@@ -192,20 +202,22 @@ template <typename T> struct Family<T, ARM7, 7> {
         }
         p[0] = x; p[1] = y; p[2] = w;
     }
-    static __device__ T loglik(const DevModel<T> &m, const T *z, const uint8_t *mask, const T *x)
+    template <class Mask>
+    static __device__ __forceinline__ T loglik(const DevModel<T> &m, const T *z, Mask mask, const T *x)
     {
-        if (mask && !mask[0]) return (T)0;
+        if (!observed(mask, 0)) return (T)0;
         T st[7], ct[7], vx[7], vy[7], p[3];
         end_effector(m, x, st, ct, vx, vy, p);
         const T e0 = z[0] - p[0], e1 = z[1] - p[1], e2 = z[2] - p[2];
         return (T)-0.5 * (e0 * e0 + e1 * e1 + e2 * e2) / m.p[0]
                - (T)1.5 * RealOps<T>::log_((T)(2.0 * kPi) * m.p[0]);
     }
-    static __device__ void grad(const DevModel<T> &m, const T *z, const uint8_t *mask, const T *x, T *g)
+    template <class Mask>
+    static __device__ __forceinline__ void grad(const DevModel<T> &m, const T *z, Mask mask, const T *x, T *g)
     {
 #pragma unroll
         for (int a = 0; a < 7; ++a) g[a] = (T)0;
-        if (mask && !mask[0]) return;
+        if (!observed(mask, 0)) return;
         T st[7], ct[7], vx[7], vy[7], p[3];
         end_effector(m, x, st, ct, vx, vy, p);
         const T ir = (T)1 / m.p[0];
@@ -230,7 +242,7 @@ template <typename T> struct Family<T, ARM7, 7> {
 // joint-angle gradient are ARM7's, the velocity gradient is zero.
 template <typename T> struct Family<T, ARM14, 14> {
     using Arm = Family<T, ARM7, 7>;
-    static __device__ void mean(const DevModel<T> &m, int t, const T *x, T *out)
+    static __device__ __forceinline__ void mean(const DevModel<T> &m, int t, const T *x, T *out)
     {
         const T dt = m.p[22];
 #pragma unroll
@@ -240,11 +252,13 @@ template <typename T> struct Family<T, ARM14, 14> {
             out[7 + a] = x[7 + a] + u * dt;
         }
     }
-    static __device__ T loglik(const DevModel<T> &m, const T *z, const uint8_t *mask, const T *x)
+    template <class Mask>
+    static __device__ __forceinline__ T loglik(const DevModel<T> &m, const T *z, Mask mask, const T *x)
     {
         return Arm::loglik(m, z, mask, x);
     }
-    static __device__ void grad(const DevModel<T> &m, const T *z, const uint8_t *mask, const T *x, T *g)
+    template <class Mask>
+    static __device__ __forceinline__ void grad(const DevModel<T> &m, const T *z, Mask mask, const T *x, T *g)
     {
         Arm::grad(m, z, mask, x, g);
 #pragma unroll
@@ -261,7 +275,7 @@ template <typename T> struct Family<T, ARM14, 14> {
 // responsibility-weighted sum of the per-landmark gradients, accumulated in
 // the same pass).  The bearing residual is mapped into [-pi, pi).
 template <typename T> struct Family<T, SE2, 3> {
-    static __device__ void mean(const DevModel<T> &m, int, const T *x, T *out)
+    static __device__ __forceinline__ void mean(const DevModel<T> &m, int, const T *x, T *out)
     {
         const T th = x[2] + m.p[2] * m.p[0];
         T s, c;
@@ -271,13 +285,13 @@ template <typename T> struct Family<T, SE2, 3> {
         out[1] = x[1] + vdt * s;
         out[2] = th;
     }
-    static __device__ T wrap(T a)
+    static __device__ __forceinline__ T wrap(T a)
     {
         const T tau = (T)(2.0 * kPi);
         return a - tau * RealOps<T>::floor_((a + (T)kPi) / tau);
     }
     // log-mixture and, with g != nullptr, its gradient in (px, py)
-    static __device__ T mixture(const DevModel<T> &m, const T *z, const T *x, T *g)
+    static __device__ __forceinline__ T mixture(const DevModel<T> &m, const T *z, const T *x, T *g)
     {
         const int nl = (int)m.p[5];
         T mx = -RealOps<T>::inf(), s = 0, g0 = 0, g1 = 0;
@@ -313,22 +327,24 @@ template <typename T> struct Family<T, SE2, 3> {
         }
         return mx + RealOps<T>::log_(s) + m.aux[2];
     }
-    static __device__ T loglik(const DevModel<T> &m, const T *z, const uint8_t *mask, const T *x)
+    template <class Mask>
+    static __device__ __forceinline__ T loglik(const DevModel<T> &m, const T *z, Mask mask, const T *x)
     {
-        if (mask && !mask[0]) return (T)0;
+        if (!observed(mask, 0)) return (T)0;
         return mixture(m, z, x, nullptr);
     }
-    static __device__ void grad(const DevModel<T> &m, const T *z, const uint8_t *mask, const T *x, T *g)
+    template <class Mask>
+    static __device__ __forceinline__ void grad(const DevModel<T> &m, const T *z, Mask mask, const T *x, T *g)
     {
         g[0] = g[1] = g[2] = (T)0;
-        if (mask && !mask[0]) return;
+        if (!observed(mask, 0)) return;
         mixture(m, z, x, g);
     }
 };
 
 // ---------------------------------------------------------------------------
 template <typename T, int D> struct Family<T, LINGAUSS, D> {
-    static __device__ void mean(const DevModel<T> &m, int, const T *x, T *out)
+    static __device__ __forceinline__ void mean(const DevModel<T> &m, int, const T *x, T *out)
     {
 #pragma unroll
         for (int a = 0; a < D; ++a) {
@@ -338,9 +354,10 @@ template <typename T, int D> struct Family<T, LINGAUSS, D> {
             out[a] = s;
         }
     }
-    static __device__ T loglik(const DevModel<T> &m, const T *z, const uint8_t *mask, const T *x)
+    template <class Mask>
+    static __device__ __forceinline__ T loglik(const DevModel<T> &m, const T *z, Mask mask, const T *x)
     {
-        if (mask && !mask[0]) return (T)0;
+        if (!observed(mask, 0)) return (T)0;
         T s = 0;
         for (int r = 0; r < m.obs_dim; ++r) {
             T hx = 0;
@@ -351,11 +368,12 @@ template <typename T, int D> struct Family<T, LINGAUSS, D> {
         }
         return s;
     }
-    static __device__ void grad(const DevModel<T> &m, const T *z, const uint8_t *mask, const T *x, T *g)
+    template <class Mask>
+    static __device__ __forceinline__ void grad(const DevModel<T> &m, const T *z, Mask mask, const T *x, T *g)
     {
 #pragma unroll
         for (int c = 0; c < D; ++c) g[c] = (T)0;
-        if (mask && !mask[0]) return;
+        if (!observed(mask, 0)) return;
         for (int r = 0; r < m.obs_dim; ++r) {
             T hx = 0;
 #pragma unroll
