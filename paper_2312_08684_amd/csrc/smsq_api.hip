@@ -745,17 +745,20 @@ template <typename P> hipError_t dev_alloc(P **p, size_t count, size_t &total)
 struct smsq_init_mlp_s {
     int max_batch = 0, adam_t = 0;
     float *P = nullptr, *G = nullptr, *Mo = nullptr, *Ve = nullptr;
-    uint16_t *w1b = nullptr, *w2b = nullptr, *w3b = nullptr;
+    uint16_t *w1b = nullptr, *w2b = nullptr, *w3b = nullptr, *w2t = nullptr, *w3t = nullptr;
     float *F = nullptr, *anc = nullptr, *scl = nullptr;
     uint16_t *Fb = nullptr;
-    float *pre1 = nullptr, *pre2 = nullptr, *out = nullptr, *dout = nullptr, *d2 = nullptr, *d1 = nullptr;
-    uint16_t *h1 = nullptr, *h2 = nullptr, *doutb = nullptr, *d2b = nullptr, *d1b = nullptr;
-    float *lossv = nullptr;
+    float *pre1 = nullptr, *pre2 = nullptr, *out = nullptr, *dout = nullptr;
+    // transposed: rows of ldT examples (a multiple of 16)
+    uint16_t *FbT = nullptr, *h1T = nullptr, *h2T = nullptr, *doutT = nullptr, *d2T = nullptr, *d1T = nullptr;
+    long ldT = 0;
+    float *part = nullptr, *lossv = nullptr;
     size_t bytes = 0;
+    MlpParams params() const { return MlpParams{P, G, Mo, Ve, w1b, w2b, w3b, w2t, w3t}; }
     void free_all()
     {
-        void *ps[] = {P, G, Mo, Ve, w1b, w2b, w3b, F, anc, scl, Fb, pre1, pre2, out, dout, d2, d1,
-                      h1, h2, doutb, d2b, d1b, lossv};
+        void *ps[] = {P, G, Mo, Ve, w1b, w2b, w3b, w2t, w3t, F, anc, scl, Fb, pre1, pre2, out, dout,
+                      FbT, h1T, h2T, doutT, d2T, d1T, part, lossv};
         for (void *q : ps)
             if (q) (void)hipFree(q);
     }
@@ -778,42 +781,22 @@ hipError_t zero_alloc_bytes(void **p, size_t bytes, size_t &total)
     return e;
 }
 
-void gemm(int M, int N, int K, const uint16_t *A, long sam, long sak, const uint16_t *B, long sbk, long sbn,
-          float *C, long ldc, uint16_t *Cb, long ldcb, const float *bias, const float *pre, long ldpre, int mode,
-          hipStream_t s)
-{
-    const int tiles = ((M + 15) / 16) * ((N + 15) / 16);
-    hipLaunchKernelGGL(k_gemm_bf16, dim3((tiles + 3) / 4), dim3(256), 0, s, M, N, K, A, sam, sak, B, sbk, sbn, C,
-                       ldc, Cb, ldcb, bias, pre, ldpre, mode);
-}
-
 // forward on mlp->Fb (batch rows) into mlp->out
 void mlp_forward(smsq_init_mlp_s *m, int B, hipStream_t s)
 {
-    const int H = kInitHidden;
-    gemm(B, H, kInitFeat, m->Fb, kInitFeat, 1, m->w1b, 1, kInitFeat, m->pre1, H, m->h1, H, m->P + kOffB1, nullptr,
-         0, 0, s);
-    gemm(B, H, H, m->h1, H, 1, m->w2b, 1, H, m->pre2, H, m->h2, H, m->P + kOffB2, nullptr, 0, 0, s);
-    gemm(B, kInitOut, H, m->h2, H, 1, m->w3b, 1, H, m->out, kInitOut, nullptr, 0, m->P + kOffB3, nullptr, 0, 1, s);
+    hipLaunchKernelGGL(k_mlp_forward, dim3((B + kMlpRows - 1) / kMlpRows), dim3(1024), 0, s, B, m->Fb, m->w1b, m->w2b,
+                       m->w3b, m->P, m->pre1, m->pre2, m->out, m->FbT, m->h1T, m->h2T, m->ldT);
 }
 
-// gradients of sum_e <dout_e, out_e> into mlp->G (dout in mlp->dout)
-void mlp_backward(smsq_init_mlp_s *m, int B, hipStream_t s)
+// gradients of sum_e <dout_e, out_e> into mlp->G (dout in mlp->dout); with
+// `adam` also the parameters' step and, unless null, the mean loss
+void mlp_backward(smsq_init_mlp_s *m, int B, const AdamStep *adam, float *mean_loss, hipStream_t s)
 {
-    const int H = kInitHidden, O = kInitOut;
-    hipLaunchKernelGGL(k_to_bf16, dim3((B * O + 255) / 256), dim3(256), 0, s, m->dout, m->doutb, (long)B * O);
-    // W3, b3
-    gemm(O, H, B, m->doutb, 1, O, m->h2, H, 1, m->G + kOffW3, H, nullptr, 0, nullptr, nullptr, 0, 3, s);
-    hipLaunchKernelGGL(k_colsum, dim3((O + 63) / 64), dim3(64), 0, s, B, O, m->dout, (long)O, m->G + kOffB3);
-    // through layer 3 and the second ReLU
-    gemm(B, H, O, m->doutb, O, 1, m->w3b, H, 1, m->d2, H, m->d2b, H, nullptr, m->pre2, H, 2, s);
-    gemm(H, H, B, m->d2b, 1, H, m->h1, H, 1, m->G + kOffW2, H, nullptr, 0, nullptr, nullptr, 0, 3, s);
-    hipLaunchKernelGGL(k_colsum, dim3((H + 63) / 64), dim3(64), 0, s, B, H, m->d2, (long)H, m->G + kOffB2);
-    // through layer 2 and the first ReLU
-    gemm(B, H, H, m->d2b, H, 1, m->w2b, H, 1, m->d1, H, m->d1b, H, nullptr, m->pre1, H, 2, s);
-    gemm(H, kInitFeat, B, m->d1b, 1, H, m->Fb, kInitFeat, 1, m->G + kOffW1, kInitFeat, nullptr, 0, nullptr, nullptr,
-         0, 3, s);
-    hipLaunchKernelGGL(k_colsum, dim3((H + 63) / 64), dim3(64), 0, s, B, H, m->d1, (long)H, m->G + kOffB1);
+    hipLaunchKernelGGL(k_mlp_backward, dim3((B + kMlpRows - 1) / kMlpRows), dim3(1024), 0, s, B, m->dout, m->w2t,
+                       m->w3t, m->pre1, m->pre2, m->doutT, m->d2T, m->d1T, m->part, m->ldT);
+    hipLaunchKernelGGL(k_mlp_grad, dim3(kGradTiles + kGradBias + (mean_loss ? 1 : 0)), dim3(kWave), 0, s, B, m->FbT,
+                       m->h1T, m->h2T, m->d1T, m->d2T, m->doutT, m->part, m->lossv, mean_loss, m->ldT, m->params(),
+                       adam ? *adam : AdamStep{}, adam ? 1 : 0);
 }
 
 void mlp_features(smsq_init_mlp_s *m, const InitExample *ex, int count, hipStream_t s)
@@ -1565,20 +1548,24 @@ smsq_status_t smsq_init_mlp_create(uint64_t seed, int max_batch, smsq_init_mlp_t
     if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->scl, B * 8 * 4, t);
     if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->pre1, B * H * 4, t);
     if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->pre2, B * H * 4, t);
-    if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->h1, B * H * 2, t);
-    if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->h2, B * H * 2, t);
     if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->out, B * kInitOut * 4, t);
     if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->dout, B * kInitOut * 4, t);
-    if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->doutb, B * kInitOut * 2, t);
-    if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->d2, B * H * 4, t);
-    if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->d1, B * H * 4, t);
-    if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->d2b, B * H * 2, t);
-    if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->d1b, B * H * 2, t);
+    if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->w2t, H * H * 2, t);
+    if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->w3t, kInitOutPad * H * 2, t);
+    const size_t ldT = (B + kMlpRows - 1) / kMlpRows * kMlpRows;
+    m->ldT = (long)ldT;
+    if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->FbT, ldT * kInitFeat * 2, t);
+    if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->h1T, ldT * H * 2, t);
+    if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->h2T, ldT * H * 2, t);
+    if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->doutT, ldT * kInitOut * 2, t);
+    if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->d2T, ldT * H * 2, t);
+    if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->d1T, ldT * H * 2, t);
+    if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->part, ldT / kMlpRows * kInitBias * 4, t);
     if (e == hipSuccess) e = zero_alloc_bytes((void **)&m->lossv, B * 4, t);
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_init_he, dim3((kInitParams + 255) / 256), dim3(256), 0, nullptr, m->P, seed);
-        hipLaunchKernelGGL(k_init_weights_bf16, dim3((kInitParams + 255) / 256), dim3(256), 0, nullptr, m->P,
-                           m->w1b, m->w2b, m->w3b);
+        hipLaunchKernelGGL(k_init_weights_bf16, dim3((kInitParams + 255) / 256), dim3(256), 0, nullptr,
+                           m->params());
         e = hipGetLastError();
         if (e == hipSuccess) e = hipDeviceSynchronize();
     }
@@ -1612,8 +1599,7 @@ smsq_status_t smsq_init_mlp_params(smsq_init_mlp_t m, float **params, float **gr
 smsq_status_t smsq_init_mlp_sync(smsq_init_mlp_t m, hipStream_t s)
 {
     if (!m) return SMSQ_ERR_INVALID;
-    hipLaunchKernelGGL(k_init_weights_bf16, dim3((kInitParams + 255) / 256), dim3(256), 0, s, m->P, m->w1b, m->w2b,
-                       m->w3b);
+    hipLaunchKernelGGL(k_init_weights_bf16, dim3((kInitParams + 255) / 256), dim3(256), 0, s, m->params());
     hipLaunchKernelGGL(k_fill_f32, dim3((kInitParams + 255) / 256), dim3(256), 0, s, m->Mo, 0.f, kInitParams);
     hipLaunchKernelGGL(k_fill_f32, dim3((kInitParams + 255) / 256), dim3(256), 0, s, m->Ve, 0.f, kInitParams);
     m->adam_t = 0;
@@ -1710,7 +1696,7 @@ smsq_status_t smsq_init_mlp_backward(smsq_init_mlp_t m, int batch, const void *d
     if (!m || batch < 1 || batch > m->max_batch || !dout) return SMSQ_ERR_INVALID;
     if (hipMemcpyAsync(m->dout, dout, (size_t)batch * kInitOut * 4, hipMemcpyDeviceToDevice, s) != hipSuccess)
         return SMSQ_ERR_HIP;
-    mlp_backward(m, batch, s);
+    mlp_backward(m, batch, nullptr, nullptr, s);
     return hipGetLastError() == hipSuccess ? SMSQ_OK : SMSQ_ERR_HIP;
 }
 
@@ -1719,7 +1705,7 @@ smsq_status_t smsq_init_mixture_nll(smsq_init_set_t st, int first, int count, co
 {
     if (!st || first < 0 || count < 1 || first + count > st->count || !out || !anchors || !scales || !loss || !dout)
         return SMSQ_ERR_INVALID;
-    hipLaunchKernelGGL(k_mix_nll, dim3(count), dim3(kWave), 0, s, st->ex + first, count, (const float *)out,
+    hipLaunchKernelGGL(k_mix_nll, dim3(count), dim3(kWave * kInitK), 0, s, st->ex + first, count, (const float *)out,
                        (const float *)anchors, (const float *)scales, (float *)dout, (float *)loss, (float)gscale);
     return hipGetLastError() == hipSuccess ? SMSQ_OK : SMSQ_ERR_HIP;
 }
@@ -1731,17 +1717,15 @@ smsq_status_t smsq_init_mlp_train_step(smsq_init_mlp_t m, smsq_init_set_t st, in
     const InitExample *ex = st->ex + first;
     mlp_features(m, ex, count, s);
     mlp_forward(m, count, s);
-    hipLaunchKernelGGL(k_mix_nll, dim3(count), dim3(kWave), 0, s, ex, count, m->out, m->anc, m->scl, m->dout,
+    hipLaunchKernelGGL(k_mix_nll, dim3(count), dim3(kWave * kInitK), 0, s, ex, count, m->out, m->anc, m->scl, m->dout,
                        m->lossv, 1.f / (float)count);
-    mlp_backward(m, count, s);
     m->adam_t += 1;
     // Adam constants as FP32 values; their bias corrections in FP64
     const float b1 = 0.9f, b2 = 0.999f;
     const double c1 = 1.0 / (1.0 - std::pow((double)b1, m->adam_t));
     const double c2 = 1.0 / (1.0 - std::pow((double)b2, m->adam_t));
-    hipLaunchKernelGGL(k_adam, dim3((kInitParams + 255) / 256), dim3(256), 0, s, m->P, m->G, m->Mo, m->Ve,
-                       kInitParams, (float)lr, b1, b2, 1e-8f, (float)c1, (float)c2, m->w1b, m->w2b, m->w3b);
-    if (loss_out) hipLaunchKernelGGL(k_mean_f32, dim3(1), dim3(kWave), 0, s, m->lossv, count, (float *)loss_out);
+    const AdamStep adam{(float)lr, b1, b2, 1e-8f, (float)c1, (float)c2};
+    mlp_backward(m, count, &adam, (float *)loss_out, s);
     return hipGetLastError() == hipSuccess ? SMSQ_OK : SMSQ_ERR_HIP;
 }
 
