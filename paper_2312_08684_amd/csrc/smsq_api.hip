@@ -16,6 +16,7 @@
 
 #include "smsq.h"
 #include "smsq_kernels.hpp"
+#include "smsq_small.hpp"
 #include "smsq_wave.hpp"
 #include "smsq_mfma.hpp"
 #include "smsq_batch.hpp"
@@ -231,15 +232,12 @@ smsq_status_t launch_wave_kd(const StepArgs<T> &a, int batch, hipStream_t s)
     return hipGetLastError() == hipSuccess ? SMSQ_OK : SMSQ_ERR_HIP;
 }
 
-// The one-wave kernel fits at most 64 particles and 64 previous ones; by
-// default it takes steps of up to 32 particles in both precisions, and of
-// up to 40 for FP32 states of one or two dimensions (measured: 8..12%
-// faster than the workgroup vector-ALU kernel at 10..20 particles, 2.2x for
-// the 14-D model in FP64, even at 32, slower at 64; in FP32 at 32 particles
-// 0.70..0.89 of the matrix-core kernel's time, and at 40 for the range
-// model 0.73, while the matrix cores win from 40 on for d >= 3 and from 48
-// on for d = 2).  step_kernel = SMSQ_STEP_WAVE selects it wherever it fits,
-// SMSQ_STEP_VALU or SMSQ_STEP_MFMA the other kernels.
+// The one-wave kernel fits at most 64 particles and 64 previous ones; of the
+// batches too large for the small-set kernel it takes steps of up to 32
+// particles in both precisions, and of up to 40 for FP32 states of one or two
+// dimensions (50 iterations of 512 sequences: 40 of the range model 0.91 ms,
+// of 64 on the matrix cores 0.45 ms).  step_kernel = SMSQ_STEP_WAVE selects it
+// wherever it fits, SMSQ_STEP_VALU or SMSQ_STEP_MFMA the other kernels.
 constexpr int kWaveDefaultMax = 32;
 constexpr int kWaveSmallStateMax = 40;
 
@@ -276,10 +274,65 @@ template <typename T>
 smsq_status_t launch_step(const smsq_model_desc_t &d, const StepArgs<T> &a, int batch, int step_kernel,
                           hipStream_t s);
 
+template <typename T, int KIND, int D>
+smsq_status_t launch_small_kd(const StepArgs<T> &a, int batch, hipStream_t s)
+{
+    const SmallLds<T> L(a.n, a.n_prev, D);
+    hipLaunchKernelGGL((k_step_small<T, KIND, D>), dim3(batch), dim3(L.nwaves * kWave), (size_t)L.total, s, a);
+    return hipGetLastError() == hipSuccess ? SMSQ_OK : SMSQ_ERR_HIP;
+}
+
+// The small-set kernel takes what fits it by default while the batch's
+// workgroups are all on the chip, or nearly: 256, one a compute unit; 512 of up
+// to 24 particles (eight waves, two a unit) and four dimensions; 512 where the
+// workgroup vector-ALU kernel is the other one (IMQ and Matern kernels and, up
+// to the 45 particles whose distances the selection holds in registers, FP64).
+// Measured there (50 iterations; time of the kernel that takes the step
+// otherwise / this one's): 1.15 to 5 at 1, 64 and 256 sequences of 10 to 64
+// particles of every family and both precisions, 1.1 to 3.0 at 512.  Beyond,
+// its sixteen lanes a particle cost more than they hide: 0.7 at 512 sequences
+// of 64 in FP32 with the RBF kernel, 0.2 to 0.8 at 2048.
+// The matrix-core kernel is faster for 64 particles of the arm in FP32 (0.90
+// to 1.03; 1.3 at 48), the one-wave kernel for the 14-D model up to 32
+// particles in FP64 (0.7 to 1.03 at 10 and 20; from 33 on 1.5 to 3.1) and, in
+// FP32, in batches above 128 (0.94 at 256; 1.3 to 2.2 up to 128).
+bool use_small(const smsq_model_desc_t &d, int n, int n_prev, int batch, int kernel, bool fp32, int step_kernel)
+{
+    if (n > kSmallMaxParticles || n_prev > kSmallMaxPrev) return false;
+    if (step_kernel == SMSQ_STEP_VALU || step_kernel == SMSQ_STEP_MFMA) return false;
+    if (step_kernel == SMSQ_STEP_WAVE && n_prev <= kWaveMaxParticles) return false;  // (it fits)
+    const bool valu_else = (kernel != 0 || !fp32) && d.d <= 7 && n > kWaveDefaultMax && (fp32 || n <= 45);
+    if (batch > ((n <= 24 && d.d <= 4) || valu_else ? 512 : 256)) return false;
+    if (d.d > 7 && n <= 32 && n_prev <= kWaveMaxParticles) return fp32 && batch <= 128;
+    return !(fp32 && kernel == 0 && d.d > 4 && d.d <= 7 && n > 48);
+}
+
+template <typename T>
+smsq_status_t launch_small(const smsq_model_desc_t &d, const StepArgs<T> &a, int batch, hipStream_t s)
+{
+    switch (d.kind) {
+    case SMSQ_MODEL_GROWTH1D: return launch_small_kd<T, GROWTH1D, 1>(a, batch, s);
+    case SMSQ_MODEL_RANGE2D: return launch_small_kd<T, RANGE2D, 2>(a, batch, s);
+    case SMSQ_MODEL_CV4D: return launch_small_kd<T, CV4D, 4>(a, batch, s);
+    case SMSQ_MODEL_ARM7: return launch_small_kd<T, ARM7, 7>(a, batch, s);
+    case SMSQ_MODEL_SE2: return launch_small_kd<T, SE2, 3>(a, batch, s);
+    case SMSQ_MODEL_ARM14: return launch_small_kd<T, ARM14, 14>(a, batch, s);
+    case SMSQ_MODEL_LINGAUSS:
+        switch (d.d) {
+        case 1: return launch_small_kd<T, LINGAUSS, 1>(a, batch, s);
+        case 2: return launch_small_kd<T, LINGAUSS, 2>(a, batch, s);
+        case 3: return launch_small_kd<T, LINGAUSS, 3>(a, batch, s);
+        case 4: return launch_small_kd<T, LINGAUSS, 4>(a, batch, s);
+        }
+    }
+    return SMSQ_ERR_INVALID;
+}
+
 template <>
 smsq_status_t launch_step<float>(const smsq_model_desc_t &d, const StepArgs<float> &a, int batch, int step_kernel,
                                  hipStream_t s)
 {
+    if (use_small(d, a.n, a.n_prev, batch, a.kernel, true, step_kernel)) return launch_small<float>(d, a, batch, s);
     if (use_wave(a.n, a.n_prev, d.d, true, step_kernel)) return launch_wave<float>(d, a, batch, s);
     // the matrix-core kernel runs the RBF kernel on states of up to 7
     // dimensions; IMQ, Matern and the 14-D model take the vector-ALU kernel
@@ -322,6 +375,7 @@ template <>
 smsq_status_t launch_step<double>(const smsq_model_desc_t &d, const StepArgs<double> &a, int batch, int step_kernel,
                                   hipStream_t s)
 {
+    if (use_small(d, a.n, a.n_prev, batch, a.kernel, false, step_kernel)) return launch_small<double>(d, a, batch, s);
     if (use_wave(a.n, a.n_prev, d.d, false, step_kernel)) return launch_wave<double>(d, a, batch, s);
     switch (d.kind) {
     case SMSQ_MODEL_GROWTH1D: return launch_step_kd<double, GROWTH1D, 1>(a, batch, s);
