@@ -187,7 +187,7 @@ smsq_status_t launch_step_kd(const StepArgs<T> &a, int batch, hipStream_t s)
 }
 
 // The FP32 matrix-core kernel takes sequences of 32 to 1024 particles whose
-// state fits LDS and which the one-wave kernel does not take (below 32
+// state fits LDS and which the kernels for small sets do not take (below 32
 // particles the vector-ALU kernels are faster).  The option step_kernel =
 // SMSQ_STEP_VALU selects the workgroup vector-ALU kernel for every size,
 // SMSQ_STEP_MFMA the matrix-core kernel for every size that fits it
@@ -285,8 +285,9 @@ smsq_status_t launch_small_kd(const StepArgs<T> &a, int batch, hipStream_t s)
 // The small-set kernel takes what fits it by default while the batch's
 // workgroups are all on the chip, or nearly: 256, one a compute unit; 512 of up
 // to 24 particles (eight waves, two a unit) and four dimensions; 512 where the
-// workgroup vector-ALU kernel is the other one (IMQ and Matern kernels and, up
-// to the 45 particles whose distances the selection holds in registers, FP64).
+// workgroup vector-ALU kernel is the other one (IMQ and Matern kernels, FP32 of
+// fewer than 32 particles after more than 64, and FP64 up to the 45 particles
+// whose distances the selection holds in registers or two dimensions).
 // Measured there (50 iterations; time of the kernel that takes the step
 // otherwise / this one's): 1.15 to 5 at 1, 64 and 256 sequences of 10 to 64
 // particles of every family and both precisions, 1.1 to 3.0 at 512.  Beyond,
@@ -301,7 +302,9 @@ bool use_small(const smsq_model_desc_t &d, int n, int n_prev, int batch, int ker
     if (n > kSmallMaxParticles || n_prev > kSmallMaxPrev) return false;
     if (step_kernel == SMSQ_STEP_VALU || step_kernel == SMSQ_STEP_MFMA) return false;
     if (step_kernel == SMSQ_STEP_WAVE && n_prev <= kWaveMaxParticles) return false;  // (it fits)
-    const bool valu_else = (kernel != 0 || !fp32) && d.d <= 7 && n > kWaveDefaultMax && (fp32 || n <= 45);
+    const bool no_wave = n > kWaveDefaultMax || n_prev > kWaveMaxParticles;
+    const bool valu_else = (kernel != 0 || !fp32 || n < kMfmaMinParticles) && no_wave && d.d <= 7 &&
+                           (fp32 || n <= 45 || d.d <= 2);
     if (batch > ((n <= 24 && d.d <= 4) || valu_else ? 512 : 256)) return false;
     if (d.d > 7 && n <= 32 && n_prev <= kWaveMaxParticles) return fp32 && batch <= 128;
     return !(fp32 && kernel == 0 && d.d > 4 && d.d <= 7 && n > 48);
