@@ -6,9 +6,8 @@
 //   * bandwidth: half the squared distances, n_i / 2 + n_k / 2 - x_i . x_k,
 //     come from 16x16 Gram tiles; the exact lower median is found by one pass
 //     that counts the distances below a window predicted from the previous
-//     iterations' medians and keeps (and bins) those inside it, then a rank
-//     among the kept values of the median's bin (radix selections as
-//     fallbacks);
+//     iterations' medians and keeps those inside it, then a rank among the
+//     kept values (histogram and radix passes as fallbacks);
 //   * scores: the transition-mixture softmax over the previous particles,
 //     logit_kj = 2 mh_j . xh_k + c_j - |mh_j|^2 (log2 units; the common
 //     -|xh_k|^2 drops out), as 16x16 tiles relative to a per-particle
@@ -37,6 +36,12 @@
 // Products of pieces are exact in FP32 and the sums accumulate in FP32.
 // Measured against 64-bit values the results are at or below the error of
 // the FP32 MFMA's.
+// Measured (us an SVGD iteration of 256 sequences; FP32 MFMA -> here): 1024
+// particles of the arm 232 -> 129 (launch 23.2 -> 12.9 ms), 512 of the clutter
+// model 72 -> 52, 256 of the range model 22 -> 19.  What bounds it now is
+// vector issue at 1024 (active in 74% of the cycles: exponentials and operand
+// splits, 10.5 vector instructions per 64 pairs beside matrix units busy 37%)
+// and, below 512, the serial stages between barriers.
 //
 // Operand layouts of the 16x16x32 MFMA (checked on gfx950): lane l gives
 // A[l % 16][8 (l / 16) + j] and B[8 (l / 16) + j][l % 16], j = 0..7; result
@@ -104,11 +109,6 @@ __device__ __forceinline__ float fmax_(float a, float b) { return a > b ? a : b;
 __device__ __forceinline__ float uniform(float v)
 {
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
-}
-
-__device__ __forceinline__ uint32_t lanes_below(unsigned long long mask)
-{
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
 // Reductions over a wave's lanes without LDS: rotations within the 16-lane

@@ -7,7 +7,9 @@
 // particle j, in registers, and the loops over the other particles read them
 // with readlane broadcasts instead of LDS round trips.  LDS holds only the
 // n(n-1)/2 pair distances for the median, written to slot k(k-1)/2 + i and
-// selected by the ballot bisection of the vector-ALU kernel.
+// selected by the ballot bisection of the vector-ALU kernel.  It takes the
+// batches that fill the chip (fewer instructions a sequence than the
+// small-set kernel's sixteen lanes a particle).
 #pragma once
 
 #include "smsq_kernels.hpp"
