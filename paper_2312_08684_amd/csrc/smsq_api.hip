@@ -718,11 +718,14 @@ int device_cus()
 // target tasks (k_step_mfma_coop): G is the largest power of two that
 // divides the sequence's 64-particle tasks with batch * G within the
 // compute units (1: the one-workgroup kernels).  Below 512 particles an
-// SVGD iteration of one workgroup (26 us at 256 particles) is too short for
-// the two barriers and exchanges per iteration to pay (measured: no gain at
-// 256, 1.9x at 512, 3.7x at 1024 for one sequence).  Families of the
-// matrix-core drivers with a multi-workgroup kernel: growth, range-only,
-// clutter, arm.
+// SVGD iteration of one workgroup (19 us at 256 particles) is too short for
+// the two barriers and exchanges per iteration to pay.  Time of one workgroup a
+// sequence / of G (50 iterations, range, clutter and arm models): 512 particles
+// 1.5 for one sequence, 1.1 to 1.2 for 16, 0.7 to 0.85 for 32 and 64, which
+// therefore stay on one; 640 1.2 to 1.3 up to 32, 1.04 to 1.08 for 64; 768 1.8
+// to 1.9 and 1.04 to 1.07; 1024 3.3 for one sequence, 2.0 for 16, 1.4 for 64.
+// Families of the matrix-core drivers with a multi-workgroup kernel: growth,
+// range-only, clutter, arm.
 constexpr int kCoopMinParticles = 512;
 bool coop_family(int kind)
 {
@@ -738,6 +741,7 @@ int coop_groups(smsq_dtype_t dt, const smsq_model_desc_t &d, int batch, int n, b
     const int ntasks = (n + 63) / 64;
     if (ntasks * 64 > kMaxParticles) return 1;
     if (!force && (n < kCoopMinParticles || 4L * batch > device_cus())) return 1;
+    if (!force && ntasks <= 8 && 16L * batch > device_cus()) return 1;
     int G = 1;
     while (2 * G <= ntasks && ntasks % (2 * G) == 0 && (long)batch * 2 * G <= device_cus()) G *= 2;
     if (G > 1 && (MfmaLds(d.d <= 3, n, n, kMaxWaves, ntasks * 64 / G).total > MfmaLds::kMfmaLdsBytes ||
