@@ -448,11 +448,17 @@ __global__ __launch_bounds__(1024) void k_step_small(StepArgs<T> a)
         }
     }
 
+    // the previous scores over the log-weights (dead by now): all of them are
+    // read before any is written, so that phi may take phi_prev's place
+    if (a.do_viterbi) {
+        for (int j = tid; j < np; j += nt)
+            SC[j] = a.phi_prev ? a.phi_prev[(long)b * a.phi_prev_stride + j] : (T)0;
+        __syncthreads();
+    }
     if (a.do_viterbi && !idle) {
         // forward recursion: c_ij = log_z - ln2 |xs_i - ms_j|^2 + phi_prev(j),
         // the lanes' candidates merged in the row (the first lane's operand
         // first: a NaN at j = 0 stays)
-        const T *pp = a.phi_prev ? a.phi_prev + (long)b * a.phi_prev_stride : nullptr;
         T xs[D];
 #pragma unroll
         for (int c = 0; c < D; ++c) xs[c] = xi[c] * rs[c];
@@ -466,7 +472,7 @@ __global__ __launch_bounds__(1024) void k_step_small(StepArgs<T> a)
                 q2 += r * r;
             }
             const T A = m.log_z - (T)kLn2 * q2;
-            const T cij = A + (pp ? pp[j] : (T)0);
+            const T cij = A + SC[j];
             nan_seen |= cij != cij ? 1 : 0;
             if (j == 0) { ab.best = cij; ab.arg = 0; }
             else argbest_push(ab, cij, j);
