@@ -162,6 +162,13 @@ constexpr int kMaxParticles = 1024;  // largest sequence the kernel takes
 constexpr float kRefShift = 10.f;
 constexpr float kRefMinSum = 32.f;
 constexpr float kKapShift = 14.f;  // kappa is held times 2^14 (same reason)
+// Largest beta |x|^2 whose kappa is formed from norms and products.  The
+// rounding of their difference reaches 0.5 in the exponent there (2^-21 of
+// beta |x|^2, the same for serial, truncating and single-rounding sums); from
+// 2, at 2^22, an f16 piece of 2^14 kappa overflows and its sums are NaN.  Sets
+// beyond (tight clouds far from their transition means, a particle far from all
+// others, a small bw_scale) take their differences directly, on the vector ALU.
+constexpr float kMaxProductExponent = 1048576.f;  // 2^20
 constexpr float kNoSource = -1e30f;  // logit of a source that takes no part (its exponential is 0)
 // Half the squared norm of a pad particle: its distances are never the median
 // and its kernel values are 0 (one bf16 piece, so no infinity minus infinity)
@@ -1206,6 +1213,41 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
         }
         target_operand<K4>(ph, pm, pl, cst, g, b0, b1);
     };
+    // coordinates of particle k
+    auto target_x = [&](int k, float (&xt)[D]) {
+        PieceRow<K4> p;
+        p.load(smem, L.off_x, npad, k);
+#pragma unroll
+        for (int c = 0; c < D; ++c) xt[c] = p.at(c);
+    };
+    // score_sums on the vector ALU, whatever the logits' magnitude: the
+    // exponentials stay in FP32, relative to the largest logit so far
+    auto score_direct = [&](int kbase, int blk0, int blk1, float &nref, float (&os)[NC]) {
+        float xs[D], mx = kNoSource, sum = 0.f, acc[D];
+        target_x(kbase + (fresh_tid() & (kTask - 1)), xs);
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+            xs[c] *= rs[c];
+            acc[c] = 0.f;
+        }
+        const int j1 = min(32 * blk1, np);
+        for (int j = 32 * blk0; j < j1; ++j) {
+            PieceRow<K4> p;
+            p.load(smem, L.off_vt, nppad, j);
+            float logit = p.at(kLast);
+#pragma unroll
+            for (int c = 0; c < D; ++c) logit += p.at(c) * xs[c];
+            const float nm = logit > mx ? logit : mx;
+            const float sf = R::exp2_(mx - nm), e = logit > 0.1f * kNoSource ? R::exp2_(logit - nm) : logit - logit;
+            mx = nm;
+            sum = sum * sf + e;
+#pragma unroll
+            for (int c = 0; c < D; ++c) acc[c] = acc[c] * sf + e * p.at(c);
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) os[c] = c == kLast ? sum : c < D ? acc[c < D ? c : 0] * ms_scale : 0.f;
+        nref = mx > 0.1f * kNoSource ? -mx : 0.f;
+    };
     // os[c] = sum_j e_kj [2 mh_j, 1] (times ms_scale but for the last) over the
     // source blocks [blk0, blk1) for this lane's particle kbase + lane,
     // e_kj = exp2(logit_kj - sref)
@@ -1265,7 +1307,11 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
             collect_rows<K4, QT>(O, os);
             const float s = os[kLast];
             const bool ok = lane >= kTask || (s >= kRefMinSum && s < 1e30f) || (nref == 0.f && s == 0.f);
-            if (from_max || !__builtin_amdgcn_ballot_w64(!ok)) break;
+            if (!__builtin_amdgcn_ballot_w64(!ok)) break;
+            if (from_max) {  // (logits so large that their rounding overflows a piece)
+                score_direct(kbase, blk0, blk1, nref, os);
+                break;
+            }
             from_max = true;
         }
         sref = -nref;
@@ -1274,12 +1320,6 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
     };
     // score row of a particle: the observation's gradient, then the transition
     // term from its softmax sums
-    auto target_x = [&](int k, float (&xt)[D]) {
-        PieceRow<K4> p;
-        p.load(smem, L.off_x, npad, k);
-#pragma unroll
-        for (int c = 0; c < D; ++c) xt[c] = p.at(c);
-    };
     auto score_grad = [&](const float (&xt)[D], float (&s)[D]) {
         float xa[D];
 #pragma unroll
@@ -1620,6 +1660,11 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
         f16_scale(uniform(smax + c2 * xmax), v_scale, v_inv);
         v_inv *= inv_n * 6.103515625e-05f;  // 2^-14 of kappa
         const float k_inv = inv_n * 6.103515625e-05f;
+        // kappa from differences (kMaxProductExponent); |x|^2 <= D max |x_c|^2.
+        // The table then holds the score rows in FP32.
+        const bool direct = !(uniform(beta * (float)D * xmax * xmax) <= kMaxProductExponent);
+        float *const srows = (float *)(smem + L.off_v);
+        if (direct) v_inv = inv_n;
         // (a workgroup that splits has two threads or more per particle: the
         // second puts the target operands)
         constexpr bool kOther = SPLIT && !COOP;
@@ -1635,6 +1680,11 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
                 put_target<K4>(smem, L.off_b, ntl, k - npad, v, cst);
             }
             if (k >= npad) break;
+            if (direct) {
+#pragma unroll
+                for (int c = 0; c < D; ++c) srows[k * D + c] = k < n ? srow[ts][c] : 0.f;
+                continue;
+            }
             p.load(smem, L.off_x, npad, k);
 #pragma unroll
             for (int c = 0; c < NC; ++c) v[c] = 0.f;
@@ -1655,6 +1705,28 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
         // sums over the source blocks [blk0, blk1) for the targets of a task
         auto stein_sums = [&](int ibase, int blk0, int blk1, float (&so)[NC]) {
             const int lane = fresh_tid() & 63, g = lane >> 4, col = lane & 15;
+            if (direct) {  // (the kernel-gradient term included; no sum of kappa)
+                float xi[D], acc[D];
+                target_x(ibase + (lane & (kTask - 1)), xi);
+#pragma unroll
+                for (int c = 0; c < D; ++c) acc[c] = 0.f;
+                const int k1 = min(32 * blk1, n);
+                for (int k = 32 * blk0; k < k1; ++k) {
+                    float df[D], dd = 0.f;
+                    target_x(k, df);
+#pragma unroll
+                    for (int c = 0; c < D; ++c) {
+                        df[c] = xi[c] - df[c];
+                        dd += df[c] * df[c];
+                    }
+                    const float kap = R::exp2_(-beta * dd);
+#pragma unroll
+                    for (int c = 0; c < D; ++c) acc[c] += kap * (srows[k * D + c] + c2 * df[c]);
+                }
+#pragma unroll
+                for (int c = 0; c < NC; ++c) so[c] = c < D ? acc[c < D ? c : 0] : 0.f;
+                return;
+            }
             u32x4 b0[QT], b1[QT];
             f32x4 O[QT];
             SourceRows<K4> src;
