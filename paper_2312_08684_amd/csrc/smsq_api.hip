@@ -197,7 +197,7 @@ constexpr int kMfmaMinParticles = 32;
 bool use_mfma(int d, int n, int n_prev, int step_kernel)
 {
     if (step_kernel == SMSQ_STEP_VALU) return false;
-    const MfmaLds L(d <= 3, n, n_prev);
+    const MfmaLds L(d, n, n_prev);
     const bool fits = L.npad <= kMaxParticles && L.total <= MfmaLds::kMfmaLdsBytes;
     if (step_kernel == SMSQ_STEP_MFMA) return fits;
     return fits && n >= kMfmaMinParticles;
@@ -211,7 +211,7 @@ smsq_status_t launch_mfma_split(const StepArgs<float> &a, int batch, hipStream_t
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [&] { attr_err = allow_big_lds(fn); });
     if (attr_err != hipSuccess) return SMSQ_ERR_HIP;
-    const MfmaLds L(D <= 3, a.n, a.n_prev);
+    const MfmaLds L(D, a.n, a.n_prev);
     hipLaunchKernelGGL(fn, dim3(batch), dim3(L.nwaves * kWave), (size_t)L.total, s, a);
     return hipGetLastError() == hipSuccess ? SMSQ_OK : SMSQ_ERR_HIP;
 }
@@ -221,7 +221,7 @@ smsq_status_t launch_mfma_split(const StepArgs<float> &a, int batch, hipStream_t
 template <int KIND, int D>
 smsq_status_t launch_mfma_kd(const StepArgs<float> &a, int batch, hipStream_t s)
 {
-    return MfmaLds(D <= 3, a.n, a.n_prev).split ? launch_mfma_split<KIND, D, true>(a, batch, s)
+    return MfmaLds(D, a.n, a.n_prev).split ? launch_mfma_split<KIND, D, true>(a, batch, s)
                                               : launch_mfma_split<KIND, D, false>(a, batch, s);
 }
 
@@ -600,7 +600,7 @@ smsq_status_t launch_coop_kd(const StepArgs<float> &a, int batch, const CoopArgs
     std::call_once(once, [&] { attr_err = allow_big_lds(fn); });
     if (attr_err != hipSuccess) return SMSQ_ERR_HIP;
     const int npad = (a.n + 63) / 64 * 64;
-    const MfmaLds L(D <= 3, a.n, a.n_prev, kMaxWaves, npad / c.G);
+    const MfmaLds L(D, a.n, a.n_prev, kMaxWaves, npad / c.G);
     hipLaunchKernelGGL(k_coop_reset, dim3((batch + 63) / 64), dim3(64), 0, s, c.base, c.stride, batch);
     StepArgs<float> aa = a;
     CoopArgs cc = c;
@@ -744,8 +744,8 @@ int coop_groups(smsq_dtype_t dt, const smsq_model_desc_t &d, int batch, int n, b
     if (!force && ntasks <= 8 && 16L * batch > device_cus()) return 1;
     int G = 1;
     while (2 * G <= ntasks && ntasks % (2 * G) == 0 && (long)batch * 2 * G <= device_cus()) G *= 2;
-    if (G > 1 && (MfmaLds(d.d <= 3, n, n, kMaxWaves, ntasks * 64 / G).total > MfmaLds::kMfmaLdsBytes ||
-                  MfmaLds(d.d <= 3, n, 1, kMaxWaves, ntasks * 64 / G).total > MfmaLds::kMfmaLdsBytes))
+    if (G > 1 && (MfmaLds(d.d, n, n, kMaxWaves, ntasks * 64 / G).total > MfmaLds::kMfmaLdsBytes ||
+                  MfmaLds(d.d, n, 1, kMaxWaves, ntasks * 64 / G).total > MfmaLds::kMfmaLdsBytes))
         return 1;
     return G;
 }
@@ -1372,7 +1372,7 @@ smsq_status_t smsq_batch_plan_create(const smsq_model_t *models, const smsq_svgd
         if (q.n > kMaxParticles) return SMSQ_ERR_UNSUPPORTED;
         // either workgroup shape, first and later steps
         for (int waves : {8, 16})
-            for (int np : {1, q.n}) lds = std::max(lds, MfmaLds(d.d <= 3, q.n, np, waves).total);
+            for (int np : {1, q.n}) lds = std::max(lds, (long)MfmaLds(d.d, q.n, np, waves).total);
         if (lds > kLdsLimit - kBatchStaticLds) return SMSQ_ERR_UNSUPPORTED;
         max_n = std::max(max_n, q.n);
         T_max = std::max(T_max, q.T);

@@ -96,7 +96,7 @@ __device__ __forceinline__ void batch_step_loop(const StepArgs<float> *__restric
         __syncthreads();
         if (k >= count) break;
         ConstStepArgs *const a = (ConstStepArgs *)(items + k);
-        const bool split = MfmaLds(a->m.d <= 3, a->n, a->n_prev, (int)(blockDim.x >> 6)).split;
+        const bool split = MfmaLds(a->m.d, a->n, a->n_prev, (int)(blockDim.x >> 6)).split;
         switch (codes[k] + (split ? kBatchFamilies : 0)) {
         case GROWTH1D: step_mfma_body<GROWTH1D, 1, TS, false>(a, 0); break;
         case RANGE2D: step_mfma_body<RANGE2D, 2, TS, false>(a, 0); break;

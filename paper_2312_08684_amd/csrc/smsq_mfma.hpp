@@ -24,21 +24,33 @@
 // meanwhile), the 16-bit one runs beside it (a 16x16x32 product takes 6 to 8
 // cycles of the ALU's time), so every contraction runs on the latter with its
 // FP32 operands split:
-//   * logits, Gram tiles and distances: each operand is cut (truncation) into
-//     three bf16 pieces h + m + l of 8 bits, which hold all 24 bits exactly,
-//     and the products hh, hm, mh, mm, hl, lh (and ml where there is room)
-//     fill the K-slots; what is left out is below 2^-24 of |a||b|;
-//   * weighted sums: the exponentials and the vectors they weigh are cut
-//     (round to nearest) into two f16 pieces, 2^-24 of the value, all four
-//     products kept; the exponentials are held near 2^10 (softmax) or at most
-//     2^14 (kappa), and the vectors scaled by a power of two, so that the
-//     pieces stay above the subnormals.
-// Products of pieces are exact in FP32 and the sums accumulate in FP32.
-// Measured against 64-bit values the results are at or below the error of
-// the FP32 MFMA's.
+//   * logits, Gram tiles and distances: each operand is cut (round to nearest)
+//     into three bf16 pieces h + m + l, which hold all 24 bits exactly, |m| and
+//     |l| at most 2^-8 and 2^-17 of the value's power of two and of either
+//     sign, and the products hh, hm, mh, mm, hl, lh and ml fill the K-slots;
+//     lm and ll are left out, 2^-25 of the operands' powers of two at most and
+//     without bias (pieces cut by truncation left out up to 2^-22, all of the
+//     product's sign);
+//   * weighted sums: the vectors are cut (round to nearest) into three f16
+//     pieces, which hold 24 bits of values above 2, with a power of two of its
+//     own as scale for each component (kScaledMax, kTinyShare).  The
+//     exponentials are cut into two f16 pieces, held near 2^3 (softmax) or at
+//     most 2^3 (kappa): the pair is the FP32 value or, for a quarter of them, its
+//     even neighbour, as far off as v_exp_f32 itself, and the same in the sums
+//     and in their divisor (a third piece changes no error below in its third
+//     digit and takes 25% longer).
+// Products of pieces are exact in FP32.  The products of a block of 32 sources
+// are summed by the matrix cores, the blocks by the vector ALU: an MFMA adds
+// with 0.6 units in the last place (rms) of its largest addend, and 16 blocks
+// chained through its accumulator put the direction of 512 particles 1.6 times
+// as far off as FP32 MFMAs do.
+// Error of an iteration's direction against 64 bits (rms over sets; FP32 MFMA
+// -> here): 64 and 256 particles of the arm 4.4e-7 -> 3.6e-7 and 4.1e-7 -> 3.4e-7,
+// of the range model 3.3e-7 -> 3.1e-7 and 3.2e-7 -> 2.8e-7, 512 of the clutter
+// model 2.2e-7 -> 1.9e-7.
 // Measured (us an SVGD iteration of 256 sequences; FP32 MFMA -> here): 1024
-// particles of the arm 232 -> 129 (launch 23.2 -> 12.9 ms), 512 of the clutter
-// model 72 -> 52, 256 of the range model 22 -> 19.  What bounds it now is
+// particles of the arm 240 -> 145, 512 of the clutter model 70 -> 45, 256 of the
+// range model 21 -> 17.  What bounds it now is
 // vector issue at 1024 (active in 74% of the cycles: exponentials and operand
 // splits, 10.5 vector instructions per 64 pairs beside matrix units busy 37%)
 // and, below 512, the serial stages between barriers.
@@ -57,6 +69,7 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
@@ -72,24 +85,44 @@ __device__ __forceinline__ f32x4 mfma_f16(u32x4 a, u32x4 b, f32x4 c)
                                                   0);
 }
 
-// the three bf16 pieces of two floats, packed (first float in the low half)
+// low / high bf16 of a packed word as a float
+__device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+
+// two floats as bf16, packed (first float in the low half)
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+// the three bf16 pieces of two floats, packed
 struct Pieces3 {
     uint32_t h, m, l;
 };
 __device__ __forceinline__ Pieces3 split3(float a, float b)
 {
-    const uint32_t ah = __float_as_uint(a) & 0xffff0000u, bh = __float_as_uint(b) & 0xffff0000u;
-    const float ar = a - __uint_as_float(ah), br = b - __uint_as_float(bh);
-    const uint32_t am = __float_as_uint(ar) & 0xffff0000u, bm = __float_as_uint(br) & 0xffff0000u;
-    const float al = ar - __uint_as_float(am), bl = br - __uint_as_float(bm);
-    // the high halves of two words (0x07060302: bytes 2, 3 of the second
-    // argument, then of the first)
-    return Pieces3{__builtin_amdgcn_perm(bh, ah, 0x07060302u), __builtin_amdgcn_perm(bm, am, 0x07060302u),
-                   __builtin_amdgcn_perm(__float_as_uint(bl), __float_as_uint(al), 0x07060302u)};
+    Pieces3 p;
+    p.h = pack_bf16(a, b);
+    a -= bf_lo(p.h);
+    b -= bf_hi(p.h);
+    p.m = pack_bf16(a, b);
+    p.l = pack_bf16(a - bf_lo(p.m), b - bf_hi(p.m));
+    return p;
 }
-// low / high bf16 of a packed word as a float
-__device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+
+// The same with the second float's pieces cut by truncation, all of its sign: a
+// component that meets a pad's norm, whose products of pieces overflow, and may
+// do so to one infinity only.
+__device__ __forceinline__ Pieces3 split3_last(float a, float b)
+{
+    auto put = [](float lo, float hi) { return (pack_bf16(lo, 0.f) & 0xffffu) | (__float_as_uint(hi) & 0xffff0000u); };
+    Pieces3 p;
+    p.h = put(a, b);
+    a -= bf_lo(p.h);
+    b -= bf_hi(p.h);
+    p.m = put(a, b);
+    p.l = put(a - bf_lo(p.m), b - bf_hi(p.m));
+    return p;
+}
 
 // the two f16 pieces of two floats, packed.  `neg1` is -1 held in a register
 // the compiler cannot see through, so that the residuals stay mixed-precision
@@ -153,26 +186,40 @@ __device__ __forceinline__ float group_max4(float v)
 constexpr int kMaxWaves = 16;
 constexpr int kMaxParticles = 1024;  // largest sequence the kernel takes
 // A workgroup of W waves takes up to W * TS tasks (TS task slots per wave).
-// Exponentials of the softmax are taken relative to a reference 10 below (in
+// Exponentials of the softmax are taken relative to a reference 3 below (in
 // log2 units) the particle's log-sum-exp at the previous iteration, so they
-// sum to about 2^10.  A pass whose sums leave [2^5, inf) repeats with the
+// sum to about 2^3.  A pass whose sums leave [1, inf) repeats with the
 // reference at the largest logit: above 2^16 an f16 piece overflows (and
-// turns the sum into a NaN), and below 2^5 the smallest pieces, of absolute
-// error 2^-25, would show beside FP32 rounding.
-constexpr float kRefShift = 10.f;
-constexpr float kRefMinSum = 32.f;
-constexpr float kKapShift = 14.f;  // kappa is held times 2^14 (same reason)
-// Largest beta |x|^2 whose kappa is formed from norms and products.  The
-// rounding of their difference reaches 0.5 in the exponent there (2^-21 of
-// beta |x|^2, the same for serial, truncating and single-rounding sums); from
-// 2, at 2^22, an f16 piece of 2^14 kappa overflows and its sums are NaN.  Sets
-// beyond (tight clouds far from their transition means, a particle far from all
-// others, a small bw_scale) take their differences directly, on the vector ALU.
-constexpr float kMaxProductExponent = 1048576.f;  // 2^20
+// turns the sum into a NaN), and below 1 the smallest pieces, of absolute
+// error 2^-25, would show beside FP32 rounding.  The shift also adds to the
+// rounding of the exponents, which are largest where the weights are: at 10
+// the direction of 256 particles of the clutter model is off by 3.6e-7, at 3
+// by 2.1e-7.
+constexpr float kRefShift = 3.f;
+constexpr float kRefMinSum = 1.f;
 constexpr float kNoSource = -1e30f;  // logit of a source that takes no part (its exponential is 0)
 // Half the squared norm of a pad particle: its distances are never the median
 // and its kernel values are 0 (one bf16 piece, so no infinity minus infinity)
 constexpr float kPadHalfNorm = 8.507059173023462e37f;  // 2^126
+constexpr float kKapShift = 3.f;   // kappa is held times 2^3 (same reasons)
+constexpr float kKapScale = 8.f;
+// Largest beta |x|^2 whose kappa is formed from norms and products.  The
+// rounding of their difference reaches 0.5 in the exponent there (2^-21 of
+// beta |x|^2, the same for serial, truncating and single-rounding sums) and 13
+// at 2^25, where an f16 piece of 2^3 kappa overflows and its sums are NaN.  Sets
+// beyond (tight clouds far from their transition means, a particle
+// far from all others, a small bw_scale) take their differences directly, on
+// the vector ALU.
+constexpr float kMaxProductExponent = 1048576.f;  // 2^20
+// Scales of the sums' vectors, a power of two for each component, bring the
+// largest value to 2^13 .. 2^14 when they are set, and stay until a value
+// reaches 2^15 or more than one in kTinyShare of a wave's values lie below 2,
+// where three f16 pieces hold fewer than 24 bits.  (Fewer than that are values
+// near a zero crossing, which count for nothing beside the others.)  Where fresh
+// scales leave as many below 2 (one particle far beyond all others), the sums
+// are formed on the vector ALU.
+constexpr float kScaledMax = 32768.f;
+constexpr int kTinyShare = 4;
 
 // LDS byte layout of the MFMA step workgroup, and how its waves share the
 // pairwise work.  Large sequences (more 32-particle tasks than waves): each
@@ -193,20 +240,22 @@ constexpr float kPadHalfNorm = 8.507059173023462e37f;  // 2^126
 // place of eight.  Tables, with R = 4 or 8 components:
 //   off_x   three planes [npad][R] bf16, the pieces of [x, |x|^2 / 2]
 //   off_vt  three planes [nppad][R] bf16, the pieces of [2 mh, c']
-//   off_v   [npad / 32][2 R][32] f16: pieces of the scaled [v, 1] (Stein sums)
-//   off_ms  [nppad / 32][2 R][32] f16: pieces of the scaled [2 mh, 1]
+//   off_v   [npad / 32][sum_rows][32] f16: pieces of the scaled [v, 1] (Stein sums)
+//   off_ms  [nppad / 32][sum_rows][32] f16: pieces of the scaled [2 mh, 1]
 //   off_b   operands of the workgroup's targets, in turn of the score and the
 //           Stein pass, where several waves share a task (each would form them
 //           again: 250 to 550 instructions a pass, as much as the pass itself
 //           at 256 particles)
 // The two sums' tables share one region where LDS is short (1024 particles of
 // d >= 4): the transition one is then rebuilt each iteration.
+__host__ __device__ constexpr int sum_rows(int d) { return d <= 3 ? 12 : d == 4 ? 13 : 24; }
 struct MfmaLds {
-    long off_x, off_vt, off_v, off_ms, off_b, off_win, off_z, off_red, off_ones, off_part, total;
+    int off_x, off_vt, off_v, off_ms, off_b, off_win, off_z, off_red, off_ones, off_part, total;
     int npad, nppad, nwaves, task, ntasks, ns_sc, ns_st, ns_max, win_cap;
     bool split, ms_shared, b_table;
-    __host__ __device__ MfmaLds(bool k4, int n, int n_prev, int waves = kMaxWaves, int targets_local = 0)
+    __host__ __device__ MfmaLds(int d, int n, int n_prev, int waves = kMaxWaves, int targets_local = 0)
     {
+        const bool k4 = d <= 3;
         npad = (n + 63) / 64 * 64;
         nppad = (n_prev + 31) / 32 * 32;
         const int targets = targets_local > 0 ? targets_local : npad;
@@ -223,20 +272,22 @@ struct MfmaLds {
             // (from 256 particles on the idle waves take part in the median's pass)
             if (npad < 256) nwaves = ntasks * ns_max;
         }
-        const long row = k4 ? 8 : 16;  // bytes of a table row
+        const int row = k4 ? 8 : 16;  // bytes of a table row
         // partial sums of the splits: [ns_max][targets][R + 1] floats
-        const long part = split ? align16((long)ns_max * targets * (k4 ? 5 : 9) * 4) : 0;
+        const int part = split ? (int)align16(ns_max * targets * (k4 ? 5 : 9) * 4) : 0;
         // the multi-workgroup mode keeps them over the sums' tables
         const bool alias = targets_local > 0;
-        const long vb = (long)npad * 2 * row, mb = (long)nppad * 2 * row;
+        const int vb = npad * 2 * sum_rows(d), mb = nppad * 2 * sum_rows(d);
+        // (also the rows [mh, phi] of the forward recursion, in FP32)
+        const int rows = nppad * (k4 ? 16 : 32);
         // target operands: four planes (k4: three) of 16 bytes per target
-        const long bb = (long)targets * (k4 ? 48 : 64);
-        const long fixed = 3 * row * (npad + nppad) + 128 + 512 + 16 + (alias ? 0 : part) + 1024;
+        const int bb = targets * (k4 ? 48 : 64);
+        const int fixed = 3 * row * (npad + nppad) + 128 + 512 + 16 + (alias ? 0 : part) + 1024;
         // what fits, in the order of what it saves: target operands in a table
         // (several waves share each task), the sums' tables apart (else the
         // transition one is rebuilt each iteration), a window buffer of 4096
         // values (else 2048; also the histogram of a range or radix pass)
-        long sums = 0;
+        int sums = 0;
         for (int choice = 0; choice < 8; ++choice) {
             b_table = !(choice & 4);
             ms_shared = alias || (choice & 2);
@@ -244,9 +295,10 @@ struct MfmaLds {
             if (b_table && !split) continue;
             sums = ms_shared ? (vb > mb ? vb : mb) : vb + mb;
             if (alias && sums < part) sums = part;
-            if (fixed + sums + (b_table ? bb : 0) + 4L * win_cap <= kMfmaLdsBytes) break;
+            if (sums < rows) sums = rows;
+            if (fixed + sums + (b_table ? bb : 0) + 4 * win_cap <= kMfmaLdsBytes) break;
         }
-        long o = 0;
+        int o = 0;
         off_x = o; o += 3 * row * npad;
         off_vt = o; o += 3 * row * nppad;
         off_v = o;
@@ -254,52 +306,65 @@ struct MfmaLds {
         off_part = alias ? o : o + sums;
         o += sums + (alias ? 0 : part);
         off_b = o; o += b_table ? bb : 0;
-        off_win = o; o += 4L * win_cap + 1024;  // window buffer, bins of its selection
+        off_win = o; o += 4 * win_cap + 1024;  // window buffer, bins of its selection
         off_z = o; o += 128;
         off_red = o; o += 512;  // uint slots 0..63, float slots from byte 256
         off_ones = o; o += 16;
         total = o;
     }
-    static constexpr long kMfmaLdsBytes = 160 * 1024 - 256;  // less the persistent kernels' static words
+    static constexpr int kMfmaLdsBytes = 160 * 1024 - 256;  // less the persistent kernels' static words
 };
+
+// LDS addresses held as such, opaque to the compiler (which would keep an offset
+// and add the array's address at every read)
+__device__ __forceinline__ uint32_t lds_address(const unsigned char *p, uint32_t offset)
+{
+    uint32_t a = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) unsigned char *)p + offset;
+    asm("" : "+v"(a));
+    return a;
+}
+template <typename V> __device__ __forceinline__ V lds_read(uint32_t address)
+{
+    return *(const __attribute__((address_space(3))) V *)(uintptr_t)address;
+}
 
 // A lane's 16-bit A operands of one table: rows are sources, K-slots the
 // piece products.  With eight components lane group g holds in the first MFMA
 // piece (h, h, m, m)[g] against the B pieces (h, m, h, m)[g], in the second
 // (h, l, 1, m)[g] against (l, h, constant, l)[g]; with four components the
 // one MFMA holds two products per group, (hh, hm | mh, mm | hl, lh |
-// constant).  The constant group carries the pieces of a per-target constant
-// against ones.
+// constant, ml).  The constant's slots carry the pieces of a per-target
+// constant against ones.
 template <bool K4> struct SourceRows {
     uint32_t o0, o1, s1;
-    __device__ void init(long base, int rows, long ones, int g, int col)
+    __device__ void init(const unsigned char *smem, int base, int rows, int ones, int g, int col)
     {
         if (K4) {
-            o0 = (uint32_t)(g == 3 ? ones : base + (long)(g == 1 ? rows * 8 : 0) + col * 8);
-            o1 = (uint32_t)(g == 3 ? ones + 8 : base + (long)g * rows * 8 + col * 8);
+            o0 = lds_address(smem, (uint32_t)(g == 3 ? ones : base + (g == 1 ? rows * 8 : 0) + col * 8));
+            o1 = lds_address(smem, (uint32_t)(base + (g == 3 ? 1 : g) * rows * 8 + col * 8));
             s1 = g == 3 ? 0u : 128u;
         } else {
-            o0 = (uint32_t)(base + (long)(g >> 1) * rows * 16 + col * 16);
-            o1 = (uint32_t)(g == 2 ? ones : base + (long)(g == 0 ? 0 : g == 1 ? 2 : 1) * rows * 16 + col * 16);
+            o0 = lds_address(smem, (uint32_t)(base + (g >> 1) * rows * 16 + col * 16));
+            o1 = lds_address(smem, (uint32_t)(g == 2 ? ones : base + (g == 0 ? 0 : g == 1 ? 2 : 1) * rows * 16 + col * 16));
             s1 = g == 2 ? 0u : 256u;
         }
     }
-    __device__ __forceinline__ void load(const unsigned char *smem, int tile, u32x4 &a0, u32x4 &a1) const
+    __device__ __forceinline__ void load(int tile, u32x4 &a0, u32x4 &a1) const
     {
         if (K4) {
-            const u32x2 p = *(const u32x2 *)(smem + o0 + (uint32_t)tile * s1);
-            const u32x2 q = *(const u32x2 *)(smem + o1 + (uint32_t)tile * s1);
+            const u32x2 p = lds_read<u32x2>(o0 + (uint32_t)tile * s1);
+            const u32x2 q = lds_read<u32x2>(o1 + (uint32_t)tile * 128u);
             a0 = u32x4{p[0], p[1], q[0], q[1]};
         } else {
-            a0 = *(const u32x4 *)(smem + o0 + (uint32_t)tile * 256u);
-            a1 = *(const u32x4 *)(smem + o1 + (uint32_t)tile * s1);
+            a0 = lds_read<u32x4>(o0 + (uint32_t)tile * 256u);
+            a1 = lds_read<u32x4>(o1 + (uint32_t)tile * s1);
         }
     }
     // moves the rows on by some tiles
     __device__ __forceinline__ void skip(int tiles)
     {
         o0 += (uint32_t)tiles * (K4 ? s1 : 256u);
-        o1 += (uint32_t)tiles * s1;
+        o1 += (uint32_t)tiles * (K4 ? 128u : s1);
     }
     static __device__ __forceinline__ f32x4 dot(u32x4 a0, u32x4 a1, u32x4 b0, u32x4 b1,
                                                 f32x4 c = f32x4{0.f, 0.f, 0.f, 0.f})
@@ -325,7 +390,7 @@ __device__ __forceinline__ void target_operand(const uint32_t *h, const uint32_t
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             b0[q] = pick(high, pick(odd, cc[q], l[q]), h[q]);
-            b0[2 + q] = pick(high, h[q] & ~odd, m[q]);
+            b0[2 + q] = pick(high, pick(odd, l[q], h[q]), m[q]);
         }
     } else {
         const uint32_t g1 = odd & ~high, g2 = high & ~odd;
@@ -347,9 +412,9 @@ template <bool K4> __device__ __forceinline__ void target_constant(float cst, in
 }
 
 // The table of target operands: planes h, m, l and the constant ([h m], [l h]
-// and the constant with four components) of 16 bytes per target.
+// and [constant l] with four components) of 16 bytes per target.
 template <bool K4>
-__device__ __forceinline__ void put_target(unsigned char *smem, long base, int rows, int r, const float (&v)[K4 ? 4 : 8],
+__device__ __forceinline__ void put_target(unsigned char *smem, int base, int rows, int r, const float (&v)[K4 ? 4 : 8],
                                            float cst)
 {
     constexpr int W = K4 ? 2 : 4;
@@ -357,7 +422,7 @@ __device__ __forceinline__ void put_target(unsigned char *smem, long base, int r
     uint32_t h[W], m[W], l[W];
 #pragma unroll
     for (int q = 0; q < W; ++q) {
-        const Pieces3 p = split3(v[2 * q], v[2 * q + 1]);
+        const Pieces3 p = q == W - 1 ? split3_last(v[2 * q], v[2 * q + 1]) : split3(v[2 * q], v[2 * q + 1]);
         h[q] = p.h;
         m[q] = p.m;
         l[q] = p.l;
@@ -367,7 +432,7 @@ __device__ __forceinline__ void put_target(unsigned char *smem, long base, int r
     if constexpr (K4) {
         t[0] = u32x4{h[0], h[1], m[0], m[1]};
         t[rows] = u32x4{l[0], l[1], h[0], h[1]};
-        t[2 * rows] = cc;
+        t[2 * rows] = u32x4{cc[0], cc[1], l[0], l[1]};
     } else {
         t[0] = u32x4{h[0], h[1], h[2], h[3]};
         t[rows] = u32x4{m[0], m[1], m[2], m[3]};
@@ -376,7 +441,7 @@ __device__ __forceinline__ void put_target(unsigned char *smem, long base, int r
     }
 }
 template <bool K4>
-__device__ __forceinline__ void load_target(const unsigned char *smem, long base, int rows, int r, int g, u32x4 &b0,
+__device__ __forceinline__ void load_target(const unsigned char *smem, int base, int rows, int r, int g, u32x4 &b0,
                                             u32x4 &b1)
 {
     const u32x4 *t = (const u32x4 *)(smem + base) + r;
@@ -391,7 +456,7 @@ __device__ __forceinline__ void load_target(const unsigned char *smem, long base
 // Rows of a three-plane table: the FP32 values are the exact sums of their
 // pieces.
 template <bool K4>
-__device__ __forceinline__ void put_row(unsigned char *smem, long base, int rows, int r, const float (&v)[K4 ? 4 : 8])
+__device__ __forceinline__ void put_row(unsigned char *smem, int base, int rows, int r, const float (&v)[K4 ? 4 : 8])
 {
     constexpr int W = K4 ? 2 : 4;
     uint32_t h[W], m[W], l[W];
@@ -403,28 +468,28 @@ __device__ __forceinline__ void put_row(unsigned char *smem, long base, int rows
         l[q] = p.l;
     }
     if constexpr (K4) {
-        *(u32x2 *)(smem + base + (long)r * 8) = u32x2{h[0], h[1]};
-        *(u32x2 *)(smem + base + (long)(rows + r) * 8) = u32x2{m[0], m[1]};
-        *(u32x2 *)(smem + base + (long)(2 * rows + r) * 8) = u32x2{l[0], l[1]};
+        *(u32x2 *)(smem + base + r * 8) = u32x2{h[0], h[1]};
+        *(u32x2 *)(smem + base + (rows + r) * 8) = u32x2{m[0], m[1]};
+        *(u32x2 *)(smem + base + (2 * rows + r) * 8) = u32x2{l[0], l[1]};
     } else {
-        *(u32x4 *)(smem + base + (long)r * 16) = u32x4{h[0], h[1], h[2], h[3]};
-        *(u32x4 *)(smem + base + (long)(rows + r) * 16) = u32x4{m[0], m[1], m[2], m[3]};
-        *(u32x4 *)(smem + base + (long)(2 * rows + r) * 16) = u32x4{l[0], l[1], l[2], l[3]};
+        *(u32x4 *)(smem + base + r * 16) = u32x4{h[0], h[1], h[2], h[3]};
+        *(u32x4 *)(smem + base + (rows + r) * 16) = u32x4{m[0], m[1], m[2], m[3]};
+        *(u32x4 *)(smem + base + (2 * rows + r) * 16) = u32x4{l[0], l[1], l[2], l[3]};
     }
 }
 template <bool K4> struct PieceRow {
     static constexpr int W = K4 ? 2 : 4;
     uint32_t h[W], m[W], l[W];
-    __device__ __forceinline__ void load(const unsigned char *smem, long base, int rows, int r)
+    __device__ __forceinline__ void load(const unsigned char *smem, int base, int rows, int r)
     {
 #pragma unroll
         for (int p = 0; p < 3; ++p) {
             uint32_t *d = p == 0 ? h : p == 1 ? m : l;
             if constexpr (K4) {
-                const u32x2 v = *(const u32x2 *)(smem + base + (long)(p * rows + r) * 8);
+                const u32x2 v = *(const u32x2 *)(smem + base + (p * rows + r) * 8);
                 d[0] = v[0]; d[1] = v[1];
             } else {
-                const u32x4 v = *(const u32x4 *)(smem + base + (long)(p * rows + r) * 16);
+                const u32x4 v = *(const u32x4 *)(smem + base + (p * rows + r) * 16);
                 d[0] = v[0]; d[1] = v[1]; d[2] = v[2]; d[3] = v[3];
             }
         }
@@ -436,64 +501,122 @@ template <bool K4> struct PieceRow {
     }
 };
 
-// Sums' table (off_v, off_ms): component c of source s as two f16 pieces, row
-// c and row R + c of its 32-source block, at the position that matches the
-// K-slots of a pair of 16x16 tiles: lane group g holds sources 4 g + r of the
-// first tile in slots r and of the second in slots 4 + r.
-template <bool K4>
-__device__ __forceinline__ void put_sum_row(unsigned char *smem, long base, int s, const float (&v)[K4 ? 4 : 8])
+// Sums' table (off_v, off_ms): the f16 pieces h, m, l of the D components and
+// the one of source s, in the rows of its 32-source block, at the position that
+// matches the K-slots of a pair of 16x16 tiles: lane group g holds sources
+// 4 g + r of the first tile in slots r and of the second in slots 4 + r.  Rows:
+//   D <= 3   h, m, l / 2 of four components (the one is component 3); one
+//            MFMA takes them all, its last four rows l / 2 again
+//   D = 4    h, m, l of four components, then the one; one MFMA
+//   above    h, m, l / 2 of eight components (the one is component 7); one
+//            MFMA takes h and m, another l / 2 in either half of its rows
+// (so that every lane reads a row of values and steps from block to block by
+// the same distance).
+template <int D> __device__ __forceinline__ void put_sum_row(unsigned char *smem, int base, int s, const float (&v)[D], float one)
 {
-    constexpr int R = K4 ? 4 : 8;
+    constexpr int C = D <= 4 ? 4 : 8, kOne = D <= 3 ? 3 : D == 4 ? 12 : 7;
     const int pos = ((s >> 2) & 3) * 8 + ((s >> 4) & 1) * 4 + (s & 3);
-    _Float16 *d = (_Float16 *)(smem + base + (long)(s >> 5) * (2 * R * 64)) + pos;
+    _Float16 *d = (_Float16 *)(smem + base + (s >> 5) * (sum_rows(D) * 64)) + pos;
 #pragma unroll
-    for (int c = 0; c < R; ++c) {
-        const _Float16 hi = (_Float16)v[c];
-        d[c * 32] = hi;
-        d[(R + c) * 32] = (_Float16)(v[c] - (float)hi);
+    for (int c = 0; c < D; ++c) {
+        const _Float16 h = (_Float16)v[c];
+        const float r = v[c] - (float)h;
+        const _Float16 m = (_Float16)r;
+        d[c * 32] = h;
+        d[(C + c) * 32] = m;
+        d[(2 * C + c) * 32] = (_Float16)((r - (float)m) * (D == 4 ? 1.f : 0.5f));
     }
+    d[kOne * 32] = (_Float16)one;
+    if constexpr (D != 4) d[(kOne + C) * 32] = d[(kOne + 2 * C) * 32] = (_Float16)0.f;
 }
+// A lane's operands of the table from source block blk on
+template <int D> struct SumRows {
+    uint32_t o0, o1;
+    __device__ __forceinline__ void init(const unsigned char *smem, int table, int blk, int lane)
+    {
+        const int r = lane & 15;
+        const uint32_t at = (uint32_t)(table + (lane >> 4) * 16 + blk * (sum_rows(D) * 64));
+        o0 = lds_address(smem, at + (uint32_t)(D <= 3 && r >= 12 ? r - 4 : r) * 64u);
+        if (D > 4) o1 = lds_address(smem, at + (uint32_t)(16 + (r & 7)) * 64u);
+    }
+    // the operands of this block; on to the next
+    __device__ __forceinline__ void load(u32x4 &a0, u32x4 &a1)
+    {
+        a0 = lds_read<u32x4>(o0);
+        o0 += sum_rows(D) * 64;
+        if constexpr (D > 4) {
+            a1 = lds_read<u32x4>(o1);
+            o1 += sum_rows(D) * 64;
+        }
+    }
+};
 
-// power of two that brings values of magnitude up to `bound` below 2^15, and
-// its inverse
-__device__ __forceinline__ void f16_scale(float bound, float &scale, float &inv)
+// power of two that brings values of magnitude up to `bound` below 2^bits
+__device__ __forceinline__ float f16_scale(float bound, int bits)
 {
     const int e = min(max((int)(__float_as_uint(bound) >> 23) & 0xff, 20), 250);  // 2^(e - 127) <= bound < 2^(e - 126)
-    scale = __uint_as_float((uint32_t)(268 - e) << 23);  // 2^(141 - e): below 2^15
-    inv = __uint_as_float((uint32_t)(e - 14) << 23);
+    return __uint_as_float((uint32_t)(253 + bits - e) << 23);
+}
+// the inverse of a power of two
+__device__ __forceinline__ float inverse_scale(float scale) { return __uint_as_float(0x7f000000u - __float_as_uint(scale)); }
+// whether too many of a wave's `count` values are below 2 (zeros aside)
+__device__ __forceinline__ bool many_tiny(float v, int count)
+{
+    const bool tiny = (__float_as_uint(v) & 0x7fffffffu) - 1u < 0x3fffffffu;
+    return kTinyShare * __builtin_popcountll(__builtin_amdgcn_ballot_w64(tiny)) > count;
 }
 
 // Sum over the lane groups that hold a component's pieces, and a transpose:
 // given O[q] of the four (two) 16-target tiles of a task (register i of lane
-// group g holds row 4 g + i of target 16 q + l % 16), lane l receives the R
-// components of target l (l < 32 with two tiles).
-template <bool K4, int QT>
-__device__ __forceinline__ void collect_rows(const f32x4 (&O)[QT], float (&out)[K4 ? 4 : 8])
+// group g holds row 4 g + i of target 16 q + l % 16), lane l receives the
+// components of target l (l < 32 with two tiles): lo and hi the sums over the
+// even and the odd lane groups.
+template <int QT>
+__device__ __forceinline__ void collect_groups(const float (&o)[QT], float &lo, float &hi)
 {
+    uint32_t u, w;
+    if constexpr (QT == 4) {
+        auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(o[0]), __float_as_uint(o[2]), false, false);
+        auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(o[1]), __float_as_uint(o[3]), false, false);
+        // lane groups 0, 1: target tile 0 (1), rows g and g + 2; groups 2, 3: tile 2 (3)
+        u = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
+        w = __float_as_uint(__uint_as_float(b[0]) + __uint_as_float(b[1]));
+    } else {
+        auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(o[0]), __float_as_uint(o[1]), false, false);
+        // lane groups 0, 1: target tile 0; groups 2, 3: tile 1, brought below
+        u = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
+        auto b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        u = b[0];
+        w = b[1];
+    }
+    auto c = __builtin_amdgcn_permlane16_swap(u, w, false, false);
+    lo = __uint_as_float(c[0]);
+    hi = __uint_as_float(c[1]);
+}
+template <int D, int QT>
+__device__ __forceinline__ void collect_rows(const f32x4 (&O)[QT], float (&out)[D <= 3 ? 4 : 8])
+{
+    float o[QT], lo, hi;
+    if constexpr (D == 4) {
+        // the one's sums: register 0 of the last lane group
+        const bool last = (threadIdx.x & 63) >= 48;
+#pragma unroll
+        for (int q = 0; q < QT; ++q) o[q] = last ? O[q][0] : 0.f;
+        collect_groups<QT>(o, lo, hi);
+        out[7] = hi;
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        uint32_t u, w;
-        if constexpr (QT == 4) {
-            auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(O[0][i]), __float_as_uint(O[2][i]), false, false);
-            auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(O[1][i]), __float_as_uint(O[3][i]), false, false);
-            // lane groups 0, 1: target tile 0 (1), rows g and g + 2; groups 2, 3: tile 2 (3)
-            u = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
-            w = __float_as_uint(__uint_as_float(b[0]) + __uint_as_float(b[1]));
+#pragma unroll
+        for (int q = 0; q < QT; ++q)
+            o[q] = D == 4 && (threadIdx.x & 63) >= 48 ? 0.f : O[q][i];
+        collect_groups<QT>(o, lo, hi);
+        if constexpr (D <= 4) {
+            out[i] = lo + hi;
+            if constexpr (D == 4) if (i < 3) out[4 + i] = 0.f;
         } else {
-            auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(O[0][i]), __float_as_uint(O[1][i]), false, false);
-            // lane groups 0, 1: target tile 0; groups 2, 3: tile 1, brought below
-            u = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
-            auto b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-            u = b[0];
-            w = b[1];
-        }
-        auto c = __builtin_amdgcn_permlane16_swap(u, w, false, false);
-        if constexpr (K4) {
-            // rows 8..15 repeat rows 0..7
-            out[i] = 0.5f * (__uint_as_float(c[0]) + __uint_as_float(c[1]));
-        } else {
-            out[i] = __uint_as_float(c[0]);
-            out[4 + i] = __uint_as_float(c[1]);
+            out[i] = lo;
+            out[4 + i] = hi;
         }
     }
 }
@@ -508,19 +631,19 @@ __device__ __forceinline__ void collect_rows(const f32x4 (&O)[QT], float (&out)[
 // one the walk took twice the LDS reads, which bounded it.
 template <bool K4> struct BlockWalker {
     const unsigned char *smem;
-    long base;
+    int base;
     int rows, nb, g, col, I, K, left;
     SourceRows<K4> src;
 
     // blocks [p0, p1) of the list
-    __device__ void start(const unsigned char *lds, long x_base, int npad, long ones, int lane, int p0, int p1)
+    __device__ void start(const unsigned char *lds, int x_base, int npad, int ones, int lane, int p0, int p1)
     {
         smem = lds;
         base = x_base;
         rows = npad;
         g = lane >> 4;
         col = lane & 15;
-        src.init(x_base, npad, ones, g, col);
+        src.init(lds, x_base, npad, ones, g, col);
         nb = npad / 32;
         left = p1 - p0;
         I = 0;
@@ -572,8 +695,8 @@ template <bool K4> struct BlockWalker {
             // the next block's operands are read one block ahead (the last
             // reads run past the table into the one behind it, unused)
             u32x4 a00, a01, a10, a11;
-            at.load(smem, 0, a00, a01);
-            at.load(smem, 1, a10, a11);
+            at.load(0, a00, a01);
+            at.load(1, a10, a11);
             for (; K < end; ++K) {
                 f32x4 D[4];
                 D[0] = SourceRows<K4>::dot(a00, a01, b00, b01, diag);
@@ -581,8 +704,8 @@ template <bool K4> struct BlockWalker {
                 D[2] = SourceRows<K4>::dot(a10, a11, b00, b01);
                 D[3] = SourceRows<K4>::dot(a10, a11, b10, b11, diag);
                 at.skip(2);
-                at.load(smem, 0, a00, a01);
-                at.load(smem, 1, a10, a11);
+                at.load(0, a00, a01);
+                at.load(1, a10, a11);
                 diag = all = f32x4{0.f, 0.f, 0.f, 0.f};
                 fn(D);
             }
@@ -930,7 +1053,7 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
     constexpr int QT = SPLIT ? 2 : 4;   // 16-target tiles of a task
     constexpr int kTask = 16 * QT;
     const int npad0 = (n + 63) / 64 * 64;
-    const MfmaLds L(K4, n, np, (int)(blockDim.x >> 6), COOP ? npad0 / G : 0);
+    const MfmaLds L(D, n, np, (int)(blockDim.x >> 6), COOP ? npad0 / G : 0);
     const int npad = L.npad, nppad = L.nppad;
     float *PART = (float *)(smem + L.off_part); // [ns_max][targets][kPart] partial sums of the splits
     // the workgroup's targets: particles [tbase, tbase + ntl) (all of them outside COOP)
@@ -961,6 +1084,12 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
     asm("" : "+s"(neg1));  // see split_f16
 
     if (tid == 0) *(u32x4 *)(smem + L.off_ones) = u32x4{0x3f803f80u, 0x3f80u, 0u, 0u};
+    // red[12] what stands against a table just written (kRescale, kDirect);
+    // [16 + c] largest |2 mh_c|, [24 + c] largest |v_c| where scales are set.
+    // The scales themselves: redf[32 + c] of 2 mh, redf[40 + c] of v.
+    constexpr uint32_t kRescale = 1, kDirect = 2;
+    if (tid >= 12 && tid < 32) red[tid] = 0;
+    const float *const ms_scale = redf + 32, *const v_scale = redf + 40;
     for (int o = tid; o < m.obs_dim; o += nt) sz[o] = a.z[(long)b * a.z_stride + o];
     static_assert(kMaxObs <= kWave, "one lane per element of an observation");
     const bool on = lane < m.n_obs && (!a.mask || a.mask[(long)b * a.mask_stride + lane]);
@@ -996,7 +1125,9 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
     // transition means, centred and log2-scaled: row j = [2 mh_j, c'_j] with
     // c'_j = log2 w_j - |mh_j|^2; pad sources and those of weight zero get a
     // logit that counts for nothing
-    float mmax = 0.f;
+    float mmax[D];
+#pragma unroll
+    for (int c = 0; c < D; ++c) mmax[c] = 0.f;
     for (int j = tid; j < nppad; j += nt) {
         float row[NC];
 #pragma unroll
@@ -1012,7 +1143,7 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
             for (int c = 0; c < D; ++c) {
                 const float mh = (mu[c] - ref[c]) * rs[c];
                 row[c] = 2.f * mh;
-                mmax = fmax_(mmax, fabsf(row[c]));
+                mmax[c] = fmax_(mmax[c], fabsf(row[c]));
                 nrm += mh * mh;
             }
             const float lw = a.log_w ? a.log_w[(long)b * a.log_w_stride + j] : -R::log_((float)np);
@@ -1021,26 +1152,36 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
         }
         put_row<K4>(smem, L.off_vt, nppad, j, row);
     }
-    // scale of the f16 pieces of 2 mh
-    mmax = wave_max_abs(mmax);
-    if (lane == 0) redf[wave] = mmax;
+    // scales of the f16 pieces, from the largest magnitude of each component of
+    // a wave's values
+    auto note_max = [&](const float (&v)[D], int slot) {
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+            const float mx = wave_max_abs(fabsf(v[c]));
+            if (lane == 0) atomicMax(&red[slot + c], __float_as_uint(mx));
+        }
+    };
+    note_max(mmax, 16);
     __syncthreads();
-    mmax = wave_max_abs((lane & 15) < nwaves ? redf[lane & 15] : 0.f);
-    float ms_scale, ms_inv;
-    f16_scale(uniform(mmax), ms_scale, ms_inv);
+    if (tid < D) redf[32 + tid] = f16_scale(__uint_as_float(red[16 + tid]), 15);
+    __syncthreads();
     // the sums' table of the transition means, from its rows
-    auto build_ms = [&]() {
+    auto build_ms = [&](bool first) {
         for (int j = tid; j < nppad; j += nt) {
             PieceRow<K4> p;
             p.load(smem, L.off_vt, nppad, j);
-            float v[NC];
+            float v[D];
+            bool tiny = false;
 #pragma unroll
-            for (int c = 0; c < kLast; ++c) v[c] = p.at(c) * ms_scale;
-            v[kLast] = 1.f;
-            put_sum_row<K4>(smem, L.off_ms, j, v);
+            for (int c = 0; c < D; ++c) {
+                v[c] = p.at(c) * ms_scale[c];
+                tiny |= first && many_tiny(v[c], min(kWave, np - (j & ~(kWave - 1))));  // (pads are zero)
+            }
+            if (tiny) red[12] = kDirect;
+            put_sum_row<D>(smem, L.off_ms, j, v, 1.f);
         }
     };
-    build_ms();
+    build_ms(true);
     const int ntl = L.ntasks * kTask;
     // score operand of particle i (at its place in a row), where it is one of
     // the workgroup's targets and they are kept
@@ -1081,6 +1222,7 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
     }
     if (tid < 2) red[10 + tid] = 0;
     __syncthreads();
+    const bool score_on_valu = __builtin_amdgcn_readfirstlane((int)red[12]) != 0;
 
     // mean of the centred transition means (literal score reading)
     float mbar_all[D];
@@ -1104,6 +1246,8 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
         }
     }
 
+    __syncthreads();
+    if (tid == 0) red[12] = 0;  // (read above; used again past the next barrier)
     const int ntasks = L.ntasks;   // target tasks of this workgroup
     // every workgroup of the sequence has read its inputs before any writes
     // its outputs (the x array may hold the initial particles)
@@ -1116,6 +1260,7 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
     // lane, kept from one iteration to the next
     float negref[TS];
     bool have_ref = false;
+    bool have_scale = false;  // of v
 
     // This thread's index, opaque to the compiler: addresses derived from it in
     // a pass are formed there instead of being kept (and spilled) across all
@@ -1131,7 +1276,6 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
         asm volatile("" : "+s"(q));
         return ((const StepArgs<float> *)q)->m;
     };
-    constexpr uint32_t kSumBlock = 2 * NC * 64;
     // O[q] = the sums over the source blocks [blk0, blk1) of 2^(exponent) times
     // the rows of a sums' table (at byte `table`), for the 16-target
     // tiles of a task (operands b0, b1).  A wave's instructions issue in order
@@ -1140,45 +1284,46 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
     // matrix cores form the exponents of the tile after it and the sums of the
     // tile before it, one MFMA every four vector instructions; nothing waits
     // for a result of its own step.
-    auto weighted_sums = [&](const SourceRows<K4> &src, long table, const u32x4 (&b0)[QT],
+    auto weighted_sums = [&](const SourceRows<K4> &src, int table, const u32x4 (&b0)[QT],
                              const u32x4 (&b1)[QT], int blk0, int blk1, f32x4 (&O)[QT]) {
         constexpr int kQ = QT;
         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-        // operands of the sums' table: row (component piece) l % 16, K-slots of
-        // group l / 16
-        const int l = fresh_tid() & 63;
-        const uint32_t sum_off = (uint32_t)((l & (K4 ? 7 : 15)) * 64 + (l >> 4) * 16);
-        u32x4 a00, a01, a10, a11, eh = {0u, 0u, 0u, 0u}, el = {0u, 0u, 0u, 0u};
-        src.load(smem, 2 * blk0, a00, a01);
-        src.load(smem, 2 * blk0 + 1, a10, a11);
-        u32x4 av = *(const u32x4 *)(smem + table + sum_off + (uint32_t)blk0 * kSumBlock);
+        SumRows<D> sums;
+        sums.init(smem, table, blk0, fresh_tid() & 63);
+        u32x4 a00, a01, a10, a11, eh = {0u, 0u, 0u, 0u}, el = eh, av = eh, aw = eh;
+        SourceRows<K4> at = src;
+        at.skip(2 * blk0);
+        at.load(0, a00, a01);
+        at.load(1, a10, a11);
         f32x4 T0 = SourceRows<K4>::dot(a00, a01, b0[0], b1[0]), T1 = SourceRows<K4>::dot(a10, a11, b0[0], b1[0]);
 #pragma unroll
         for (int q = 0; q < kQ; ++q) O[q] = zero;
         for (int blk = blk0; blk < blk1; ++blk) {
-            const int next = min(blk + 1, blk1 - 1);
 #pragma unroll
             for (int q = 0; q < kQ; ++q) {
                 const int qn = (q + 1) % kQ, qp = (q + kQ - 1) % kQ;
-                f32x4 N0, N1;
+                f32x4 N0, N1, S;
                 if (K4) {
                     N0 = mfma_bf16(a00, b0[qn], zero);
-                    O[qp] = mfma_f16(av, eh, O[qp]);
+                    S = mfma_f16(av, el, zero);
                     N1 = mfma_bf16(a10, b0[qn], zero);
-                    O[qp] = mfma_f16(av, el, O[qp]);
+                    S = mfma_f16(av, eh, S);
                 } else {
                     N0 = mfma_bf16(a01, b1[qn], zero);
-                    O[qp] = mfma_f16(av, eh, O[qp]);
+                    S = mfma_f16(av, el, zero);
                     N1 = mfma_bf16(a11, b1[qn], zero);
-                    O[qp] = mfma_f16(av, el, O[qp]);
+                    if (D > 4) S = mfma_f16(aw, eh, S);
                     N0 = mfma_bf16(a00, b0[qn], N0);
+                    S = mfma_f16(av, eh, S);
                     N1 = mfma_bf16(a10, b0[qn], N1);
                 }
-                if (q == 0) av = *(const u32x4 *)(smem + table + sum_off + (uint32_t)blk * kSumBlock);
+                if (q == 0) sums.load(av, aw);
                 if (q == kQ - 2) {
                     // the exponents of the next block start at the next step
-                    src.load(smem, 2 * next, a00, a01);
-                    src.load(smem, 2 * next + 1, a10, a11);
+                    // (past the last one: into the table behind, unused)
+                    at.skip(2);
+                    at.load(0, a00, a01);
+                    at.load(1, a10, a11);
                 }
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
@@ -1190,12 +1335,14 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
                 split_f16(T0[2], T0[3], neg1, hi, lo); eh[1] = hi; el[1] = lo;
                 split_f16(T1[0], T1[1], neg1, hi, lo); eh[2] = hi; el[2] = lo;
                 split_f16(T1[2], T1[3], neg1, hi, lo); eh[3] = hi; el[3] = lo;
+                O[qp] += S;
                 T0 = N0;
                 T1 = N1;
             }
         }
-        O[kQ - 1] = mfma_f16(av, eh, O[kQ - 1]);
-        O[kQ - 1] = mfma_f16(av, el, O[kQ - 1]);
+        f32x4 S = mfma_f16(av, el, zero);
+        if (D > 4) S = mfma_f16(aw, eh, S);
+        O[kQ - 1] += mfma_f16(av, eh, S);
     };
 
     // components of the target operands: [x_k in log2 units, 1] of the scores,
@@ -1208,7 +1355,7 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
         uint32_t ph[NC / 2], pm[NC / 2], pl[NC / 2];
 #pragma unroll
         for (int w = 0; w < NC / 2; ++w) {
-            const Pieces3 s = split3(v[2 * w], v[2 * w + 1]);
+            const Pieces3 s = w == NC / 2 - 1 ? split3_last(v[2 * w], v[2 * w + 1]) : split3(v[2 * w], v[2 * w + 1]);
             ph[w] = s.h; pm[w] = s.m; pl[w] = s.l;
         }
         target_operand<K4>(ph, pm, pl, cst, g, b0, b1);
@@ -1245,17 +1392,17 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
             for (int c = 0; c < D; ++c) acc[c] = acc[c] * sf + e * p.at(c);
         }
 #pragma unroll
-        for (int c = 0; c < NC; ++c) os[c] = c == kLast ? sum : c < D ? acc[c < D ? c : 0] * ms_scale : 0.f;
+        for (int c = 0; c < NC; ++c) os[c] = c == kLast ? sum : c < D ? acc[c < D ? c : 0] * ms_scale[c < D ? c : 0] : 0.f;
         nref = mx > 0.1f * kNoSource ? -mx : 0.f;
     };
-    // os[c] = sum_j e_kj [2 mh_j, 1] (times ms_scale but for the last) over the
+    // os[c] = sum_j e_kj [2 mh_j, 1] (times ms_scale[c] but for the last) over the
     // source blocks [blk0, blk1) for this lane's particle kbase + lane,
     // e_kj = exp2(logit_kj - sref)
     auto score_sums = [&](int kbase, int blk0, int blk1, float &nref, float (&os)[NC], float &sref) {
         const int lane = fresh_tid() & 63, g = lane >> 4, col = lane & 15;
         u32x4 b0[QT], b1[QT];
         SourceRows<K4> src;
-        src.init(L.off_vt, nppad, L.off_ones, g, col);
+        src.init(smem, L.off_vt, nppad, L.off_ones, g, col);
 #pragma unroll
         for (int q = 0; q < QT; ++q) {
             const float cst = have_ref ? __shfl(nref, 16 * q + col, kWave) : 0.f;
@@ -1276,6 +1423,10 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
         }
         bool from_max = !have_ref;
         for (;;) {
+            if (score_on_valu) {
+                score_direct(kbase, blk0, blk1, nref, os);
+                break;
+            }
             if (from_max) {
                 // references from the largest logits of the sources
                 float mx[QT];
@@ -1286,7 +1437,7 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
                 }
                 for (int jt = 2 * blk0; jt < 2 * blk1; ++jt) {
                     u32x4 a0, a1;
-                    src.load(smem, jt, a0, a1);
+                    src.load(jt, a0, a1);
 #pragma unroll
                     for (int q = 0; q < QT; ++q) {
                         const f32x4 T = SourceRows<K4>::dot(a0, a1, b0[q], b1[q]);
@@ -1304,7 +1455,7 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
             }
             f32x4 O[QT];
             weighted_sums(src, L.off_ms, b0, b1, blk0, blk1, O);
-            collect_rows<K4, QT>(O, os);
+            collect_rows<D, QT>(O, os);
             const float s = os[kLast];
             const bool ok = lane >= kTask || (s >= kRefMinSum && s < 1e30f) || (nref == 0.f && s == 0.f);
             if (!__builtin_amdgcn_ballot_w64(!ok)) break;
@@ -1329,10 +1480,10 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
     auto score_transition = [&](const float *os, const float (&xt)[D], float (&s)[D]) {
         const DevModel<float> &m = fresh_model();
         if (a.trans_mode == 0) {
-            const float inv_sum = ms_inv / os[kLast];
+            const float inv_sum = 1.f / os[kLast];
 #pragma unroll
             for (int c = 0; c < D; ++c) {
-                const float mb = os[c] * inv_sum * half_irs[c];
+                const float mb = os[c] * inv_sum * (inverse_scale(ms_scale[c]) * half_irs[c]);
                 s[c] -= (xt[c] - mb) * m.inv_q[c];
             }
         } else {
@@ -1344,11 +1495,11 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
     // sums rebased to their largest reference)
     auto merge_part = [&](int kl, int ns, bool softmax, float (&os)[NC]) {
         float mx = -inf;
-        for (int sp = 0; softmax && sp < ns; ++sp) mx = fmax_(mx, PART[((long)sp * ntl + kl) * kPart + NC]);
+        for (int sp = 0; softmax && sp < ns; ++sp) mx = fmax_(mx, PART[(sp * ntl + kl) * kPart + NC]);
 #pragma unroll
         for (int c = 0; c < NC; ++c) os[c] = 0.f;
         for (int sp = 0; sp < ns; ++sp) {
-            const float *pp = PART + ((long)sp * ntl + kl) * kPart;
+            const float *pp = PART + (sp * ntl + kl) * kPart;
             const float w = softmax ? R::exp2_(pp[NC] - mx) : 1.f;
 #pragma unroll
             for (int c = 0; c < NC; ++c) os[c] += pp[c] * w;
@@ -1522,14 +1673,6 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
         const bool need_median = (a.bw_mode == 0 || it == 0) && M > 0;
         const bool window = need_median && tracker.plan(M, cap);
         float srow[TS][D];        // scores of this thread's particles
-        float smax = 0.f, xmax = 0.f;  // largest |s|, |x| of its particles
-        auto note_max = [&](const float (&s)[D], const float (&xt)[D]) {
-#pragma unroll
-            for (int c = 0; c < D; ++c) {
-                smax = fmax_(smax, fabsf(s[c]));
-                xmax = fmax_(xmax, fabsf(xt[c]));
-            }
-        };
 
         // (1) scores
         float os[NC], sref = 0.f;
@@ -1552,7 +1695,6 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
                     target_x(k, xt);
                     score_grad(xt, srow[ts]);
                     score_transition(os, xt, srow[ts]);
-                    note_max(srow[ts], xt);
                 }
             }
         }
@@ -1566,7 +1708,7 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
         if constexpr (SPLIT) {
             // partial sums of the splits to LDS
             if (a.trans_mode == 0 && sp < L.ns_sc && lane < kTask) {
-                float *pp = PART + ((long)sp * ntl + wave % ntasks * kTask + lane) * kPart;
+                float *pp = PART + (sp * ntl + wave % ntasks * kTask + lane) * kPart;
 #pragma unroll
                 for (int c = 0; c < NC; ++c) pp[c] = os[c];
                 pp[NC] = sref;
@@ -1585,7 +1727,6 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
                 target_x(tbase + il, xt);
                 score_grad(xt, srow[0]);
                 score_transition(os, xt, srow[0]);
-                if (!COOP) note_max(srow[0], xt);
             }
         }
         if constexpr (COOP) {
@@ -1600,28 +1741,14 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
             coop_barrier(cctr, ++epoch * (uint32_t)G, a.status);
             // every score row: thread tid takes particle tid
             if (tid < n) {
-                float xt[D];
-                PieceRow<K4> p;
-                p.load(smem, L.off_x, npad, tid);
 #pragma unroll
-                for (int c = 0; c < D; ++c) {
-                    srow[0][c] = cS[(long)tid * 8 + c];
-                    xt[c] = p.at(c);
-                }
-                note_max(srow[0], xt);
+                for (int c = 0; c < D; ++c) srow[0][c] = cS[(long)tid * 8 + c];
             }
             if (window) {
                 collect_window();
                 found = in_window();
                 if (found && red[10] <= kSelectMax && wave == nwaves - 1) select_by_wave();
             }
-        }
-        // the largest |s| and |x| bound the Stein sums' operands
-        smax = wave_max_abs(smax);
-        xmax = wave_max_abs(xmax);
-        if (lane == 0) {
-            redf[32 + wave] = smax;
-            redf[48 + wave] = xmax;
         }
         __syncthreads();
         if (need_median || it == 0) {
@@ -1646,25 +1773,86 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
         // rows, so one contraction of kappa with [v, 1] gives both sums).
         const float twob = 2.f * beta;
         const float c2 = 2.f / h;
-        smax = wave_max_abs((lane & 15) < nwaves ? redf[32 + (lane & 15)] : 0.f);
-        xmax = wave_max_abs((lane & 15) < nwaves ? redf[48 + (lane & 15)] : 0.f);
-        // B = [2 beta x_i, -2 beta], constant 14 - beta n_i: a tile holds the
-        // exponent -beta |x_k - x_i|^2 + 14 of kappa
+        // B = [2 beta x_i, -2 beta], constant kKapShift - beta n_i: a tile holds the
+        // exponent kKapShift - beta |x_k - x_i|^2
         auto stein_target = [&](const PieceRow<K4> &p, float (&v)[NC], float &cst) {
 #pragma unroll
             for (int c = 0; c < NC; ++c) v[c] = c == kLast ? -twob : c < D ? twob * p.at(c) : 0.f;
             const float half = p.at(kLast);
             cst = kKapShift - (half < 0.5f * kPadHalfNorm ? twob * half : 0.f);
         };
-        float v_scale, v_inv;
-        f16_scale(uniform(smax + c2 * xmax), v_scale, v_inv);
-        v_inv *= inv_n * 6.103515625e-05f;  // 2^-14 of kappa
-        const float k_inv = inv_n * 6.103515625e-05f;
-        // kappa from differences (kMaxProductExponent); |x|^2 <= D max |x_c|^2.
-        // The table then holds the score rows in FP32.
-        const bool direct = !(uniform(beta * (float)D * xmax * xmax) <= kMaxProductExponent);
+        const float k_inv = inv_n / kKapScale;
+        // What the matrix cores cannot take (kMaxProductExponent, kTinyShare): the
+        // table holds the score rows in FP32, and differences are formed.
+        bool direct = false;
         float *const srows = (float *)(smem + L.off_v);
-        if (direct) v_inv = inv_n;
+        auto put_scores = [&]() {
+#pragma unroll
+            for (int ts = 0; ts < TS; ++ts) {
+                const int k = fresh_tid() + ts * nt;
+                if (k >= npad) break;
+#pragma unroll
+                for (int c = 0; c < D; ++c) srows[k * D + c] = k < n ? srow[ts][c] : 0.f;
+            }
+        };
+        // v of this thread's ts-th particle k
+        auto vector = [&](int ts, int k, const PieceRow<K4> &p, float (&w)[D]) {
+#pragma unroll
+            for (int c = 0; c < D; ++c) w[c] = k < n ? srow[ts][c] - c2 * p.at(c) : 0.f;
+        };
+        // scales from the largest values (a block-wide barrier before and after)
+        auto set_scales = [&]() {
+            __syncthreads();
+            float mx[D];
+#pragma unroll
+            for (int c = 0; c < D; ++c) mx[c] = 0.f;
+#pragma unroll
+            for (int ts = 0; ts < TS; ++ts) {
+                const int k = fresh_tid() + ts * nt;
+                if (k >= n) break;
+                PieceRow<K4> p;
+                float w[D];
+                p.load(smem, L.off_x, npad, k);
+                vector(ts, k, p, w);
+#pragma unroll
+                for (int c = 0; c < D; ++c) mx[c] = fabsf(w[c]) > mx[c] || w[c] != w[c] ? fabsf(w[c]) : mx[c];
+            }
+            note_max(mx, 24);
+            __syncthreads();
+            if (tid < D) {
+                redf[40 + tid] = f16_scale(__uint_as_float(red[24 + tid]), 14);
+                red[24 + tid] = 0;
+            }
+            if (tid == 0) red[12] = 0;
+            have_scale = true;
+            __syncthreads();
+        };
+        if (!have_scale) set_scales();
+        // the table and what stands against it
+        auto put_vectors = [&]() {
+#pragma unroll
+            for (int ts = 0; ts < TS; ++ts) {
+                const int k = fresh_tid() + ts * nt;
+                if (k >= npad) break;
+                PieceRow<K4> p;
+                float w[D];
+                p.load(smem, L.off_x, npad, k);
+                vector(ts, k, p, w);
+                bool off = false, tiny = false;
+#pragma unroll
+                for (int c = 0; c < D; ++c) {
+                    w[c] *= v_scale[c];
+                    off |= !(fabsf(w[c]) < kScaledMax);
+                    tiny |= many_tiny(w[c], min(kWave, n - (k & ~(kWave - 1))));
+                }
+                const bool far = k < n && !(twob * p.at(kLast) <= kMaxProductExponent);
+                const uint32_t bad = (tiny || __builtin_amdgcn_ballot_w64(off) ? kRescale : 0u) |
+                                     (__builtin_amdgcn_ballot_w64(far) ? kDirect : 0u);
+                if (bad) atomicOr(&red[12], bad);
+                put_sum_row<D>(smem, L.off_v, k, w, k < n ? 1.f : 0.f);
+            }
+        };
+        put_vectors();
         // (a workgroup that splits has two threads or more per particle: the
         // second puts the target operands)
         constexpr bool kOther = SPLIT && !COOP;
@@ -1672,36 +1860,32 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
         for (int ts = 0; ts < TS; ++ts) {
             const int k = fresh_tid() + ts * nt;
             PieceRow<K4> p;
-            float v[NC];
-            if (kOther && L.b_table && k >= npad && k < 2 * npad) {
-                float cst;
-                p.load(smem, L.off_x, npad, k - npad);
+            float v[NC], cst;
+            const int r = kOther ? k - npad : k;
+            if (SPLIT && L.b_table && r >= tbase && r < tbase + ntl) {
+                p.load(smem, L.off_x, npad, r);
                 stein_target(p, v, cst);
-                put_target<K4>(smem, L.off_b, ntl, k - npad, v, cst);
-            }
-            if (k >= npad) break;
-            if (direct) {
-#pragma unroll
-                for (int c = 0; c < D; ++c) srows[k * D + c] = k < n ? srow[ts][c] : 0.f;
-                continue;
-            }
-            p.load(smem, L.off_x, npad, k);
-#pragma unroll
-            for (int c = 0; c < NC; ++c) v[c] = 0.f;
-            if (k < n) {
-#pragma unroll
-                for (int c = 0; c < D; ++c) v[c] = (srow[ts][c] - c2 * p.at(c)) * v_scale;
-                v[kLast] = 1.f;
-            }
-            put_sum_row<K4>(smem, L.off_v, k, v);
-            if (SPLIT && !kOther && L.b_table && k >= tbase && k < tbase + ntl) {
-                float cst;
-                stein_target(p, v, cst);
-                put_target<K4>(smem, L.off_b, ntl, k - tbase, v, cst);
+                put_target<K4>(smem, L.off_b, ntl, r - tbase, v, cst);
             }
         }
         __syncthreads();
         if (tid < 2) red[10 + tid] = 0;  // the next walk's counters (past the last read)
+        uint32_t against = red[12];
+        if (__builtin_amdgcn_readfirstlane((int)against)) {
+            if (!(against & kDirect)) {
+                set_scales();
+                put_vectors();
+                __syncthreads();
+            }
+            if (red[12]) {
+                direct = true;
+                __syncthreads();
+                if (tid == 0) red[12] = 0;
+                have_scale = false;
+                put_scores();
+                __syncthreads();
+            }
+        }
         // sums over the source blocks [blk0, blk1) for the targets of a task
         auto stein_sums = [&](int ibase, int blk0, int blk1, float (&so)[NC]) {
             const int lane = fresh_tid() & 63, g = lane >> 4, col = lane & 15;
@@ -1730,7 +1914,7 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
             u32x4 b0[QT], b1[QT];
             f32x4 O[QT];
             SourceRows<K4> src;
-            src.init(L.off_x, npad, L.off_ones, g, col);
+            src.init(smem, L.off_x, npad, L.off_ones, g, col);
 #pragma unroll
             for (int q = 0; q < QT; ++q) {
                 b1[q] = u32x4{0u, 0u, 0u, 0u};
@@ -1745,7 +1929,7 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
                 }
             }
             weighted_sums(src, L.off_v, b0, b1, blk0, blk1, O);
-            collect_rows<K4, QT>(O, so);
+            collect_rows<D, QT>(O, so);
         };
         // the moved particle and half its squared norm
         auto move = [&](int i, const float *so, float (&xn)[NC]) {
@@ -1757,7 +1941,7 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
 #pragma unroll
             for (int c = 0; c < D; ++c) {
                 const float xc = p.at(c);
-                const float v = xc + a.step * (so[c] * v_inv + c2 * xc * (so[kLast] * k_inv));
+                const float v = xc + a.step * (so[c] * (direct ? inv_n : k_inv * inverse_scale(v_scale[c])) + c2 * xc * (so[kLast] * k_inv));
                 xn[c] = v;
                 nrm += v * v;
             }
@@ -1770,7 +1954,7 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
                 stein_sums(tbase + wave % ntasks * kTask, sp * nb / L.ns_st, (sp + 1) * nb / L.ns_st, so[0]);
             if (COOP) __syncthreads();
             if (sp < L.ns_st && lane < kTask) {
-                float *pp = PART + ((long)sp * ntl + wave % ntasks * kTask + lane) * kPart;
+                float *pp = PART + (sp * ntl + wave % ntasks * kTask + lane) * kPart;
 #pragma unroll
                 for (int c = 0; c < NC; ++c) pp[c] = so[0][c];
             }
@@ -1833,7 +2017,7 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
             }
         }
         // the sums' tables share their region where LDS is short
-        if (L.ms_shared) build_ms();
+        if (L.ms_shared) build_ms(false);
         __syncthreads();
     }
 
@@ -1851,14 +2035,14 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
     }
 
     if (a.do_viterbi) {
-        // rows [mh_j, phi_{t-1}(j)] over the sums' table (dead by now)
-        float *VF = (float *)(smem + L.off_ms);
+        // rows [mh_j, phi_{t-1}(j)] over the sums' tables (dead by now)
+        float *VF = (float *)(smem + L.off_v);
         for (int j = tid; j < np; j += nt) {
             PieceRow<K4> p;
             p.load(smem, L.off_vt, nppad, j);
 #pragma unroll
-            for (int c = 0; c < kLast; ++c) VF[(long)j * NC + c] = 0.5f * p.at(c);
-            VF[(long)j * NC + kLast] = a.phi_prev ? a.phi_prev[(long)b * a.phi_prev_stride + j] : 0.f;
+            for (int c = 0; c < kLast; ++c) VF[j * NC + c] = 0.5f * p.at(c);
+            VF[j * NC + kLast] = a.phi_prev ? a.phi_prev[(long)b * a.phi_prev_stride + j] : 0.f;
         }
         __syncthreads();
         for (int i = i_lo + tid; i < i_hi; i += nt) {
@@ -1876,7 +2060,7 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
             for (int j = 0; j < np; ++j) {
                 float mj[NC];
 #pragma unroll
-                for (int c = 0; c < NC; ++c) mj[c] = VF[(long)j * NC + c];
+                for (int c = 0; c < NC; ++c) mj[c] = VF[j * NC + c];
                 float q2 = 0.f;
 #pragma unroll
                 for (int c = 0; c < D; ++c) {

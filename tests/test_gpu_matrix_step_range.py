@@ -99,3 +99,75 @@ def test_small_bandwidth_on_several_workgroups(n):
         res.append(host(parts).astype(np.float64)[0, 0])
     # FP32 sums in another order, three iterations of a step of 0.05 / n scores
     assert np.linalg.norm(res[0] - res[1]) <= 1e-5 * np.linalg.norm(res[1])
+
+
+@pytest.mark.parametrize("n", [100, 600])
+def test_one_score_far_beyond_the_others(n):
+    """One particle of the growth model at 15,000: its score is 2^30 of the
+    others'.  They move as without it, to FP32 rounding (1e-4 is far above it,
+    and far below what pieces scaled to the largest value would lose, 2^-10)."""
+    announce("matrix step score outlier", n)
+    wl, desc, xp, x, z, mask = _svgd_case("growth1d", n, 90, 72, "f32")
+    x[n // 2] = 15000.0
+    rest = np.arange(n) != n // 2
+    s = O.scores(desc, 2, xp, None, z, mask, x)
+    assert abs(s[n // 2, 0]) > 2.0 ** 26 * np.abs(s[rest]).max()
+    bw_scale = 200.0
+    step = float(x[rest].std() / np.abs(O.stein_phi(x, s, O.bandwidth(x, bw_scale)[0])[rest]).max())
+    xg, h = one_iteration(desc, xp, z, mask, x, step, bw_scale)
+    assert 2.0 / h * 0.5 * np.log2(np.e) * 15000.0 ** 2 < 2.0 ** 20   # (products, not differences)
+    xo = expected(desc, xp, z, mask, x, step, h)
+    err, disp = np.linalg.norm((xg - xo)[rest]), np.linalg.norm((xo - x)[rest])
+    print("h %.3e, error %.3e of the displacement" % (h, err / disp))
+    assert err <= 1e-4 * disp + 4 * EPS * np.linalg.norm(x[rest])
+
+
+@pytest.mark.parametrize("n", [100, 600])
+def test_dimensions_of_unequal_scale(n):
+    """A linear-Gaussian state whose deviations are 1, 2^-16 and 2^-32, so that
+    its scores are 1, 2^16 and 2^32: each dimension moves to FP32 rounding of
+    its own displacement."""
+    announce("matrix step unequal dimensions", n)
+    from paper_2312_08684_amd import scenarios as S
+    sd = np.array([1.0, 2.0 ** -16, 2.0 ** -32])
+    desc = S.lingauss_model(np.eye(3), np.array([[1.0, 0.0, 0.0]]), sd ** 2, [0.5])  # observes the first one
+    rng = np.random.default_rng(7)
+    xp = f32(sd * rng.normal(size=(n, 3)))
+    x = f32(xp[rng.integers(n, size=n)] + sd * rng.normal(size=(n, 3)))
+    z = f32(np.array([0.3]))
+    s = O.scores(desc, 2, xp, None, z, None, x)
+    step = float(0.3 / np.abs(O.stein_phi(x, s, O.bandwidth(x)[0])[:, 0]).max())
+    xg, h = one_iteration(desc, xp, z, None, x, step)
+    xo = expected(desc, xp, z, None, x, step, h)
+    for c in range(3):
+        err, disp = np.linalg.norm((xg - xo)[:, c]), np.linalg.norm((xo - x)[:, c])
+        print("dimension %d: error %.3e of the displacement" % (c, err / disp))
+        assert err <= 1e-4 * disp
+
+
+# the rms error of the direction with FP32 matrix products in place of the
+# operand pieces, on these inputs: 2.7, 2.9; 2.1, 2.2; 3.7, 3.5 (1e-7), and a
+# quarter for the choice of six sets
+@pytest.mark.parametrize("name,n,bound", [("range2d", 64, 3.4e-7), ("range2d", 512, 3.6e-7), ("cv4d", 64, 2.6e-7),
+                                          ("cv4d", 512, 2.8e-7), ("arm7", 64, 4.6e-7), ("arm7", 512, 4.4e-7)])
+def test_direction_is_as_accurate_as_fp32_products(name, n, bound):
+    announce("matrix step accuracy", name, n)
+    from paper_2312_08684_amd import scenarios as S
+    errs = []
+    for seed in range(6):
+        wl = S.make_workload(name, B=1, seed=seed + 100, T=3)
+        desc, rng = wl.model, np.random.default_rng(seed)
+        sd = np.sqrt(desc.q_var[:desc.d])
+        xp = wl.truth[0, 1][None] + 2 * sd * rng.normal(size=(n, desc.d))
+        mu = np.stack([O.transition_mean(desc, 2, v) for v in xp])
+        x = f32(mu[rng.integers(n, size=n)] + sd * rng.normal(size=(n, desc.d)))
+        xp, z, mask = f32(xp), f32(wl.z[0, 1]), None if wl.mask is None else wl.mask[0, 1]
+        # a step so large that the positions' own rounding counts for nothing
+        phi = O.stein_phi(x, O.scores(desc, 2, xp, None, z, mask, x), O.bandwidth(x)[0])
+        step = float(np.float32(1e3 * np.linalg.norm(x) / np.linalg.norm(phi)))
+        xg, h = one_iteration(desc, xp, z, mask, x, step)
+        xo = expected(desc, xp, z, mask, x, step, h)
+        errs.append(np.linalg.norm(xg - xo) / np.linalg.norm(xo - x))
+    rms = float(np.sqrt(np.mean(np.square(errs))))
+    print("rms error of the direction %.2e" % rms)
+    assert rms <= bound
