@@ -203,10 +203,10 @@ bool use_mfma(int d, int n, int n_prev, int step_kernel)
     return fits && n >= kMfmaMinParticles;
 }
 
-template <int KIND, int D, bool SPLIT>
+template <int KIND, int D, bool SPLIT, bool CHUNKED = false>
 smsq_status_t launch_mfma_split(const StepArgs<float> &a, int batch, hipStream_t s)
 {
-    auto fn = &k_step_mfma<KIND, D, SPLIT>;
+    auto fn = &k_step_mfma<KIND, D, SPLIT, CHUNKED>;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [&] { attr_err = allow_big_lds(fn); });
@@ -221,7 +221,14 @@ smsq_status_t launch_mfma_split(const StepArgs<float> &a, int batch, hipStream_t
 template <int KIND, int D>
 smsq_status_t launch_mfma_kd(const StepArgs<float> &a, int batch, hipStream_t s)
 {
-    return MfmaLds(D, a.n, a.n_prev).split ? launch_mfma_split<KIND, D, true>(a, batch, s)
+    const MfmaLds L(D, a.n, a.n_prev);
+    if constexpr (D > 3) {
+        // previous sets too large for LDS at once
+        if (L.chunks > 1)
+            return L.split ? launch_mfma_split<KIND, D, true, true>(a, batch, s)
+                           : launch_mfma_split<KIND, D, false, true>(a, batch, s);
+    }
+    return L.split ? launch_mfma_split<KIND, D, true>(a, batch, s)
                                               : launch_mfma_split<KIND, D, false>(a, batch, s);
 }
 
@@ -1372,7 +1379,10 @@ smsq_status_t smsq_batch_plan_create(const smsq_model_t *models, const smsq_svgd
         if (q.n > kMaxParticles) return SMSQ_ERR_UNSUPPORTED;
         // either workgroup shape, first and later steps
         for (int waves : {8, 16})
-            for (int np : {1, q.n}) lds = std::max(lds, (long)MfmaLds(d.d, q.n, np, waves).total);
+            for (int np : {1, q.n}) {
+                if (MfmaLds(d.d, q.n, np, waves).chunks > 1) return SMSQ_ERR_UNSUPPORTED;
+                lds = std::max(lds, (long)MfmaLds(d.d, q.n, np, waves).total);
+            }
         if (lds > kLdsLimit - kBatchStaticLds) return SMSQ_ERR_UNSUPPORTED;
         max_n = std::max(max_n, q.n);
         T_max = std::max(T_max, q.T);

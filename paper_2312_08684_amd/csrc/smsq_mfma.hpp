@@ -239,70 +239,82 @@ constexpr int kTinyShare = 4;
 // k4 (d <= 3): rows of four components (three coordinates and the last) in
 // place of eight.  Tables, with R = 4 or 8 components:
 //   off_x   three planes [npad][R] bf16, the pieces of [x, |x|^2 / 2]
-//   off_vt  three planes [nppad][R] bf16, the pieces of [2 mh, c']
+//   off_vt  three planes [chunk][R] bf16, the pieces of [2 mh, c']
 //   off_v   [npad / 32][sum_rows][32] f16: pieces of the scaled [v, 1] (Stein sums)
-//   off_ms  [nppad / 32][sum_rows][32] f16: pieces of the scaled [2 mh, 1]
+//   off_ms  [chunk / 32][sum_rows][32] f16: pieces of the scaled [2 mh, 1]
 //   off_b   operands of the workgroup's targets, in turn of the score and the
 //           Stein pass, where several waves share a task (each would form them
 //           again: 250 to 550 instructions a pass, as much as the pass itself
 //           at 256 particles)
 // The two sums' tables share one region where LDS is short (1024 particles of
-// d >= 4): the transition one is then rebuilt each iteration.
+// d >= 4): the transition one is then rebuilt each iteration.  Previous sets of
+// d >= 4 that are too large even so (beyond 1088 particles of the arm and 1280 of
+// the clutter model after 1024, 1376 and 1632 after 64; FP32 rows held 1376 and
+// 2000) are taken in `chunks` of `chunk` sources, whose tables every iteration
+// forms again from the previous particles (CHUNKED).
 __host__ __device__ constexpr int sum_rows(int d) { return d <= 3 ? 12 : d == 4 ? 13 : 24; }
 struct MfmaLds {
     int off_x, off_vt, off_v, off_ms, off_b, off_win, off_z, off_red, off_ones, off_part, total;
-    int npad, nppad, nwaves, task, ntasks, ns_sc, ns_st, ns_max, win_cap;
+    int npad, nwaves, task, ntasks, ns_sc, ns_st, ns_max, win_cap, chunk, chunks;
     bool split, ms_shared, b_table;
-    __host__ __device__ MfmaLds(int d, int n, int n_prev, int waves = kMaxWaves, int targets_local = 0)
+    __host__ __device__ MfmaLds(int d, int n, int n_prev, int waves = kMaxWaves, int targets_local = 0,
+                                int max_chunks = kMaxChunks)
     {
         const bool k4 = d <= 3;
         npad = (n + 63) / 64 * 64;
-        nppad = (n_prev + 31) / 32 * 32;
         const int targets = targets_local > 0 ? targets_local : npad;
         split = targets / 32 <= waves;
         task = split ? 32 : 64;
         ntasks = targets / task;
-        ns_sc = ns_st = ns_max = 1;
-        nwaves = waves;
-        if (split) {
-            const int cap = waves / ntasks;
-            ns_sc = cap < nppad / 32 ? cap : nppad / 32;
-            ns_st = cap < npad / 32 ? cap : npad / 32;
-            ns_max = ns_sc > ns_st ? ns_sc : ns_st;
-            // (from 256 particles on the idle waves take part in the median's pass)
-            if (npad < 256) nwaves = ntasks * ns_max;
-        }
         const int row = k4 ? 8 : 16;  // bytes of a table row
-        // partial sums of the splits: [ns_max][targets][R + 1] floats
-        const int part = split ? (int)align16(ns_max * targets * (k4 ? 5 : 9) * 4) : 0;
-        // the multi-workgroup mode keeps them over the sums' tables
+        // the multi-workgroup mode keeps the partial sums over the sums' tables
         const bool alias = targets_local > 0;
-        const int vb = npad * 2 * sum_rows(d), mb = nppad * 2 * sum_rows(d);
-        // (also the rows [mh, phi] of the forward recursion, in FP32)
-        const int rows = nppad * (k4 ? 16 : 32);
-        // target operands: four planes (k4: three) of 16 bytes per target
-        const int bb = targets * (k4 ? 48 : 64);
-        const int fixed = 3 * row * (npad + nppad) + 128 + 512 + 16 + (alias ? 0 : part) + 1024;
-        // what fits, in the order of what it saves: target operands in a table
-        // (several waves share each task), the sums' tables apart (else the
-        // transition one is rebuilt each iteration), a window buffer of 4096
-        // values (else 2048; also the histogram of a range or radix pass)
-        int sums = 0;
-        for (int choice = 0; choice < 8; ++choice) {
-            b_table = !(choice & 4);
-            ms_shared = alias || (choice & 2);
-            win_cap = alias || (choice & 1) ? 2048 : 4096;
-            if (b_table && !split) continue;
-            sums = ms_shared ? (vb > mb ? vb : mb) : vb + mb;
-            if (alias && sums < part) sums = part;
-            if (sums < rows) sums = rows;
-            if (fixed + sums + (b_table ? bb : 0) + 4 * win_cap <= kMfmaLdsBytes) break;
+        const int sources = (n_prev + 31) / 32;  // blocks of them
+        int sums = 0, part = 0, bb = 0;
+        bool fits = false;
+        for (chunks = 1; !fits; ++chunks) {
+            chunk = (sources + chunks - 1) / chunks * 32;
+            ns_sc = ns_st = ns_max = 1;
+            nwaves = waves;
+            if (split) {
+                const int cap = waves / ntasks;
+                ns_sc = cap < chunk / 32 ? cap : chunk / 32;
+                ns_st = cap < npad / 32 ? cap : npad / 32;
+                ns_max = ns_sc > ns_st ? ns_sc : ns_st;
+                // (from 256 particles on the idle waves take part in the median's pass)
+                if (npad < 256) nwaves = ntasks * ns_max;
+            }
+            // partial sums of the splits: [ns_max][targets][R + 1] floats
+            part = split ? (int)align16(ns_max * targets * (k4 ? 5 : 9) * 4) : 0;
+            const int vb = npad * 2 * sum_rows(d), mb = chunk * 2 * sum_rows(d);
+            // (also the rows [mh, phi] of the forward recursion, in FP32; in
+            // chunks from off_vt on)
+            const int rows = sources * 32 * (k4 ? 16 : 32) - (chunks > 1 ? 3 * row * chunk : 0);
+            // target operands: four planes (k4: three) of 16 bytes per target
+            bb = targets * (k4 ? 48 : 64);
+            const int fixed = 3 * row * (npad + chunk) + 128 + 512 + 16 + (alias ? 0 : part) + 1024;
+            // what fits, in the order of what it saves: target operands in a table
+            // (several waves share each task), the sums' tables apart (else the
+            // transition one is rebuilt each iteration), a window buffer of 4096
+            // values (else 2048; also the histogram of a range or radix pass)
+            for (int choice = 0; choice < 8 && !fits; ++choice) {
+                b_table = !(choice & 4);
+                ms_shared = alias || (choice & 2);
+                win_cap = alias || (choice & 1) ? 2048 : 4096;
+                if (b_table && !split) continue;
+                sums = ms_shared ? (vb > mb ? vb : mb) : vb + mb;
+                if (alias && sums < part) sums = part;
+                if (sums < rows) sums = rows;
+                off_ms = ms_shared ? 0 : vb;
+                fits = fixed + sums + (b_table ? bb : 0) + 4 * win_cap <= kMfmaLdsBytes;
+            }
+            if (fits || k4 || alias || chunks >= max_chunks) break;
         }
         int o = 0;
         off_x = o; o += 3 * row * npad;
-        off_vt = o; o += 3 * row * nppad;
+        off_vt = o; o += 3 * row * chunk;
         off_v = o;
-        off_ms = ms_shared ? o : o + vb;
+        off_ms += o;
         off_part = alias ? o : o + sums;
         o += sums + (alias ? 0 : part);
         off_b = o; o += b_table ? bb : 0;
@@ -312,6 +324,7 @@ struct MfmaLds {
         off_ones = o; o += 16;
         total = o;
     }
+    static constexpr int kMaxChunks = 8;
     static constexpr int kMfmaLdsBytes = 160 * 1024 - 256;  // less the persistent kernels' static words
 };
 
@@ -1034,7 +1047,7 @@ using ConstStepArgs = const __attribute__((address_space(4))) StepArgs<float>;
 // Thread tid owns particles tid + ts nt: it keeps their scores in registers
 // from the score pass to the bandwidth, and moves them.  In the passes a wave
 // covers a task of 64 targets, one per lane once its sums are collected.
-template <int KIND, int D, int TS, bool SPLIT, bool COOP = false>
+template <int KIND, int D, int TS, bool SPLIT, bool COOP = false, bool CHUNKED = false>
 __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const int b, const CoopArgs cx = CoopArgs{})
 {
     const StepArgs<float> &a = *(const StepArgs<float> *)ap;
@@ -1043,6 +1056,7 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
     static_assert(D <= 7, "component 7 carries the norms");
     extern __shared__ __align__(16) unsigned char smem[];
     static_assert(!COOP || (SPLIT && TS == 1), "the multi-workgroup mode splits the sources");
+    static_assert(!CHUNKED || (TS == 1 && !COOP), "chunks: one task a wave, one workgroup");
     // d <= 3: rows of four components, one MFMA per tile instead of two
     constexpr bool K4 = D <= 3;
     constexpr int NC = K4 ? 4 : 8;      // components of a table row
@@ -1053,8 +1067,8 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
     constexpr int QT = SPLIT ? 2 : 4;   // 16-target tiles of a task
     constexpr int kTask = 16 * QT;
     const int npad0 = (n + 63) / 64 * 64;
-    const MfmaLds L(D, n, np, (int)(blockDim.x >> 6), COOP ? npad0 / G : 0);
-    const int npad = L.npad, nppad = L.nppad;
+    const MfmaLds L(D, n, np, (int)(blockDim.x >> 6), COOP ? npad0 / G : 0, CHUNKED ? MfmaLds::kMaxChunks : 1);
+    const int npad = L.npad, chunk = L.chunk;   // (chunk: every source but for CHUNKED)
     float *PART = (float *)(smem + L.off_part); // [ns_max][targets][kPart] partial sums of the splits
     // the workgroup's targets: particles [tbase, tbase + ntl) (all of them outside COOP)
     const int tbase = gi * L.ntasks * kTask;
@@ -1128,30 +1142,35 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
     float mmax[D];
 #pragma unroll
     for (int c = 0; c < D; ++c) mmax[c] = 0.f;
-    for (int j = tid; j < nppad; j += nt) {
-        float row[NC];
+    // the table of the sources from `first` on
+    auto build_vt = [&](int first) {
+        for (int r = tid; r < chunk; r += nt) {
+            const int j = first + r;
+            float row[NC];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) row[c] = 0.f;
-        row[kLast] = kNoSource;
-        if (j < np) {
-            float xp[D], mu[D];
+            for (int c = 0; c < NC; ++c) row[c] = 0.f;
+            row[kLast] = kNoSource;
+            if (j < np) {
+                float xp[D], mu[D];
 #pragma unroll
-            for (int q = 0; q < D; ++q) xp[q] = xprev[(long)j * D + q];
-            F::mean(m, a.t, xp, mu);
-            float nrm = 0.f;
+                for (int q = 0; q < D; ++q) xp[q] = xprev[(long)j * D + q];
+                F::mean(m, a.t, xp, mu);
+                float nrm = 0.f;
 #pragma unroll
-            for (int c = 0; c < D; ++c) {
-                const float mh = (mu[c] - ref[c]) * rs[c];
-                row[c] = 2.f * mh;
-                mmax[c] = fmax_(mmax[c], fabsf(row[c]));
-                nrm += mh * mh;
+                for (int c = 0; c < D; ++c) {
+                    const float mh = (mu[c] - ref[c]) * rs[c];
+                    row[c] = 2.f * mh;
+                    mmax[c] = fmax_(mmax[c], fabsf(row[c]));
+                    nrm += mh * mh;
+                }
+                const float lw = a.log_w ? a.log_w[(long)b * a.log_w_stride + j] : -R::log_((float)np);
+                const float cj = lw * (float)kLog2e - nrm;
+                row[kLast] = cj < kNoSource ? kNoSource : cj;
             }
-            const float lw = a.log_w ? a.log_w[(long)b * a.log_w_stride + j] : -R::log_((float)np);
-            const float cj = lw * (float)kLog2e - nrm;
-            row[kLast] = cj < kNoSource ? kNoSource : cj;
+            put_row<K4>(smem, L.off_vt, chunk, r, row);
         }
-        put_row<K4>(smem, L.off_vt, nppad, j, row);
-    }
+    };
+    for (int ch = 0; ch < (CHUNKED ? L.chunks : 1); ++ch) build_vt(ch * chunk);
     // scales of the f16 pieces, from the largest magnitude of each component of
     // a wave's values
     auto note_max = [&](const float (&v)[D], int slot) {
@@ -1166,22 +1185,25 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
     if (tid < D) redf[32 + tid] = f16_scale(__uint_as_float(red[16 + tid]), 15);
     __syncthreads();
     // the sums' table of the transition means, from its rows
-    auto build_ms = [&](bool first) {
-        for (int j = tid; j < nppad; j += nt) {
+    auto build_ms = [&](bool first, int from) {
+        for (int j = tid; j < chunk; j += nt) {
             PieceRow<K4> p;
-            p.load(smem, L.off_vt, nppad, j);
+            p.load(smem, L.off_vt, chunk, j);
             float v[D];
             bool tiny = false;
 #pragma unroll
             for (int c = 0; c < D; ++c) {
                 v[c] = p.at(c) * ms_scale[c];
-                tiny |= first && many_tiny(v[c], min(kWave, np - (j & ~(kWave - 1))));  // (pads are zero)
+                tiny |= first && many_tiny(v[c], min(kWave, max(np - from - (j & ~(kWave - 1)), 0)));  // (pads are zero)
             }
             if (tiny) red[12] = kDirect;
             put_sum_row<D>(smem, L.off_ms, j, v, 1.f);
         }
     };
-    build_ms(true);
+    for (int ch = 0; ch < (CHUNKED ? L.chunks : 1); ++ch) {
+        if (CHUNKED) build_vt(ch * chunk);  // (a thread's rows are its own in both tables)
+        build_ms(true, ch * chunk);
+    }
     const int ntl = L.ntasks * kTask;
     // score operand of particle i (at its place in a row), where it is one of
     // the workgroup's targets and they are kept
@@ -1232,9 +1254,17 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
         for (int c = 0; c < D; ++c) {
             float part = 0.f;
             for (int j = tid; j < np; j += nt) {
-                PieceRow<K4> p;
-                p.load(smem, L.off_vt, nppad, j);
-                part += p.at(c) * half_irs[c];
+                if constexpr (CHUNKED) {
+                    float xp[D], mu[D];
+#pragma unroll
+                    for (int q = 0; q < D; ++q) xp[q] = xprev[(long)j * D + q];
+                    F::mean(m, a.t, xp, mu);
+                    part += mu[c] - ref[c];
+                } else {
+                    PieceRow<K4> p;
+                    p.load(smem, L.off_vt, chunk, j);
+                    part += p.at(c) * half_irs[c];
+                }
             }
             part = wave_sum(part);
             if (lane == 0) redf[wave] = part;
@@ -1369,6 +1399,7 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
     };
     // score_sums on the vector ALU, whatever the logits' magnitude: the
     // exponentials stay in FP32, relative to the largest logit so far
+    int first_source = 0;   // of the tables
     auto score_direct = [&](int kbase, int blk0, int blk1, float &nref, float (&os)[NC]) {
         float xs[D], mx = kNoSource, sum = 0.f, acc[D];
         target_x(kbase + (fresh_tid() & (kTask - 1)), xs);
@@ -1377,10 +1408,10 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
             xs[c] *= rs[c];
             acc[c] = 0.f;
         }
-        const int j1 = min(32 * blk1, np);
+        const int j1 = min(32 * blk1, np - first_source);
         for (int j = 32 * blk0; j < j1; ++j) {
             PieceRow<K4> p;
-            p.load(smem, L.off_vt, nppad, j);
+            p.load(smem, L.off_vt, chunk, j);
             float logit = p.at(kLast);
 #pragma unroll
             for (int c = 0; c < D; ++c) logit += p.at(c) * xs[c];
@@ -1402,7 +1433,7 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
         const int lane = fresh_tid() & 63, g = lane >> 4, col = lane & 15;
         u32x4 b0[QT], b1[QT];
         SourceRows<K4> src;
-        src.init(smem, L.off_vt, nppad, L.off_ones, g, col);
+        src.init(smem, L.off_vt, chunk, L.off_ones, g, col);
 #pragma unroll
         for (int q = 0; q < QT; ++q) {
             const float cst = have_ref ? __shfl(nref, 16 * q + col, kWave) : 0.f;
@@ -1677,10 +1708,34 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
         // (1) scores
         float os[NC], sref = 0.f;
         const int sp = SPLIT ? wave / ntasks : 0;
+        if constexpr (CHUNKED) {
+            // chunk by chunk, each relative to its own largest logit; the sums so
+            // far move to the larger reference
+            float tot[NC], tref = kNoSource;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) tot[c] = 0.f;
+            for (int ch = 0; a.trans_mode == 0 && ch < L.chunks; ++ch) {
+                first_source = ch * chunk;
+                __syncthreads();
+                build_vt(first_source);
+                build_ms(false, first_source);
+                __syncthreads();
+                const int nb = chunk / 32;
+                if (sp >= L.ns_sc) continue;
+                score_sums(tbase + wave % ntasks * kTask, sp * nb / L.ns_sc, (sp + 1) * nb / L.ns_sc, negref[0], os, sref);
+                const float top = fmax_(tref, sref), w0 = R::exp2_(tref - top), w1 = R::exp2_(sref - top);
+#pragma unroll
+                for (int c = 0; c < NC; ++c) tot[c] = tot[c] * w0 + os[c] * w1;
+                tref = top;
+            }
+#pragma unroll
+            for (int c = 0; c < NC; ++c) os[c] = tot[c];
+            sref = tref;
+        }
         if constexpr (SPLIT) {
             // this wave's split of its task's sources
-            if (a.trans_mode == 0 && sp < L.ns_sc) {
-                const int nb = nppad / 32;
+            if (!CHUNKED && a.trans_mode == 0 && sp < L.ns_sc) {
+                const int nb = chunk / 32;
                 score_sums(tbase + wave % ntasks * kTask, sp * nb / L.ns_sc, (sp + 1) * nb / L.ns_sc, negref[0], os, sref);
             }
         } else {
@@ -1688,7 +1743,7 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
             for (int ts = 0; ts < TS; ++ts) {
                 const int task = wave + ts * nwaves;
                 if (task >= ntasks) break;
-                if (a.trans_mode == 0) score_sums(task * kTask, 0, nppad / 32, negref[ts], os, sref);
+                if (!CHUNKED && a.trans_mode == 0) score_sums(task * kTask, 0, chunk / 32, negref[ts], os, sref);
                 const int k = task * kTask + (fresh_tid() & 63);
                 if (k < n) {
                     float xt[D];
@@ -1698,7 +1753,7 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
                 }
             }
         }
-        have_ref = true;
+        have_ref = !CHUNKED;
 
         // (2) the bandwidth needs the exact lower median of the squared
         // distances of the current particles: their window pass
@@ -2017,9 +2072,32 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
             }
         }
         // the sums' tables share their region where LDS is short
-        if (L.ms_shared) build_ms(false);
+        if (!CHUNKED && L.ms_shared) build_ms(false, 0);
         __syncthreads();
     }
+
+    // rows [mh_j, phi_{t-1}(j)] of the forward recursion over the sums' tables
+    // (dead by now; chunks: from the previous particles, over every table of
+    // theirs), before the particles are written, which may take the previous
+    // ones' place
+    float *VF = (float *)(smem + (CHUNKED ? L.off_vt : L.off_v));
+    for (int j = tid; a.do_viterbi && j < np; j += nt) {
+        if constexpr (CHUNKED) {
+            float xp[D], mu[D];
+#pragma unroll
+            for (int c = 0; c < D; ++c) xp[c] = xprev[(long)j * D + c];
+            F::mean(m, a.t, xp, mu);
+#pragma unroll
+            for (int c = 0; c < kLast; ++c) VF[j * NC + c] = c < D ? (mu[c < D ? c : 0] - ref[c < D ? c : 0]) * rs[c] : 0.f;
+        } else {
+            PieceRow<K4> p;
+            p.load(smem, L.off_vt, chunk, j);
+#pragma unroll
+            for (int c = 0; c < kLast; ++c) VF[j * NC + c] = 0.5f * p.at(c);
+        }
+        VF[j * NC + kLast] = a.phi_prev ? a.phi_prev[(long)b * a.phi_prev_stride + j] : 0.f;
+    }
+    __syncthreads();
 
     bool bad = false;
     const int i_lo = COOP ? tbase : 0, i_hi = COOP ? min(n, tbase + ntl) : n;
@@ -2035,16 +2113,6 @@ __device__ __forceinline__ void step_mfma_body(ConstStepArgs *const ap, const in
     }
 
     if (a.do_viterbi) {
-        // rows [mh_j, phi_{t-1}(j)] over the sums' tables (dead by now)
-        float *VF = (float *)(smem + L.off_v);
-        for (int j = tid; j < np; j += nt) {
-            PieceRow<K4> p;
-            p.load(smem, L.off_vt, nppad, j);
-#pragma unroll
-            for (int c = 0; c < kLast; ++c) VF[j * NC + c] = 0.5f * p.at(c);
-            VF[j * NC + kLast] = a.phi_prev ? a.phi_prev[(long)b * a.phi_prev_stride + j] : 0.f;
-        }
-        __syncthreads();
         for (int i = i_lo + tid; i < i_hi; i += nt) {
             float xs[D], xa[D];
             PieceRow<K4> p;
@@ -2095,10 +2163,10 @@ __device__ __forceinline__ ConstStepArgs *kernel_args()
     return (ConstStepArgs *)__builtin_amdgcn_kernarg_segment_ptr();
 }
 
-template <int KIND, int D, bool SPLIT>
+template <int KIND, int D, bool SPLIT, bool CHUNKED = false>
 __global__ __launch_bounds__(kMaxWaves * 64) void k_step_mfma(StepArgs<float> a)
 {
-    step_mfma_body<KIND, D, kMaxParticles / 64 / kMaxWaves, SPLIT>(kernel_args(), blockIdx.x);
+    step_mfma_body<KIND, D, kMaxParticles / 64 / kMaxWaves, SPLIT, false, CHUNKED>(kernel_args(), blockIdx.x);
 }
 
 // Multi-workgroup step: workgroup blockIdx.x is group blockIdx.x % G of
