@@ -225,13 +225,35 @@ __global__ __launch_bounds__(1024) void k_step_small(StepArgs<T> a)
     const ObsBits mk{__builtin_amdgcn_ballot_w64(on)};
 
     // particles and means relative to the first previous particle's
-    // transition mean, as in k_step
+    // transition mean, as in k_step; in FP32 iterations to the mean of all of
+    // them (every wave forms it), as in the matrix-core step: a particle is
+    // rounded at every move, by its distance from the centre (rms error after 50
+    // iterations of 64 particles of the clutter model, over the displacement:
+    // 8.3e-6 about the first one, 6.2e-6 in the matrix-core step)
     T cen[D], rs[D], irs[D];
     {
         T xp[D];
 #pragma unroll
         for (int c = 0; c < D; ++c) xp[c] = xprev[c];
         F::mean(m, a.t, xp, cen);
+    }
+    if (sizeof(T) == 4 && a.n_iter > 0) {
+        T off[D];
+#pragma unroll
+        for (int c = 0; c < D; ++c) off[c] = (T)0;
+        for (int j = lane; j < np; j += kWave) {
+            T xp[D], mu[D];
+#pragma unroll
+            for (int c = 0; c < D; ++c) xp[c] = xprev[(long)j * D + c];
+            F::mean(m, a.t, xp, mu);
+#pragma unroll
+            for (int c = 0; c < D; ++c) off[c] += mu[c] - cen[c];
+        }
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+            const T at = cen[c] + wave_sum(off[c]) / (T)np;
+            cen[c] = R::finite(at) ? at : cen[c];
+        }
     }
 #pragma unroll
     for (int c = 0; c < D; ++c) {
