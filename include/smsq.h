@@ -186,14 +186,22 @@ smsq_status_t smsq_workspace_size(smsq_model_t model, smsq_dtype_t dtype, int ba
  * do not fit one compute unit's LDS.
  * Kernel choice (also for smsq_batch_step, smsq_run_batch and
  * smsq_run_sequence): up to 64 particles and 128 previous ones, in batches
- * of up to 256 sequences (some shapes 512), a small-set kernel with sixteen
- * lanes a particle; in larger batches of up to 32 particles (FP32 states of
- * one or two dimensions: 40) and at most 64 previous ones, a one-wave kernel
- * with the particles in registers;
+ * of up to one sequence a compute unit (256; some shapes two), a small-set
+ * kernel with sixteen lanes a particle.  It leaves out FP32 RBF states of 5 to 7
+ * dimensions above 48 particles, and the 14-D model up to 32 particles after at
+ * most 64 (in FP64; in FP32 in batches of more than half a sequence a compute
+ * unit).  Of the rest, up to 32 particles (FP32 states of one or two
+ * dimensions: 40) after at most 64 take a one-wave kernel with the particles in
+ * registers;
  * otherwise FP32 with the RBF kernel, d <= 7 and up to 1024 particles runs
- * on the matrix cores, and FP64, the IMQ and Matern kernels, d > 7 or more
- * than 1024 particles on the workgroup vector-ALU kernel.  opts->step_kernel
- * forces one of them wherever it fits; results agree to rounding. */
+ * on the matrix cores, after up to 2688 (1024 particles) to 2944 (64) previous
+ * ones of d <= 3 and 3264 to 4128 of more dimensions (in chunks where they do not
+ * fit LDS at once), and FP64, the IMQ and Matern kernels, d > 7 or more particles
+ * on the workgroup vector-ALU kernel.
+ * opts->step_kernel forces one of them wherever it fits; results agree to
+ * rounding.  The choice depends on the batch, so a sequence's results agree
+ * from one batch size to another, or for a batch taken in parts with
+ * seq_offset, to rounding only, unless step_kernel names the kernel. */
 smsq_status_t smsq_svgd_step(smsq_model_t model, smsq_dtype_t dtype, int t,
                              int n_prev, const void *x_prev, const void *log_w_prev,
                              const void *z_t, const uint8_t *z_mask,

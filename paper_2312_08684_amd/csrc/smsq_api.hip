@@ -289,13 +289,15 @@ smsq_status_t launch_small_kd(const StepArgs<T> &a, int batch, hipStream_t s)
     return hipGetLastError() == hipSuccess ? SMSQ_OK : SMSQ_ERR_HIP;
 }
 
+int device_cus();
+
 // The small-set kernel takes what fits it by default while the batch's
-// workgroups are all on the chip, or nearly: 256, one a compute unit; 512 of up
-// to 24 particles (eight waves, two a unit) and four dimensions; 512 where the
-// workgroup vector-ALU kernel is the other one (IMQ and Matern kernels, FP32 of
-// fewer than 32 particles after more than 64, and FP64 up to the 45 particles
-// whose distances the selection holds in registers or two dimensions).
-// Measured there (50 iterations; time of the kernel that takes the step
+// workgroups are all on the chip, or nearly: one a compute unit; two of up to 24
+// particles (eight waves each) and four dimensions, and two where the workgroup
+// vector-ALU kernel is the other one (IMQ and Matern kernels, FP32 of fewer than
+// 32 particles after more than 64, and FP64 up to the 45 particles whose
+// distances the selection holds in registers or two dimensions).
+// Measured on 256 compute units (50 iterations; time of the kernel that takes the step
 // otherwise / this one's): 1.15 to 5 at 1, 64 and 256 sequences of 10 to 64
 // particles of every family and both precisions, 1.1 to 3.0 at 512.  Beyond,
 // its sixteen lanes a particle cost more than they hide: 0.7 at 512 sequences
@@ -312,8 +314,9 @@ bool use_small(const smsq_model_desc_t &d, int n, int n_prev, int batch, int ker
     const bool no_wave = n > kWaveDefaultMax || n_prev > kWaveMaxParticles;
     const bool valu_else = (kernel != 0 || !fp32 || n < kMfmaMinParticles) && no_wave && d.d <= 7 &&
                            (fp32 || n <= 45 || d.d <= 2);
-    if (batch > ((n <= 24 && d.d <= 4) || valu_else ? 512 : 256)) return false;
-    if (d.d > 7 && n <= 32 && n_prev <= kWaveMaxParticles) return fp32 && batch <= 128;
+    const int cus = device_cus();
+    if (batch > ((n <= 24 && d.d <= 4) || valu_else ? 2 * cus : cus)) return false;
+    if (d.d > 7 && n <= 32 && n_prev <= kWaveMaxParticles) return fp32 && batch <= cus / 2;
     return !(fp32 && kernel == 0 && d.d > 4 && d.d <= 7 && n > 48);
 }
 
@@ -725,15 +728,19 @@ int device_cus()
 // target tasks (k_step_mfma_coop): G is the largest power of two that
 // divides the sequence's 64-particle tasks with batch * G within the
 // compute units (1: the one-workgroup kernels).  Below 512 particles an
-// SVGD iteration of one workgroup (19 us at 256 particles) is too short for
-// the two barriers and exchanges per iteration to pay.  Time of one workgroup a
-// sequence / of G (50 iterations, range, clutter and arm models): 512 particles
-// 1.5 for one sequence, 1.1 to 1.2 for 16, 0.7 to 0.85 for 32 and 64, which
-// therefore stay on one; 640 1.2 to 1.3 up to 32, 1.04 to 1.08 for 64; 768 1.8
-// to 1.9 and 1.04 to 1.07; 1024 3.3 for one sequence, 2.0 for 16, 1.4 for 64.
-// Families of the matrix-core drivers with a multi-workgroup kernel: growth,
+// SVGD iteration of one workgroup (17 us at 256 particles) is too short for
+// the two barriers and exchanges per iteration to pay.  Above, one workgroup's
+// iteration grows with n^2 and the barriers with the part of the chip that
+// takes part, batch * G of its compute units, so the several workgroups need
+// n^2 of at least kCoopPairs times that part.  Time of one workgroup a
+// sequence / of G (50 iterations, range, clutter and arm models; the part in
+// brackets): 512 particles 1.5 for one sequence, 1.1 to 1.2 for 16 (1/2), 0.7
+// to 0.85 for 32 and 64 (1); 640 1.2 to 1.3 up to 32 (1/4), 1.04 to 1.08 for 64
+// (1/2); 768 1.8 to 1.9 and 1.04 to 1.07 for 64 (1); 1024 3.3 for one sequence,
+// 2.0 for 16 (1), 1.4 for 64 (1).  Families of the matrix-core drivers with a multi-workgroup kernel: growth,
 // range-only, clutter, arm.
 constexpr int kCoopMinParticles = 512;
+constexpr long kCoopPairs = 1L << 19;
 bool coop_family(int kind)
 {
     return kind == SMSQ_MODEL_GROWTH1D || kind == SMSQ_MODEL_RANGE2D || kind == SMSQ_MODEL_CV4D ||
@@ -748,9 +755,9 @@ int coop_groups(smsq_dtype_t dt, const smsq_model_desc_t &d, int batch, int n, b
     const int ntasks = (n + 63) / 64;
     if (ntasks * 64 > kMaxParticles) return 1;
     if (!force && (n < kCoopMinParticles || 4L * batch > device_cus())) return 1;
-    if (!force && ntasks <= 8 && 16L * batch > device_cus()) return 1;
     int G = 1;
     while (2 * G <= ntasks && ntasks % (2 * G) == 0 && (long)batch * 2 * G <= device_cus()) G *= 2;
+    if (!force && (long)n * n * device_cus() < kCoopPairs * batch * G) return 1;
     if (G > 1 && (MfmaLds(d.d, n, n, kMaxWaves, ntasks * 64 / G).total > MfmaLds::kMfmaLdsBytes ||
                   MfmaLds(d.d, n, 1, kMaxWaves, ntasks * 64 / G).total > MfmaLds::kMfmaLdsBytes))
         return 1;
