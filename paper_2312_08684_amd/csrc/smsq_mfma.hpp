@@ -863,8 +863,11 @@ __device__ float window_select(const float *buf, uint32_t n, uint32_t r, float l
 // of the arm, where nine tiles in ten then held one) and missed 1%.
 // Without a prediction, or when the window misses the rank or overflows,
 // histogram passes over the distances narrow the range to one of few enough
-// values (MedianRange).  All passes see the same distances, so the result is
-// the same exact lower median whichever ran.
+// values (MedianRange).  The result is the exact lower median of the distances
+// as the pass that ran rounds them: the window's pass subtracts lo within the
+// products' sum, the others nothing, so the median may differ in its last bits
+// with the path taken, and that with the buffer's capacity (workgroup shape,
+// multi-workgroup mode).
 constexpr int kWinTarget = 128;
 constexpr int kMaxHistPasses = 4;
 struct MedianTracker {
