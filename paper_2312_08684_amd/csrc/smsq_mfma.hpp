@@ -50,10 +50,10 @@
 // model 2.2e-7 -> 1.9e-7.
 // Measured (us an SVGD iteration of 256 sequences; FP32 MFMA -> here): 1024
 // particles of the arm 240 -> 145, 512 of the clutter model 70 -> 45, 256 of the
-// range model 21 -> 17.  What bounds it now is
-// vector issue at 1024 (active in 74% of the cycles: exponentials and operand
-// splits, 10.5 vector instructions per 64 pairs beside matrix units busy 37%)
-// and, below 512, the serial stages between barriers.
+// range model 21 -> 17.  What bounds it now is vector issue at 1024 (active in 74%
+// of the cycles: exponentials, operand splits and block sums, 11.8 vector
+// instructions per 64 pairs of both passes, beside matrix units busy 37%) and,
+// below 512, the serial stages between barriers.
 //
 // Operand layouts of the 16x16x32 MFMA (checked on gfx950): lane l gives
 // A[l % 16][8 (l / 16) + j] and B[8 (l / 16) + j][l % 16], j = 0..7; result
@@ -207,9 +207,10 @@ constexpr float kKapScale = 8.f;
 // rounding of their difference reaches 0.5 in the exponent there (2^-21 of
 // beta |x|^2, the same for serial, truncating and single-rounding sums) and 13
 // at 2^25, where an f16 piece of 2^3 kappa overflows and its sums are NaN.  Sets
-// beyond (tight clouds far from their transition means, a particle
-// far from all others, a small bw_scale) take their differences directly, on
-// the vector ALU.
+// beyond (tight clouds far from their transition means, a particle far from all
+// others, a small bw_scale) take their differences directly, on the vector ALU (us
+// an iteration of 256 sequences, products and differences: 256 of the range model
+// 17 and 36, 512 of the clutter model 45 and 166, 1024 of the arm 146 and 478).
 constexpr float kMaxProductExponent = 1048576.f;  // 2^20
 // Scales of the sums' vectors, a power of two for each component, bring the
 // largest value to 2^13 .. 2^14 when they are set, and stay until a value
