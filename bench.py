@@ -53,9 +53,10 @@ C_OBS = {"growth1d": 10, "range2d": 60, "cv4d": 150, "arm7": 1100, "lingauss": 1
 
 def executed_matrix_flops(n: int, n_prev: int, d: int) -> float:
     """16-bit matrix-core flops of one iteration of the matrix-core step: a
-    16x16x32 product is 64 flops per pair, three of them per pair of the score
-    and Stein passes and two per distance (d <= 3: two and one)."""
-    p, w = (3, 2) if d > 3 else (2, 1)
+    16x16x32 product is 64 flops per pair of a tile and 32 per pair of a sum; two
+    products a tile (d <= 3: one) and three a sum (d <= 4: two) in the score and
+    Stein passes, and those of a tile per distance."""
+    p, w = (3.5 if d > 4 else 3, 2) if d > 3 else (2, 1)
     return 64.0 * (p * n * n_prev + p * n * n + w * n * n / 2)
 
 
